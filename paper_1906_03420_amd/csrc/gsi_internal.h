@@ -250,16 +250,24 @@ void fill_u64(gsi_ctx *c, uint64_t *p, uint64_t value, uint64_t n);
 // `total` is given the sum is also written there (device memory).
 void exclusive_scan(gsi_ctx *c, const uint32_t *in, uint64_t n, uint64_t *out, Scratch &s,
                     uint64_t *total = nullptr);
-// Stable LSD radix sort of `n` tuples held in `na` parallel uint32 arrays
-// (a[0..na-1]); pass p orders by bits [shift, shift+8) of array key_arr[p].
-// tmp holds na arrays of n entries.  Returns true if the result ended in tmp
-// (the caller swaps pointers).
+// Stable sort of n 64-bit keys by their bits [lo, hi).  Returns true if the
+// result ended in tmp.
+bool key_sort(gsi_ctx *c, uint32_t n, uint64_t *a, uint64_t *tmp, int lo, int hi, Scratch &s);
+// The directed entries of m > 0 edges (both directions) packed as label,
+// source, destination (vb bits an end), sorted by source, then destination.
+// Returns true if the result ended in tmp.
+bool edge_key_sort(gsi_ctx *c, uint32_t m, const uint32_t *src, const uint32_t *dst, const uint32_t *el, int vb,
+                   uint64_t *a, uint64_t *tmp, Scratch &s);
+// Stable LSD radix sort of n triples held in 3 parallel uint32 arrays; pass
+// p orders by bits [shift, shift+8) of array key_arr[p].  tmp holds 3 arrays
+// of n entries.  Returns true if the result ended in tmp (the caller swaps
+// pointers).
 struct SortPass {
     int key_arr;
     int shift;
 };
-bool radix_sort(gsi_ctx *c, uint32_t n, int na, uint32_t *const *a, uint32_t *const *tmp,
-                const std::vector<SortPass> &passes, Scratch &s);
+bool radix_sort(gsi_ctx *c, uint32_t n, uint32_t *const *a, uint32_t *const *tmp, const std::vector<SortPass> &passes,
+                Scratch &s);
 
 // --------------------------------------------------------------- pieces
 // d_vlabel: one label per vertex; for a multi-labelled graph (g->multi) it
