@@ -703,8 +703,8 @@ __global__ __launch_bounds__(QT) void k_tile_rows(const uint64_t *F, uint64_t R,
     if (i == R - 1) tile_row[ntiles] = R - 1;
 }
 
-void tile_rows(gsi_ctx *c, const uint64_t *F, uint64_t R, uint64_t ntiles, uint64_t *tile_row) {
-    launch(c, "k_tile_rows", 8.0 * (R + 1) + 8.0 * (ntiles + 1), k_tile_rows, nblocks(R), QT, F, R, ntiles, (uint32_t)QT,
+void tile_rows(gsi_ctx *c, const uint64_t *F, uint64_t R, uint64_t ntiles, uint32_t ts, uint64_t *tile_row) {
+    launch(c, "k_tile_rows", 8.0 * (R + 1) + 8.0 * (ntiles + 1), k_tile_rows, nblocks(R), QT, F, R, ntiles, ts,
            tile_row);
 }
 

@@ -7,14 +7,17 @@
 //   k_wlocate one thread per global row: N(v, l) for every linking edge of
 //             the row's own query; bound = |N(v', l0)|
 //   scan      F over all rows -> one global slot space [0, |GBA|)
-//   k_wjoin   256-slot tiles over the global slots: the same tests as the
-//             single-query join, with each slot's query found from its row
+//   k_wjoin   groups of 256-slot tiles over the global slots: the same tests
+//             as the single-query join, with each slot's query found from
+//             its row; survivors as (element, row) records per group
 //   scan      survivor offsets; k_wsurv turns them into each query's first
 //             and last survivor, so every query's next table gets its exact
 //             size (host readback)
-//   k_wlink   (m_i, x) into the query's own next table, or, at a query's
-//             last level, its rows in query-vertex order plus each row's
-//             hash (digest summed per query by k_wdigest)
+//   k_wlink   a thread per survivor: (m_i, x) into the query's own next
+//             table, or, at a query's last level, its rows in query-vertex
+//             order, the rows' hashes summed per query
+// When 8 bytes per slot do not fit the arena comfortably the join writes a
+// keep bit per slot instead, and k_wlink_bits works on slot groups.
 // Slots of a query are contiguous and ordered by its rows, so each query's
 // result, row order included, equals the single-query path's.
 #include <algorithm>
@@ -187,7 +190,7 @@ template <uint32_t TPW>
 __global__ __launch_bounds__(WT) void k_wjoin(const WQ *qs, const uint32_t *rowq, const WEdge *edges,
                                              const uint32_t *ci_all, const uint64_t *F, const uint64_t *tile_row,
                                              uint64_t ntiles, uint64_t gba, const uint32_t *loc, uint64_t *bitmap,
-                                             uint32_t *tile_cnt) {
+                                             uint32_t *rec_x, uint32_t *rec_r, uint32_t *tile_cnt) {
     __shared__ uint64_t s_F[(TPW * WT)];
     __shared__ uint32_t s_st[(TPW * WT)];
     __shared__ uint32_t s_row[(TPW * WT)];  // row (from r_lo) of each slot, staged groups
@@ -199,9 +202,10 @@ __global__ __launch_bounds__(WT) void k_wjoin(const WQ *qs, const uint32_t *rowq
     __shared__ uint16_t s_slot[(TPW * WT)]; // and their slots in the group
     __shared__ uint64_t s_keep[(TPW * WT) / 64];
     __shared__ uint32_t s_n;
-    const uint64_t t0 = (uint64_t)blockIdx.x * TPW;
-    const uint64_t t1 = t0 + TPW < ntiles ? t0 + TPW : ntiles;
-    const uint64_t p0 = t0 * WT;
+    // tile_row and tile_cnt are kept per group with records, per tile without
+    const uint64_t t0 = (uint64_t)blockIdx.x * (rec_x ? 1 : TPW);
+    const uint64_t t1 = rec_x ? t0 + 1 : t0 + TPW < ntiles ? t0 + TPW : ntiles;
+    const uint64_t p0 = (uint64_t)blockIdx.x * (TPW * WT);
     const uint64_t r_lo = tile_row[t0], r_hi = tile_row[t1];
     const uint64_t nr = r_hi - r_lo + 1;
     const bool staged = nr <= (TPW * WT);
@@ -347,6 +351,28 @@ __global__ __launch_bounds__(WT) void k_wjoin(const WQ *qs, const uint32_t *rowq
         if (keep) atomicOr(&s_keep[slot >> 6], 1ull << (slot & 63));
     }
     __syncthreads();
+    if (rec_x) {
+        // the group's survivors as records in slot order (element, row from
+        // r_lo): every kept slot is among the compacted candidates
+        __shared__ uint32_t s_pre[(TPW * WT) / 64];
+        if (threadIdx.x < 64) {
+            const uint32_t c = threadIdx.x < (TPW * WT) / 64 ? (uint32_t)__popcll(s_keep[threadIdx.x]) : 0u;
+            const uint32_t inc = wave_inclusive_sum(c);
+            if (threadIdx.x < (TPW * WT) / 64) s_pre[threadIdx.x] = inc - c;
+            if (threadIdx.x == 63) tile_cnt[blockIdx.x] = inc;
+        }
+        __syncthreads();
+        for (uint32_t e = threadIdx.x; e < n; e += WT) {
+            const uint32_t sl = s_slot[e];
+            const uint64_t word = s_keep[sl >> 6];
+            if ((word >> (sl & 63)) & 1ull) {
+                const uint64_t q = p0 + s_pre[sl >> 6] + (uint32_t)__popcll(word & ((1ull << (sl & 63)) - 1));
+                rec_x[q] = s_x[e];
+                rec_r[q] = s_r[e];
+            }
+        }
+        return;
+    }
     // per 256-slot tile: its WT/64 bitmap words and their count
     if (threadIdx.x < 64) {
         const uint32_t tk = threadIdx.x / (WT / 64);  // tile of the group
@@ -373,15 +399,38 @@ __device__ __forceinline__ uint64_t survivors_before(const uint64_t *bitmap, con
     return r;
 }
 
+// survivors of rows before r, p being the first slot of row r: those of the
+// groups before p's and the records of p's group with an earlier row (rows
+// ascend within a group)
+__device__ __forceinline__ uint64_t records_before(const uint32_t *rec_r, const uint64_t *tile_row,
+                                                   const uint64_t *tile_off, uint64_t ngroups, uint32_t group,
+                                                   uint64_t p, uint64_t r) {
+    const uint64_t g = p / group;
+    if (g >= ngroups) return tile_off[ngroups];
+    uint32_t lo = 0, hi = (uint32_t)(tile_off[g + 1] - tile_off[g]);
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (tile_row[g] + rec_r[g * group + mid] < r) lo = mid + 1;
+        else hi = mid;
+    }
+    return tile_off[g] + lo;
+}
+
 // per query: first survivor, end of its survivors, first slot, end of slots
 __global__ __launch_bounds__(WT) void k_wsurv(const WQ *qs, uint32_t nq, const uint64_t *F, const uint64_t *bitmap,
-                                             const uint64_t *tile_off, uint64_t gba, uint64_t *sb) {
+                                             const uint32_t *rec_r, const uint64_t *tile_row, uint64_t ntiles,
+                                             uint32_t group, const uint64_t *tile_off, uint64_t gba, uint64_t *sb) {
     const uint32_t q = blockIdx.x * WT + threadIdx.x;
     if (q >= nq) return;
     const WQ &Q = qs[q];
     const uint64_t f0 = F[Q.rbase], f1 = F[Q.rbase + Q.R];
-    sb[4 * (uint64_t)q] = survivors_before(bitmap, tile_off, gba, f0);
-    sb[4 * (uint64_t)q + 1] = survivors_before(bitmap, tile_off, gba, f1);
+    if (rec_r) {
+        sb[4 * (uint64_t)q] = records_before(rec_r, tile_row, tile_off, ntiles, group, f0, Q.rbase);
+        sb[4 * (uint64_t)q + 1] = records_before(rec_r, tile_row, tile_off, ntiles, group, f1, Q.rbase + Q.R);
+    } else {
+        sb[4 * (uint64_t)q] = survivors_before(bitmap, tile_off, gba, f0);
+        sb[4 * (uint64_t)q + 1] = survivors_before(bitmap, tile_off, gba, f1);
+    }
     sb[4 * (uint64_t)q + 2] = f0;
     sb[4 * (uint64_t)q + 3] = f1;
 }
@@ -390,7 +439,148 @@ __global__ __launch_bounds__(WT) void k_wsurv(const WQ *qs, uint32_t nq, const u
 // contiguous block when k is at most this
 constexpr uint32_t WLINK_STAGE_K = 16;
 
-// (m_i, x) of every survivor into its query's next table, or, at a query's
+// Digests: every query has WACC (sum, xor) accumulators, the workgroups
+// adding to them in turn, so that a query with many survivors does not have
+// all of them at one address.
+constexpr uint32_t WACC = 16;
+__device__ __forceinline__ void add_hash(unsigned long long *acc, uint32_t q, uint64_t sum, uint64_t xr) {
+    unsigned long long *a = acc + 2 * ((uint64_t)q * WACC + blockIdx.x % WACC);
+    atomicAdd(a, (unsigned long long)sum);
+    atomicXor(a + 1, (unsigned long long)xr);
+}
+__device__ __forceinline__ void add_hash(unsigned long long *acc, uint32_t q, uint64_t h) { add_hash(acc, q, h, h); }
+
+// one thread per query: its accumulators into dig[2q], dig[2q + 1]
+__global__ __launch_bounds__(WT) void k_wdigest(const uint64_t *acc, uint32_t nq, uint64_t *dig) {
+    const uint32_t q = blockIdx.x * WT + threadIdx.x;
+    if (q >= nq) return;
+    uint64_t sm = 0, xr = 0;
+#pragma unroll
+    for (uint32_t t = 0; t < WACC; t++) {
+        sm += acc[2 * ((uint64_t)q * WACC + t)];
+        xr ^= acc[2 * ((uint64_t)q * WACC + t) + 1];
+    }
+    dig[2 * (uint64_t)q] = sm;
+    dig[2 * (uint64_t)q + 1] = xr;
+}
+
+// The survivor's row of query Q (its row i of M, extended by x) into its
+// place: the next table, or at the last level the staged or direct result
+// row and, returned, its hash.  Values are loaded eight at a time, every load
+// issued before any is used (a column past the end re-reads a valid one).
+__device__ __forceinline__ uint64_t link_row(const WQ &Q, uint64_t i, uint32_t x, uint64_t pos, uint32_t *staged) {
+    if (!Q.final_level) {
+        for (uint32_t c = 0; c < Q.j; c += 8) {
+            uint32_t m[8];
+#pragma unroll
+            for (uint32_t t = 0; t < 8; t++) m[t] = Q.M[(uint64_t)(c + t < Q.j ? c + t : Q.j - 1) * Q.R + i];
+#pragma unroll
+            for (uint32_t t = 0; t < 8; t++)
+                if (c + t < Q.j) Q.Mn[(uint64_t)(c + t) * Q.S + pos] = m[t];
+        }
+        Q.Mn[(uint64_t)Q.j * Q.S + pos] = x;
+        return 0;
+    }
+    uint64_t f = 14695981039346656037ull;
+    for (uint32_t u0 = 0; u0 < Q.k; u0 += 8) {
+        uint32_t val[8];
+#pragma unroll
+        for (uint32_t t = 0; t < 8; t++) {
+            const uint32_t c = u0 + t < Q.k ? Q.qcol[u0 + t < GSI_MAX_K ? u0 + t : GSI_MAX_K - 1] : Q.j;
+            const uint32_t mv = Q.M[(uint64_t)(c < Q.j ? c : 0u) * Q.R + i];
+            val[t] = c < Q.j ? mv : x;
+        }
+#pragma unroll
+        for (uint32_t t = 0; t < 8; t++) {
+            const uint32_t u = u0 + t;
+            if (u >= Q.k) break;
+            if (staged) staged[u] = val[t];
+            else if (Q.out) Q.out[pos * Q.k + u] = val[t];
+            f = fnv_word(f, val[t]);
+        }
+    }
+    return mix64(f);
+}
+
+// The link over survivor records, a thread per survivor (grid over the
+// step's survivors, not its slots: one slot in 15 survives on a batch of
+// 1,024 queries over 10^6 vertices, and workgroups over 1,024 slots had a
+// quarter of their threads busy; there 1.24 -> 0.30 ms a step, digests
+// included 1.33 -> 0.30).  stile[b] is the group that holds survivor WT * b.  A workgroup
+// whose survivors are one query's reads that query's descriptor with scalar
+// loads, stages its last-level rows in LDS (ROWS) and adds one digest.
+template <bool ROWS>
+__global__ __launch_bounds__(WT) void k_wlink(const WQ *__restrict__ qs, const uint32_t *rowq,
+                                             const uint64_t *tile_row, const uint64_t *tile_off,
+                                             const uint64_t *stile, uint32_t group, const uint32_t *rec_x,
+                                             const uint32_t *rec_r, uint64_t S, unsigned long long *acc) {
+    __shared__ uint32_t s_q[2];
+    __shared__ uint64_t s_d[2][WT / 64];
+    __shared__ uint32_t s_rows[ROWS ? WT * WLINK_STAGE_K : 1];
+    const uint64_t s0 = (uint64_t)blockIdx.x * WT;
+    const uint32_t n = S - s0 < WT ? (uint32_t)(S - s0) : WT;  // survivors of the workgroup
+    const bool mine = threadIdx.x < n;
+    const uint64_t gpos = s0 + (mine ? threadIdx.x : 0u);
+    uint64_t g = stile[blockIdx.x];
+    uint64_t hi = stile[blockIdx.x + 1];
+    while (g < hi) {
+        const uint64_t mid = g + (hi - g + 1) / 2;
+        if (tile_off[mid] <= gpos) g = mid;
+        else hi = mid - 1;
+    }
+    const uint64_t at = g * group + (gpos - tile_off[g]);
+    const uint32_t x = rec_x[at];
+    const uint64_t r = tile_row[g] + rec_r[at];
+    const uint32_t qi = rowq[r];
+    if (threadIdx.x == 0) s_q[0] = qi;
+    if (threadIdx.x == n - 1) s_q[1] = qi;
+    __syncthreads();
+    const uint32_t q0 = __builtin_amdgcn_readfirstlane(s_q[0]), q1 = __builtin_amdgcn_readfirstlane(s_q[1]);
+    if (q0 != q1) {
+        // survivors of several queries
+        if (mine) {
+            const WQ &Q = qs[qi];
+            const uint64_t pos = gpos - Q.sbase;
+            if (pos < Q.S) {  // always, when the survivor ranges are consistent
+                const uint64_t h = link_row(Q, r - Q.rbase, x, pos, nullptr);
+                if (Q.final_level) add_hash(acc, qi, h);
+            }
+        }
+        return;
+    }
+    const WQ &Q = qs[q0];
+    const bool stage = ROWS && Q.final_level && Q.k <= WLINK_STAGE_K;
+    const uint64_t pos = gpos - Q.sbase;
+    uint64_t h = 0;
+    if (mine && pos < Q.S) h = link_row(Q, r - Q.rbase, x, pos, stage ? s_rows + threadIdx.x * Q.k : nullptr);
+    if (!Q.final_level) return;
+    const uint64_t sum = wave_sum(h), xr = wave_xor(h);
+    if (lane_id() == 0) {
+        s_d[0][threadIdx.x >> 6] = sum;
+        s_d[1][threadIdx.x >> 6] = xr;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t ts = 0, tx = 0;
+#pragma unroll
+        for (uint32_t t = 0; t < WT / 64; t++) {
+            ts += s_d[0][t];
+            tx ^= s_d[1][t];
+        }
+        add_hash(acc, q0, ts, tx);
+    }
+    if (stage) {
+        // the workgroup's rows are one contiguous block of the result
+        const uint64_t first = s0 - Q.sbase;
+        uint64_t end = first + n;
+        if (end > Q.S) end = Q.S;
+        const uint32_t nw = first < end ? (uint32_t)(end - first) * Q.k : 0u;
+        uint32_t *dst = Q.out + first * Q.k;
+        for (uint32_t v = threadIdx.x; v < nw; v += WT) dst[v] = s_rows[v];
+    }
+}
+
+// The same from keep bits, for steps whose records would not fit: (m_i, x) of every survivor into its query's next table, or, at a query's
 // last level, the row in query-vertex order and its hash.  A workgroup
 // takes the same WJ_TILES consecutive tiles as the join: their kept slots
 // are listed in slot order in LDS first, so that the waves that gather,
@@ -399,10 +589,10 @@ constexpr uint32_t WLINK_STAGE_K = 16;
 // binary search over the group's rows in LDS (survivors are often few, so
 // a map of every slot would not pay).
 template <uint32_t TPW>
-__global__ __launch_bounds__(WT) void k_wlink(const WQ *qs, const uint32_t *rowq, const uint32_t *ci_all,
+__global__ __launch_bounds__(WT) void k_wlink_bits(const WQ *qs, const uint32_t *rowq, const uint32_t *ci_all,
                                              const uint64_t *F, const uint64_t *tile_row, uint64_t ntiles,
                                              const uint32_t *loc, const uint64_t *bitmap, const uint64_t *tile_off,
-                                             uint64_t *hv) {
+                                             unsigned long long *acc) {
     __shared__ uint64_t s_F[(TPW * WT)];
     __shared__ uint32_t s_st[(TPW * WT)];
     __shared__ WQ s_Q;
@@ -456,6 +646,7 @@ __global__ __launch_bounds__(WT) void k_wlink(const WQ *qs, const uint32_t *rowq
     // the same count in every lane (the loop holds barriers)
     const uint32_t n = __builtin_amdgcn_readfirstlane(s_pre[(TPW * WT) / 64]);
     const bool stage = one && s_Q.final_level && s_Q.out && s_Q.k <= WLINK_STAGE_K;
+    uint64_t hs = 0, hx = 0;
     for (uint32_t q0 = 0; q0 < n; q0 += WT) {
         const uint32_t local = threadIdx.x;  // survivor q0 + local of the group
         const uint32_t q = q0 + local;
@@ -524,7 +715,13 @@ __global__ __launch_bounds__(WT) void k_wlink(const WQ *qs, const uint32_t *rowq
                             f = fnv_word(f, val[k4]);
                         }
                     }
-                    hv[gpos] = mix64(f);
+                    const uint64_t h = mix64(f);
+                    if (one) {
+                        hs += h;
+                        hx ^= h;
+                    } else {
+                        add_hash(acc, rowq[r], h);
+                    }
                 }
             }
         }
@@ -540,42 +737,19 @@ __global__ __launch_bounds__(WT) void k_wlink(const WQ *qs, const uint32_t *rowq
             __syncthreads();
         }
     }
-}
-
-// (sum, xor) of hv[a, b) per item, one workgroup per item
-__global__ __launch_bounds__(WT) void k_wdigest(const uint64_t *items, const uint64_t *hv, uint64_t *part) {
-    __shared__ uint64_t s_s[WT / 64], s_x[WT / 64];
-    const uint64_t a = items[2 * (uint64_t)blockIdx.x], b = items[2 * (uint64_t)blockIdx.x + 1];
-    uint64_t sm = 0, xr = 0;
-    for (uint64_t t = a + threadIdx.x; t < b; t += WT) {
-        const uint64_t h = hv[t];
-        sm += h;
-        xr ^= h;
-    }
-    sm = wave_sum(sm);
-    xr = wave_xor(xr);
-    if (lane_id() == 0) {
-        s_s[threadIdx.x >> 6] = sm;
-        s_x[threadIdx.x >> 6] = xr;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t ts = 0, tx = 0;
-        for (int q = 0; q < WT / 64; q++) {
-            ts += s_s[q];
-            tx ^= s_x[q];
-        }
-        part[2 * (uint64_t)blockIdx.x] = ts;
-        part[2 * (uint64_t)blockIdx.x + 1] = tx;
+    if (one && s_Q.final_level) {
+        hs = wave_sum(hs);
+        hx = wave_xor(hx);
+        if (lane_id() == 0) add_hash(acc, s_q[0], hs, hx);
     }
 }
 
 // One join level for the queries in `act` (all of them, or none: on an
 // allocation failure everything allocated for the step is given back and
-// no query changes state).
-static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool count_only, uint32_t tpw) {
+// no query changes state).  records: survivors as records where they fit.
+static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool count_only, uint32_t tpw,
+                      bool records) {
     gsi_ctx *c = g->ctx;
-    constexpr uint64_t DIGEST_ITEM = 1u << 16;
     {
         const uint32_t nq = (uint32_t)act.size();
         Scratch s(c);
@@ -665,21 +839,32 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
             }
             return;
         }
-        const uint64_t ntiles = (gba + WT - 1) / WT;
+        // survivor records per group of tpw tiles when they fit comfortably
+        // (8 bytes per slot), else keep bits per tile
+        const uint32_t group = tpw * WT;
+        const uint64_t ngroups = (gba + group - 1) / group;
+        const bool recs = records && 8.0 * (double)(ngroups * group) <= (double)c->arena.largest_free() / 4;
+        const uint64_t ntiles = recs ? ngroups : (gba + WT - 1) / WT;
+        uint32_t *rec_x = nullptr, *rec_r = nullptr;
+        uint64_t *bitmap = nullptr;
+        if (recs) {
+            rec_x = s.get<uint32_t>(ngroups * group, "wide survivor elements");
+            rec_r = s.get<uint32_t>(ngroups * group, "wide survivor rows");
+        } else {
+            bitmap = s.get<uint64_t>(ntiles * (WT / 64), "wide GBA bitmap");
+        }
         uint64_t *trow = s.get<uint64_t>(ntiles + 1, "wide tile rows");
-        uint64_t *bitmap = s.get<uint64_t>(ntiles * (WT / 64), "wide GBA bitmap");
         uint32_t *tcnt = s.get<uint32_t>(ntiles, "wide tile counts");
         uint64_t *toff = s.get<uint64_t>(ntiles + 1, "wide tile offsets");
         uint64_t *sb = s.get<uint64_t>(4ull * nq, "wide survivor ranges");
-        tile_rows(c, F, Rtot, ntiles, trow);
-        double jb = 4.0 * gba + gba / 8.0 + 4.0 * ntiles;
+        tile_rows(c, F, Rtot, ntiles, recs ? group : WT, trow);
+        double jb = 4.0 * gba + (recs ? 0.0 : gba / 8.0) + 4.0 * ntiles;
         for (auto &Q : hq) jb += (double)Q.R * (8.0 + 8.0 * Q.ne + 4.0 * Q.j);
         {
-            const uint32_t grid = (uint32_t)((ntiles + tpw - 1) / tpw);
             auto join = [&](auto kern) {
-                launch(c, "k_wjoin", jb, kern, grid, WT, (const WQ *)d_q, (const uint32_t *)rowq, (const WEdge *)d_e,
-                       (const uint32_t *)g->ci, (const uint64_t *)F, (const uint64_t *)trow, ntiles, gba,
-                       (const uint32_t *)loc, bitmap, tcnt);
+                launch(c, "k_wjoin", jb, kern, (uint32_t)ngroups, WT, (const WQ *)d_q, (const uint32_t *)rowq,
+                       (const WEdge *)d_e, (const uint32_t *)g->ci, (const uint64_t *)F, (const uint64_t *)trow,
+                       ntiles, gba, (const uint32_t *)loc, bitmap, rec_x, rec_r, tcnt);
             };
             if (tpw == 1) join(k_wjoin<1>);
             else if (tpw == 2) join(k_wjoin<2>);
@@ -688,16 +873,15 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
         }
         exclusive_scan(c, tcnt, ntiles, toff, s, scal + 1);
         launch(c, "k_wsurv", 48.0 * nq, k_wsurv, wblocks(nq), WT, (const WQ *)d_q, nq, (const uint64_t *)F,
-               (const uint64_t *)bitmap, (const uint64_t *)toff, gba, sb);
+               (const uint64_t *)bitmap, (const uint32_t *)rec_r, (const uint64_t *)trow, ntiles, group,
+               (const uint64_t *)toff, gba, sb);
         std::vector<uint64_t> hsb(4ull * nq);
         GSI_HIP(hipMemcpyAsync(hsb.data(), sb, 32ull * nq, hipMemcpyDeviceToHost, c->stream));
         uint64_t Stot;
         read_scalars(c, scal + 1, &Stot, 1);
         // next tables (exact sizes) and result rows
         bool any_final = false;
-        std::vector<uint64_t> items;
-        std::vector<uint32_t> item_q;
-        double kb = gba / 8.0 + 8.0 * ntiles;
+        double kb = (recs ? 8.0 * Stot : gba / 8.0) + 8.0 * ntiles;
         for (uint32_t a = 0; a < nq; a++) {
             WideQuery &x = *act[a];
             WQ &Q = hq[a];
@@ -714,11 +898,6 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
                     x.rows = Q.out;
                     kb += 4.0 * Q.k * Q.S;
                 }
-                for (uint64_t t = Q.sbase; t < Q.sbase + Q.S; t += DIGEST_ITEM) {
-                    items.push_back(t);
-                    items.push_back(std::min(t + DIGEST_ITEM, Q.sbase + Q.S));
-                    item_q.push_back(a);
-                }
             } else {
                 x.next = c->arena.alloc(4ull * (Q.j + 1) * Q.S, false);
                 if (!x.next)
@@ -728,37 +907,50 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
                 kb += 4.0 * (Q.j + 1) * Q.S;
             }
         }
-        uint64_t *hv = any_final ? s.get<uint64_t>(Stot, "wide row hashes") : nullptr;
-        GSI_HIP(hipMemcpyAsync(d_q, hq.data(), sizeof(WQ) * nq, hipMemcpyHostToDevice, c->stream));
-        {
-            const uint32_t grid = (uint32_t)((ntiles + tpw - 1) / tpw);
-            auto link = [&](auto kern) {
-                launch(c, "k_wlink", kb, kern, grid, WT, (const WQ *)d_q, (const uint32_t *)rowq,
-                       (const uint32_t *)g->ci, (const uint64_t *)F, (const uint64_t *)trow, ntiles,
-                       (const uint32_t *)loc, (const uint64_t *)bitmap, (const uint64_t *)toff, hv);
-            };
-            if (tpw == 1) link(k_wlink<1>);
-            else if (tpw == 2) link(k_wlink<2>);
-            else if (tpw == 8) link(k_wlink<8>);
-            else link(k_wlink<4>);
-        }
-        std::vector<uint64_t> part;
+        uint64_t *acc = nullptr, *d_dig = nullptr;
         if (any_final) {
-            const uint64_t ni = item_q.size();
-            uint64_t *d_items = s.get<uint64_t>(2 * ni, "digest items");
-            uint64_t *d_part = s.get<uint64_t>(2 * ni, "digest partials");
-            GSI_HIP(hipMemcpyAsync(d_items, items.data(), 16 * ni, hipMemcpyHostToDevice, c->stream));
-            launch(c, "k_wdigest", 8.0 * Stot, k_wdigest, (uint32_t)ni, WT, (const uint64_t *)d_items,
-                   (const uint64_t *)hv, d_part);
-            part.resize(2 * ni);
-            GSI_HIP(hipMemcpyAsync(part.data(), d_part, 16 * ni, hipMemcpyDeviceToHost, c->stream));
+            acc = s.get<uint64_t>(2ull * WACC * nq, "digest accumulators");
+            d_dig = s.get<uint64_t>(2ull * nq, "digests");
+            fill_u64(c, acc, 0, 2ull * WACC * nq);
         }
-        sync(c);  // uploads done, partials read
-        for (size_t t = 0; t < item_q.size(); t++) {
-            WideQuery &x = *act[item_q[t]];
-            x.digest[0] += part[2 * t];
-            x.digest[1] ^= part[2 * t + 1];
+        GSI_HIP(hipMemcpyAsync(d_q, hq.data(), sizeof(WQ) * nq, hipMemcpyHostToDevice, c->stream));
+        if (recs && Stot) {
+            const uint32_t nlt = wblocks(Stot);
+            uint64_t *stile = s.get<uint64_t>((uint64_t)nlt + 1, "wide survivor groups");
+            tile_rows(c, toff, ngroups, nlt, WT, stile);
+            auto link = [&](auto kern) {
+                launch(c, "k_wlink", kb, kern, nlt, WT, (const WQ *)d_q, (const uint32_t *)rowq,
+                       (const uint64_t *)trow, (const uint64_t *)toff, (const uint64_t *)stile, group,
+                       (const uint32_t *)rec_x, (const uint32_t *)rec_r, Stot,
+                       reinterpret_cast<unsigned long long *>(acc));
+            };
+            if (any_final && !count_only) link(k_wlink<true>);
+            else link(k_wlink<false>);
+        } else if (Stot) {
+            auto link = [&](auto kern) {
+                launch(c, "k_wlink_bits", kb, kern, (uint32_t)ngroups, WT, (const WQ *)d_q, (const uint32_t *)rowq,
+                       (const uint32_t *)g->ci, (const uint64_t *)F, (const uint64_t *)trow, ntiles,
+                       (const uint32_t *)loc, (const uint64_t *)bitmap, (const uint64_t *)toff,
+                       reinterpret_cast<unsigned long long *>(acc));
+            };
+            if (tpw == 1) link(k_wlink_bits<1>);
+            else if (tpw == 2) link(k_wlink_bits<2>);
+            else if (tpw == 8) link(k_wlink_bits<8>);
+            else link(k_wlink_bits<4>);
         }
+        std::vector<uint64_t> dig;
+        if (any_final) {
+            launch(c, "k_wdigest", 16.0 * WACC * nq, k_wdigest, wblocks(nq), WT, (const uint64_t *)acc, nq, d_dig);
+            dig.resize(2ull * nq);
+            GSI_HIP(hipMemcpyAsync(dig.data(), d_dig, 16ull * nq, hipMemcpyDeviceToHost, c->stream));
+        }
+        sync(c);  // uploads done, digests read
+        if (any_final)
+            for (uint32_t a = 0; a < nq; a++)
+                if (hq[a].final_level) {
+                    act[a]->digest[0] += dig[2ull * a];
+                    act[a]->digest[1] ^= dig[2ull * a + 1];
+                }
         pend.commit = true;
         for (uint32_t a = 0; a < nq; a++) {
             WideQuery &x = *act[a];
@@ -815,15 +1007,21 @@ uint32_t WideEngine::step() {
     uint64_t est = 0;
     while (n < act.size() && (n == 0 || est + step_bytes(*act[n]) <= room)) est += step_bytes(*act[n++]);
     size_t skipped = 0;  // queries moved behind the others (tolerant engine)
+    bool records = true;
     for (;;) {
         std::vector<WideQuery *> part(act.begin(), act.begin() + n);
         try {
-            wide_step(g_, part, count_only_, tpw_);
+            wide_step(g_, part, count_only_, tpw_, records);
             steps_++;
             break;
         } catch (const Fail &f) {
-            if (f.st != GSI_E_NOMEM || (n == 1 && !tolerant_)) throw;
+            if (f.st != GSI_E_NOMEM || (n == 1 && !records && !tolerant_)) throw;
             clear_error();
+            if (n == 1 && records) {
+                // what the records took may be what the next table lacked
+                records = false;
+                continue;
+            }
             if (n > 1) {
                 n = (n + 1) / 2;
                 continue;
@@ -841,6 +1039,7 @@ uint32_t WideEngine::step() {
             act.erase(act.begin());
             act.push_back(x);
             skipped++;
+            records = true;
         }
     }
     uint32_t done = 0;
