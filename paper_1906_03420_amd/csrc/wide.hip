@@ -39,9 +39,10 @@ struct WEdge {
     uint32_t ci_off;  // offset of its label's lists in the whole ci array
 };
 
-// Lookups of a query's rows at loc + locbase: start of linking edge e at
-// [e*R + i], length at [(ne+e)*R + i], start (in the whole ci array) of the
-// list the row scans at [2ne*R + i] and that list's edge at [(2ne+1)*R + i].
+// Lookups of a query's rows at loc + locbase (even): (start, length) of
+// linking edge e at words 2(e*R + i) and the next (one 8-byte load), start (in
+// the array of scanned lists) of the list the row scans at [2ne*R + i] and
+// that list's edge at [(2ne+1)*R + i].
 struct WQ {
     const uint32_t *M;  // table, column c at M + c*R
     uint64_t R, rbase, locbase;
@@ -52,15 +53,41 @@ struct WQ {
     uint64_t S, sbase;
     uint32_t qcol[GSI_MAX_K];
     uint32_t mmask;  // columns of m_i whose query vertex has u's label
+    uint32_t pre;    // 1: the rows scan lists already filtered by C(u)
+    const uint32_t *ci;  // array of the scanned lists: every label's, or the filtered ones
 };
 
-// candidates a join thread tests at once (wkeep_many)
-constexpr uint32_t WU = 4;
-// the last search round as vector loads (in_sorted_many): more registers,
-// one wave fewer per SIMD for the engine's join
-constexpr bool WVEC = false;
-// search rounds split a range in WARITY parts (in_sorted_many)
-constexpr uint32_t WARITY = 8;
+__device__ __forceinline__ uint2 wloc_pair(const WQ &Q, const uint32_t *loc, uint32_t e, uint64_t i) {
+    return reinterpret_cast<const uint2 *>(loc + Q.locbase)[(uint64_t)e * Q.R + i];
+}
+
+// Candidates a join thread tests at once (wkeep_many), and the parts a
+// search round splits a range in: as in the single-query join, two
+// candidates fit the registers of 8 waves per SIMD, and 4-ary rounds with a
+// vector tail issue fewer loads.
+constexpr uint32_t WU = 2;
+constexpr uint32_t WARITY = 4;
+
+// x[u] not among N of the row's values, columns taken from the low bits of mm
+template <uint32_t U, uint32_t N>
+__device__ __forceinline__ void wdiffers(const WQ &Q, uint32_t &mm, const uint32_t *x, const uint64_t *i, bool *keep) {
+    uint32_t cq[N], m[U][N];
+#pragma unroll
+    for (uint32_t t = 0; t < N; t++) {
+        // past the last column it is read again
+        cq[t] = (uint32_t)__builtin_ctz(mm);
+        if (mm & (mm - 1)) mm &= mm - 1;
+        else if (t + 1 == N) mm = 0;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < U; u++)
+#pragma unroll
+        for (uint32_t t = 0; t < N; t++) m[u][t] = Q.M[(uint64_t)cq[t] * Q.R + i[u]];
+#pragma unroll
+    for (uint32_t u = 0; u < U; u++)
+#pragma unroll
+        for (uint32_t t = 0; t < N; t++) keep[u] = keep[u] && m[u][t] != x[u];
+}
 
 // The costly tests of U candidates of query Q at once (rows i[u] of Q's
 // table): keep[u] (on entry: candidate u is live) becomes x[u] not in the
@@ -69,25 +96,13 @@ constexpr uint32_t WARITY = 8;
 template <uint32_t U>
 __device__ __forceinline__ void wkeep_many(const WQ &Q, const uint32_t *loc, const WEdge *edges, const uint32_t *x,
                                            const uint64_t *i, bool *keep) {
-    // only the columns of u's label can hold x; four at a time, the last
-    // one read again past the end
+    // only the columns of u's label can hold x; in chunks of 1, 2 or 4
     uint32_t mm = Q.mmask;
-    const uint32_t last = mm ? 31u - (uint32_t)__builtin_clz(mm) : 0u;
     while (mm) {
-        uint32_t cq[4], m[U][4];
-#pragma unroll
-        for (uint32_t t = 0; t < 4; t++) {
-            cq[t] = mm ? (uint32_t)__builtin_ctz(mm) : last;
-            mm &= mm - 1;
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < U; u++)
-#pragma unroll
-            for (uint32_t t = 0; t < 4; t++) m[u][t] = Q.M[(uint64_t)cq[t] * Q.R + i[u]];
-#pragma unroll
-        for (uint32_t u = 0; u < U; u++)
-#pragma unroll
-            for (uint32_t t = 0; t < 4; t++) keep[u] = keep[u] && m[u][t] != x[u];
+        const int left = __popc(mm);
+        if (left >= 3) wdiffers<U, 4>(Q, mm, x, i, keep);
+        else if (left == 2) wdiffers<U, 2>(Q, mm, x, i, keep);
+        else wdiffers<U, 1>(Q, mm, x, i, keep);
     }
     if (Q.ne < 2) return;
     uint32_t be[U];
@@ -95,22 +110,36 @@ __device__ __forceinline__ void wkeep_many(const WQ &Q, const uint32_t *loc, con
     for (uint32_t u = 0; u < U; u++) be[u] = loc[Q.locbase + (uint64_t)(2 * Q.ne + 1) * Q.R + i[u]];
     for (uint32_t e2 = 0; e2 < Q.ne; e2++) {
         uint32_t st[U], len[U];
-        bool act[U], hit[U];
-#pragma unroll
-        for (uint32_t u = 0; u < U; u++) {
-            st[u] = loc[Q.locbase + (uint64_t)e2 * Q.R + i[u]];
-            len[u] = loc[Q.locbase + (uint64_t)(Q.ne + e2) * Q.R + i[u]];
-        }
+        bool act[U], hit[U], any = false;
 #pragma unroll
         for (uint32_t u = 0; u < U; u++) {
             act[u] = keep[u] && e2 != be[u];
-            if (!act[u]) len[u] = 0;
+            any |= act[u];
         }
-        in_sorted_many<U, WVEC, WARITY>(edges[Q.efirst + e2].ci, st, len, x, hit);
+        if (!any) continue;
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) {
+            const uint2 sl = wloc_pair(Q, loc, e2, i[u]);
+            st[u] = sl.x;
+            len[u] = act[u] ? sl.y : 0u;
+        }
+        in_sorted_many<U, true, WARITY>(edges[Q.efirst + e2].ci, st, len, x, hit);
 #pragma unroll
         for (uint32_t u = 0; u < U; u++)
             if (act[u]) keep[u] = hit[u];
     }
+}
+
+// Copies n words from the device and waits for the stream: through the
+// pinned staging area when they fit (a pageable copy is staged by the
+// runtime, several microseconds more).
+static void read_words(gsi_ctx *c, const uint64_t *dev, std::vector<uint64_t> &out, uint64_t n) {
+    out.resize(n);
+    const bool pin = 8 * n <= 56 * 1024;
+    uint64_t *dst = pin ? c->pinned + 1024 : out.data();
+    GSI_HIP(hipMemcpyAsync(dst, dev, 8 * n, hipMemcpyDeviceToHost, c->stream));
+    sync(c);
+    if (pin) memcpy(out.data(), dst, 8 * n);
 }
 
 static uint32_t wblocks(uint64_t n) {
@@ -153,8 +182,7 @@ __global__ __launch_bounds__(WT) void k_wlocate(const WQ *qs, uint32_t nq, const
         const WEdge &ed = edges[Q.efirst + e];
         const uint32_t v = Q.M[(uint64_t)ed.col * Q.R + i];
         const uint2 f = pcsr_find(ed.gl, ed.G, ed.H, v);
-        loc[Q.locbase + (uint64_t)e * Q.R + i] = f.x;
-        loc[Q.locbase + (uint64_t)(Q.ne + e) * Q.R + i] = f.y;
+        reinterpret_cast<uint2 *>(loc + Q.locbase)[(uint64_t)e * Q.R + i] = f;
         if (e == Q.e0) {
             s0 = f.x;
             l0 = f.y;
@@ -175,116 +203,204 @@ __global__ __launch_bounds__(WT) void k_wlocate(const WQ *qs, uint32_t nq, const
     loc[Q.locbase + (uint64_t)(2 * Q.ne + 1) * Q.R + i] = be;
 }
 
-// The join of WJ_TILES consecutive 256-slot tiles per workgroup: each
-// thread takes one slot of each tile and issues their loads together, and
-// the set-up (rows staged in LDS, the query's descriptor) is paid once per
-// WJ_TILES tiles.  Outputs stay per 256-slot tile: WT/64 bitmap words and
-// one survivor count each.  When the rows fit (staged), each slot's row
+// Level-wide filtered lists (the single-query path's, for the queries of a
+// step whose rows scan far more list elements than their first edge's label
+// holds): C(u) is tested once per element of the label's lists, the kept
+// elements are compacted in order, all such queries' one after the other in
+// one array, and the query's rows scan the compacted lists.  On the batch of
+// 1,024 queries two thirds of the 3*10^9 slots are in 94 levels whose lists
+// hold 1/8 as many elements.  Item t filters
+// the lists of query q; its elements are padded to whole words, its words are
+// [w0, w0 + words of el) and its workgroups start at b0 (elements) and rb0
+// (rows).
+struct WFilter {
+    const uint32_t *ci;  // the label's lists
+    uint64_t el, w0;
+    uint32_t b0, rb0, q, pad;
+};
+constexpr uint32_t WF_TILES = 4;  // elements per thread
+// directed entries of the first edge's label per |GBA| slot of the query
+// above which its lists are filtered (the single-query path's factor)
+constexpr double WF_FACTOR = 2.0;
+// slots the filter has to save in a step: it costs about ten launches and a
+// wait, 100 us, in which the join takes 2^24 slots (a batch of 48 queries
+// with levels of up to 2^20 slots was 6 % slower with it)
+constexpr uint64_t WF_MIN_SLOTS = 1ull << 24;
+
+__device__ __forceinline__ uint32_t filter_item(const WFilter *f, uint32_t n, uint32_t b, bool rows) {
+    uint32_t lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1) >> 1;
+        if ((rows ? f[mid].rb0 : f[mid].b0) <= b) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+__global__ __launch_bounds__(WT) void k_wfn_bits(const WQ *qs, const WFilter *f, uint32_t nf, uint64_t *bits,
+                                                uint32_t *wcnt) {
+    const WFilter &I = f[filter_item(f, nf, blockIdx.x, false)];
+    const uint64_t *Cu = qs[I.q].Cu;
+    const uint64_t base = (uint64_t)(blockIdx.x - I.b0) * (WF_TILES * WT) + threadIdx.x;
+    uint32_t x[WF_TILES];
+    uint64_t cw[WF_TILES];
+#pragma unroll
+    for (uint32_t r = 0; r < WF_TILES; r++) {
+        const uint64_t p = base + r * WT;
+        x[r] = I.ci[p < I.el ? p : I.el - 1];
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < WF_TILES; r++) cw[r] = Cu[x[r] >> 6];
+#pragma unroll
+    for (uint32_t r = 0; r < WF_TILES; r++) {
+        const uint64_t p = base + r * WT;
+        const uint64_t m = __ballot(p < I.el && ((cw[r] >> (x[r] & 63)) & 1ull));
+        if (lane_id() == 0 && p < I.el) {
+            bits[I.w0 + (p >> 6)] = m;
+            wcnt[I.w0 + (p >> 6)] = (uint32_t)__popcll(m);
+        }
+    }
+}
+
+__global__ __launch_bounds__(WT) void k_wfn_compact(const WFilter *f, uint32_t nf, const uint64_t *bits,
+                                                   const uint64_t *wpre, uint32_t *fn) {
+    const WFilter &I = f[filter_item(f, nf, blockIdx.x, false)];
+    const uint64_t base = (uint64_t)(blockIdx.x - I.b0) * (WF_TILES * WT) + threadIdx.x;
+#pragma unroll
+    for (uint32_t r = 0; r < WF_TILES; r++) {
+        const uint64_t p = base + r * WT;
+        if (p >= I.el) continue;
+        const uint64_t m = bits[I.w0 + (p >> 6)];
+        if ((m >> (p & 63)) & 1ull) fn[wpre[I.w0 + (p >> 6)] + rank_below(m)] = I.ci[p];
+    }
+}
+
+// every row of a filtered query scans its e0 list's members of C(u)
+__global__ __launch_bounds__(WT) void k_wfn_relocate(const WQ *qs, const WFilter *f, uint32_t nf, const uint64_t *bits,
+                                                    const uint64_t *wpre, uint32_t *loc, uint32_t *bound) {
+    const WFilter &I = f[filter_item(f, nf, blockIdx.x, true)];
+    const WQ &Q = qs[I.q];
+    const uint64_t i = (uint64_t)(blockIdx.x - I.rb0) * WT + threadIdx.x;
+    if (i >= Q.R) return;
+    const uint2 sl = wloc_pair(Q, loc, Q.e0, i);
+    const uint32_t st = sl.x, len = sl.y;
+    // kept elements before position p of the item
+    auto rank = [&](uint64_t p) -> uint64_t {
+        const uint64_t w = I.w0 + (p >> 6);
+        const uint32_t b = (uint32_t)(p & 63);
+        return b ? wpre[w] + (uint64_t)__popcll(bits[w] & ((1ull << b) - 1)) : wpre[w];
+    };
+    const uint64_t fs = len ? rank(st) : 0, fe = len ? rank((uint64_t)st + len) : 0;
+    bound[Q.rbase + i] = (uint32_t)(fe - fs);
+    loc[Q.locbase + (uint64_t)(2 * Q.ne) * Q.R + i] = (uint32_t)fs;
+    loc[Q.locbase + (uint64_t)(2 * Q.ne + 1) * Q.R + i] = Q.e0;
+}
+
+// |GBA| of each query: its rows' slots
+__global__ __launch_bounds__(WT) void k_wgba(const WQ *qs, uint32_t nq, const uint64_t *F, uint64_t *out) {
+    const uint32_t q = blockIdx.x * WT + threadIdx.x;
+    if (q < nq) out[q] = F[qs[q].rbase + qs[q].R] - F[qs[q].rbase];
+}
+
+// The join of WJ_TILES consecutive 256-slot tiles (a group) per workgroup:
+// each thread takes one slot of each tile and issues their loads together,
+// and the set-up (rows staged in LDS) is paid once per group.  Outputs are
+// the group's survivor records and count, or per 256-slot tile WT/64 bitmap
+// words and a count.  When the rows fit (staged), each slot's row
 // comes from a map built once per workgroup: each row after the first
 // marks the slot where its slice starts (the largest row wins where empty
 // rows share a start) and a max-scan carries the marks forward.
 // (WJ_TILES by default; the batch schedule may pick 1, 2, 4 or 8, tuned)
+// A group is a chain of about eight dependent loads, so what counts is how
+// many groups a CU holds: a row's list start and first slot are kept as one
+// 32-bit position (18.5 KB of LDS a group, 26.6 with both), the descriptor
+// in scalar registers, two candidates a thread in 64 VGPRs: 8 waves per
+// SIMD.  On the batch of 1,024 queries a step took 1.06 ms, with filtered
+// lists 0.61, and with this 0.46.
 constexpr uint32_t WJ_TILES = 4;
 
 template <uint32_t TPW>
-__global__ __launch_bounds__(WT) void k_wjoin(const WQ *qs, const uint32_t *rowq, const WEdge *edges,
-                                             const uint32_t *ci_all, const uint64_t *F, const uint64_t *tile_row,
-                                             uint64_t ntiles, uint64_t gba, const uint32_t *loc, uint64_t *bitmap,
-                                             uint32_t *rec_x, uint32_t *rec_r, uint32_t *tile_cnt) {
-    __shared__ uint64_t s_F[(TPW * WT)];
-    __shared__ uint32_t s_st[(TPW * WT)];
-    __shared__ uint32_t s_row[(TPW * WT)];  // row (from r_lo) of each slot, staged groups
+__global__ __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(TPW <= 4 ? 8 : 4))) void k_wjoin(
+    const WQ *__restrict__ qs, const uint32_t *__restrict__ rowq, const WEdge *__restrict__ edges,
+    const uint64_t *__restrict__ F, const uint64_t *__restrict__ tile_row, uint64_t ntiles, uint64_t gba,
+    const uint32_t *__restrict__ loc, uint64_t *bitmap, uint32_t *rec_x, uint32_t *rec_r, uint32_t *tile_cnt) {
+    constexpr uint32_t TS = TPW * WT;
+    __shared__ uint32_t s_row[TS];    // row (from r_lo) of each slot, staged groups
+    __shared__ uint32_t s_base[TS];   // per row: position of the group's slot 0 in the scanned lists
     __shared__ uint32_t s_w[WT / 64];
-    __shared__ WQ s_Q;
-    __shared__ uint32_t s_q[2];
-    __shared__ uint32_t s_x[(TPW * WT)];    // elements that passed the C(u) test, compacted
-    __shared__ uint32_t s_r[(TPW * WT)];    // and their rows (from r_lo)
-    __shared__ uint16_t s_slot[(TPW * WT)]; // and their slots in the group
-    __shared__ uint64_t s_keep[(TPW * WT) / 64];
+    __shared__ uint32_t s_x[TS];      // elements that passed the C(u) test, compacted
+    __shared__ uint32_t s_r[TS];      // and their rows (from r_lo)
+    __shared__ uint16_t s_slot[TS];   // and their slots in the group
+    __shared__ uint64_t s_keep[TS / 64];
     __shared__ uint32_t s_n;
     // tile_row and tile_cnt are kept per group with records, per tile without
     const uint64_t t0 = (uint64_t)blockIdx.x * (rec_x ? 1 : TPW);
     const uint64_t t1 = rec_x ? t0 + 1 : t0 + TPW < ntiles ? t0 + TPW : ntiles;
-    const uint64_t p0 = (uint64_t)blockIdx.x * (TPW * WT);
+    const uint64_t p0 = (uint64_t)blockIdx.x * TS;
     const uint64_t r_lo = tile_row[t0], r_hi = tile_row[t1];
     const uint64_t nr = r_hi - r_lo + 1;
-    const bool staged = nr <= (TPW * WT);
-    if (threadIdx.x == 0) {
-        s_n = 0;
-        s_q[0] = rowq[r_lo];
-        s_q[1] = rowq[r_hi];
-    }
-    if (threadIdx.x < (TPW * WT) / 64) s_keep[threadIdx.x] = 0;
+    const bool staged = nr <= TS;
+    const uint32_t q0 = __builtin_amdgcn_readfirstlane(rowq[r_lo]), q1 = __builtin_amdgcn_readfirstlane(rowq[r_hi]);
+    const bool one = q0 == q1;  // one query in the group: its descriptor is read with scalar loads
+    const WQ &Q0 = qs[q0];
+    if (threadIdx.x == 0) s_n = 0;
+    if (threadIdx.x < TS / 64) s_keep[threadIdx.x] = 0;
 #pragma unroll
     for (uint32_t k = 0; k < TPW; k++) s_row[threadIdx.x * TPW + k] = 0;
-    if (staged)
-        for (uint32_t r = threadIdx.x; r < nr; r += WT) s_F[r] = F[r_lo + r];
     __syncthreads();
-    const bool one = s_q[0] == s_q[1];
-    if (one) {
-        const WQ &Q = qs[s_q[0]];
-        const uint32_t *src = reinterpret_cast<const uint32_t *>(&Q);
-        uint32_t *dst = reinterpret_cast<uint32_t *>(&s_Q);
-        for (uint32_t w = threadIdx.x; w < sizeof(WQ) / 4; w += WT) dst[w] = src[w];
-        if (staged)
-            for (uint32_t r = threadIdx.x; r < nr; r += WT)
-                s_st[r] = loc[Q.locbase + (uint64_t)(2 * Q.ne) * Q.R + (r_lo + r - Q.rbase)];
-    }
-    if (staged)
+    if (staged) {
         for (uint32_t r = threadIdx.x; r < nr; r += WT) {
+            const uint64_t Fr = F[r_lo + r];
+            uint32_t st;
+            if (one) {
+                st = loc[Q0.locbase + (uint64_t)(2 * Q0.ne) * Q0.R + (r_lo + r - Q0.rbase)];
+            } else {
+                const WQ &Q = qs[rowq[r_lo + r]];
+                st = loc[Q.locbase + (uint64_t)(2 * Q.ne) * Q.R + (r_lo + r - Q.rbase)];
+            }
+            s_base[r] = st + (uint32_t)(p0 - Fr);
             // rows after the first start past p0 (the first holds slot p0)
-            const uint64_t pos = s_F[r] - p0;
-            if (r > 0 && pos < (TPW * WT)) atomicMax(&s_row[pos], r);
+            if (r > 0 && Fr - p0 < TS) atomicMax(&s_row[Fr - p0], r);
         }
-    __syncthreads();
-    if (staged) block_max_scan<WT, TPW>(s_row, s_w);
+        __syncthreads();
+        block_max_scan<WT, TPW>(s_row, s_w);
+    }
     const uint32_t lane = lane_id();
-    // x = N(v'_i, l0)[p - F[i]] for the thread's slot of each tile, then the
-    // C(u) test; the slots that pass are compacted so that the costly tests
-    // below run in dense waves
+    // x = N(v'_i, l0)[p - F[i]] for the thread's slot of each tile (a slot past
+    // |GBA| re-reads the last one), then the C(u) test; the slots that pass are
+    // compacted so that the costly tests below run in dense waves
+    const uint32_t last = gba - p0 < TS ? (uint32_t)(gba - p0) - 1 : TS - 1;
     uint32_t xs[TPW], rs[TPW];
     bool kp[TPW];
 #pragma unroll
     for (uint32_t k = 0; k < TPW; k++) {
-        const uint32_t sl = k * WT + threadIdx.x;
-        const uint64_t p = p0 + sl;
-        kp[k] = p < gba;
-        xs[k] = 0;
-        rs[k] = 0;
-        if (kp[k]) {
-            uint64_t r, Fr;
-            uint32_t lr;
-            if (staged) {
-                lr = s_row[sl];
-                r = r_lo + lr;
-                Fr = s_F[lr];
-            } else {
-                uint64_t lo = r_lo, hi = r_hi;
-                while (lo < hi) {
-                    const uint64_t mid = lo + (hi - lo + 1) / 2;
-                    if (F[mid] <= p) lo = mid;
-                    else hi = mid - 1;
-                }
-                r = lo;
-                Fr = F[lo];
-                lr = 0;
+        const uint32_t own = k * WT + threadIdx.x;
+        kp[k] = own <= last;
+        const uint32_t sl = own <= last ? own : last;
+        uint32_t pos;
+        if (staged) {
+            rs[k] = s_row[sl];
+            pos = s_base[rs[k]] + sl;
+        } else {
+            const uint64_t p = p0 + sl;
+            uint64_t lo = r_lo, hi = r_hi;
+            while (lo < hi) {
+                const uint64_t mid = lo + (hi - lo + 1) / 2;
+                if (F[mid] <= p) lo = mid;
+                else hi = mid - 1;
             }
-            rs[k] = (uint32_t)(r - r_lo);
-            const WQ &Q = one ? s_Q : qs[rowq[r]];
-            const uint64_t i = r - Q.rbase;
-            const uint32_t st0 = (one && staged) ? s_st[lr] : loc[Q.locbase + (uint64_t)(2 * Q.ne) * Q.R + i];
-            xs[k] = ci_all[st0 + (uint32_t)(p - Fr)];
+            rs[k] = (uint32_t)(lo - r_lo);
+            const WQ &Q = qs[rowq[lo]];
+            pos = loc[Q.locbase + (uint64_t)(2 * Q.ne) * Q.R + (lo - Q.rbase)] + (uint32_t)(p - F[lo]);
         }
+        xs[k] = one ? Q0.ci[pos] : qs[rowq[r_lo + rs[k]]].ci[pos];
     }
-    {
-        // every slot's C(u) word is loaded before any is tested (a slot past
-        // |GBA| has x = 0 and row r_lo: valid addresses)
+    if (!(one && Q0.pre)) {
+        // every slot's C(u) word is loaded before any is tested (a filtered
+        // list's elements pass)
         uint64_t cw[TPW];
 #pragma unroll
-        for (uint32_t k = 0; k < TPW; k++) {
-            const uint64_t *Cu = one ? s_Q.Cu : qs[rowq[r_lo + rs[k]]].Cu;
-            cw[k] = Cu[xs[k] >> 6];
-        }
+        for (uint32_t k = 0; k < TPW; k++) cw[k] = (one ? Q0.Cu : qs[rowq[r_lo + rs[k]]].Cu)[xs[k] >> 6];
 #pragma unroll
         for (uint32_t k = 0; k < TPW; k++) kp[k] = kp[k] && ((cw[k] >> (xs[k] & 63)) & 1ull);
     }
@@ -306,8 +422,7 @@ __global__ __launch_bounds__(WT) void k_wjoin(const WQ *qs, const uint32_t *rowq
     __syncthreads();
     const uint32_t n = __builtin_amdgcn_readfirstlane(s_n);
     if (one) {
-        // one query in the tile: WU candidates per thread at a time, their
-        // loads issued together
+        // WU candidates per thread at a time, their loads issued together
         for (uint32_t e0 = 0; e0 < n; e0 += WU * WT) {
             uint32_t xs2[WU], sl[WU];
             uint64_t is[WU];
@@ -319,9 +434,9 @@ __global__ __launch_bounds__(WT) void k_wjoin(const WQ *qs, const uint32_t *rowq
                 const uint32_t c = kq[u] ? e : 0u;  // a past-the-end thread reads candidate 0
                 sl[u] = s_slot[c];
                 xs2[u] = s_x[c];
-                is[u] = r_lo + s_r[c] - s_Q.rbase;
+                is[u] = r_lo + s_r[c] - Q0.rbase;
             }
-            wkeep_many<WU>(s_Q, loc, edges, xs2, is, kq);
+            wkeep_many<WU>(Q0, loc, edges, xs2, is, kq);
 #pragma unroll
             for (uint32_t u = 0; u < WU; u++)
                 if (kq[u]) atomicOr(&s_keep[sl[u] >> 6], 1ull << (sl[u] & 63));
@@ -330,7 +445,7 @@ __global__ __launch_bounds__(WT) void k_wjoin(const WQ *qs, const uint32_t *rowq
     for (uint32_t e = one ? n : threadIdx.x; e < n; e += WT) {
         const uint32_t slot = s_slot[e], xv = s_x[e];
         const uint64_t r = r_lo + s_r[e];
-        const WQ &Q = one ? s_Q : qs[rowq[r]];
+        const WQ &Q = qs[rowq[r]];
         const uint64_t i = r - Q.rbase;
         bool keep = true;
         // x not in m_i: the row's values eight at a time, every load issued
@@ -345,8 +460,8 @@ __global__ __launch_bounds__(WT) void k_wjoin(const WQ *qs, const uint32_t *rowq
         const uint32_t be = (keep && Q.ne > 1) ? loc[Q.locbase + (uint64_t)(2 * Q.ne + 1) * Q.R + i] : Q.e0;
         for (uint32_t e2 = 0; keep && e2 < Q.ne; e2++) {
             if (e2 == be) continue;
-            keep = in_sorted(edges[Q.efirst + e2].ci + loc[Q.locbase + (uint64_t)e2 * Q.R + i],
-                             loc[Q.locbase + (uint64_t)(Q.ne + e2) * Q.R + i], xv);
+            const uint2 sl = wloc_pair(Q, loc, e2, i);
+            keep = in_sorted(edges[Q.efirst + e2].ci + sl.x, sl.y, xv);
         }
         if (keep) atomicOr(&s_keep[slot >> 6], 1ull << (slot & 63));
     }
@@ -589,7 +704,7 @@ __global__ __launch_bounds__(WT) void k_wlink(const WQ *__restrict__ qs, const u
 // binary search over the group's rows in LDS (survivors are often few, so
 // a map of every slot would not pay).
 template <uint32_t TPW>
-__global__ __launch_bounds__(WT) void k_wlink_bits(const WQ *qs, const uint32_t *rowq, const uint32_t *ci_all,
+__global__ __launch_bounds__(WT) void k_wlink_bits(const WQ *qs, const uint32_t *rowq,
                                              const uint64_t *F, const uint64_t *tile_row, uint64_t ntiles,
                                              const uint32_t *loc, const uint64_t *bitmap, const uint64_t *tile_off,
                                              unsigned long long *acc) {
@@ -680,7 +795,7 @@ __global__ __launch_bounds__(WT) void k_wlink_bits(const WQ *qs, const uint32_t 
             const uint64_t pos = gpos - Q.sbase;
             if (pos < Q.S) {  // always, when the survivor ranges are consistent
                 const uint32_t st0 = (one && staged) ? s_st[lr] : loc[Q.locbase + (uint64_t)(2 * Q.ne) * Q.R + i];
-                const uint32_t x = ci_all[st0 + (uint32_t)(p - Fr)];
+                const uint32_t x = Q.ci[st0 + (uint32_t)(p - Fr)];
                 // the row's values are loaded eight at a time, every load
                 // issued before any is used (clamped columns: valid
                 // addresses), not one dependent round trip per column
@@ -777,6 +892,8 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
         pend.q = act;
         pend.c = c;
         uint64_t Rtot = 0, loctot = 0;
+        std::vector<uint32_t> lab0(nq, 0);  // label of the first edge
+        double least = 1e300;               // |GBA| from which any query's lists would be filtered
         for (uint32_t a = 0; a < nq; a++) {
             WideQuery &x = *act[a];
             const HostQuery &q = *x.q;
@@ -802,10 +919,15 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
                         ed.H = g->H[l];
                         ed.col = i;
                         ed.ci_off = (uint32_t)g->ci_base[l];
-                        if (x.order[i] == x.e0src[j]) Q.e0 = Q.ne;
+                        if (x.order[i] == x.e0src[j]) {
+                            Q.e0 = Q.ne;
+                            lab0[a] = l;
+                        }
                         he.push_back(ed);
                         Q.ne++;
                     }
+            Q.ci = g->ci;
+            least = std::min(least, WF_FACTOR * 2.0 * (double)g->edges[lab0[a]]);
             Q.locbase = loctot;
             for (uint32_t v = 0; v < q.k; v++) Q.qcol[v] = x.col[v];
             for (uint32_t c = 0; c < j; c++)
@@ -820,7 +942,7 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
         uint32_t *bound = s.get<uint32_t>(Rtot, "wide bounds");
         uint32_t *rowq = s.get<uint32_t>(Rtot, "wide row queries");
         uint64_t *F = s.get<uint64_t>(Rtot + 1, "wide offsets F");
-        uint64_t *scal = s.get<uint64_t>(2, "wide scalars");
+        uint64_t *scal = c->mbox_dev + MBOX_SCALARS;  // read by the host without a copy
         GSI_HIP(hipMemcpyAsync(d_q, hq.data(), sizeof(WQ) * nq, hipMemcpyHostToDevice, c->stream));
         GSI_HIP(hipMemcpyAsync(d_e, he.data(), sizeof(WEdge) * he.size(), hipMemcpyHostToDevice, c->stream));
         double lb = 0;
@@ -838,6 +960,63 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
                 x->finish_empty();
             }
             return;
+        }
+        // queries whose rows rescan their first edge's lists many times over:
+        // filter those lists by C(u) once
+        if ((double)gba > least && gba >= WF_MIN_SLOTS) {
+            std::vector<uint64_t> qg;
+            uint64_t *d_qg = s.get<uint64_t>(nq, "wide slots per query");
+            launch(c, "k_wgba", 16.0 * nq, k_wgba, wblocks(nq), WT, (const WQ *)d_q, nq, (const uint64_t *)F, d_qg);
+            read_words(c, d_qg, qg, nq);
+            std::vector<WFilter> fl;
+            uint64_t words = 0, els = 0, blk = 0, rblk = 0, saved = 0;
+            const uint64_t room = c->arena.largest_free() / 4;
+            for (uint32_t a = 0; a < nq; a++) {
+                const uint32_t l = lab0[a];
+                const uint64_t el = 2 * g->edges[l];
+                if (el == 0 || (double)qg[a] <= WF_FACTOR * (double)el) continue;
+                // positions in the compacted array are 32-bit
+                if (els + el >= 0xFFFFFFFFull || 5 * (els + el) + 4096 > room) continue;
+                WFilter f{g->ci + g->ci_base[l], el, words, (uint32_t)blk, (uint32_t)rblk, a, 0};
+                words += (el + 63) / 64 + 1;  // one spare word: a list may end at the label's last element
+                els += el;
+                saved += qg[a] - el;
+                blk += (el + WF_TILES * WT - 1) / (WF_TILES * WT);
+                rblk += (hq[a].R + WT - 1) / WT;
+                fl.push_back(f);
+            }
+            if (saved >= WF_MIN_SLOTS) {
+                const uint32_t nf = (uint32_t)fl.size();
+                WFilter *d_f = s.get<WFilter>(nf, "wide filters");
+                uint64_t *fbits = s.get<uint64_t>(words, "filtered-list bits");
+                uint32_t *wcnt = s.get<uint32_t>(words, "filtered-list word counts");
+                uint64_t *wpre = s.get<uint64_t>(words + 1, "filtered-list word offsets");
+                uint32_t *fn = s.get<uint32_t>(els, "filtered lists");
+                GSI_HIP(hipMemcpyAsync(d_f, fl.data(), sizeof(WFilter) * nf, hipMemcpyHostToDevice, c->stream));
+                fill_u32(c, wcnt, 0, words);  // the spare words
+                launch(c, "k_fn_bits", 4.0 * els, k_wfn_bits, (uint32_t)blk, WT, (const WQ *)d_q, (const WFilter *)d_f,
+                       nf, fbits, wcnt);
+                exclusive_scan(c, wcnt, words, wpre, s);
+                launch(c, "k_fn_compact", 4.0 * els, k_wfn_compact, (uint32_t)blk, WT, (const WFilter *)d_f, nf,
+                       (const uint64_t *)fbits, (const uint64_t *)wpre, fn);
+                launch(c, "k_fn_relocate", 52.0 * WT * rblk, k_wfn_relocate, (uint32_t)rblk, WT, (const WQ *)d_q,
+                       (const WFilter *)d_f, nf, (const uint64_t *)fbits, (const uint64_t *)wpre, loc, bound);
+                exclusive_scan(c, bound, Rtot, F, s, scal);
+                for (auto &f : fl) {
+                    hq[f.q].pre = 1;
+                    hq[f.q].ci = fn;
+                }
+                GSI_HIP(hipMemcpyAsync(d_q, hq.data(), sizeof(WQ) * nq, hipMemcpyHostToDevice, c->stream));
+                read_scalars(c, scal, &gba, 1);  // also orders the uploads above
+                if (gba == 0) {
+                    pend.commit = true;
+                    for (auto *x : act) {
+                        x->levels = x->j;
+                        x->finish_empty();
+                    }
+                    return;
+                }
+            }
         }
         // survivor records per group of tpw tiles when they fit comfortably
         // (8 bytes per slot), else keep bits per tile
@@ -863,22 +1042,21 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
         {
             auto join = [&](auto kern) {
                 launch(c, "k_wjoin", jb, kern, (uint32_t)ngroups, WT, (const WQ *)d_q, (const uint32_t *)rowq,
-                       (const WEdge *)d_e, (const uint32_t *)g->ci, (const uint64_t *)F, (const uint64_t *)trow,
-                       ntiles, gba, (const uint32_t *)loc, bitmap, rec_x, rec_r, tcnt);
+                       (const WEdge *)d_e, (const uint64_t *)F, (const uint64_t *)trow, ntiles,
+                       gba, (const uint32_t *)loc, bitmap, rec_x, rec_r, tcnt);
             };
             if (tpw == 1) join(k_wjoin<1>);
             else if (tpw == 2) join(k_wjoin<2>);
             else if (tpw == 8) join(k_wjoin<8>);
             else join(k_wjoin<4>);
         }
-        exclusive_scan(c, tcnt, ntiles, toff, s, scal + 1);
+        exclusive_scan(c, tcnt, ntiles, toff, s);
         launch(c, "k_wsurv", 48.0 * nq, k_wsurv, wblocks(nq), WT, (const WQ *)d_q, nq, (const uint64_t *)F,
                (const uint64_t *)bitmap, (const uint32_t *)rec_r, (const uint64_t *)trow, ntiles, group,
                (const uint64_t *)toff, gba, sb);
-        std::vector<uint64_t> hsb(4ull * nq);
-        GSI_HIP(hipMemcpyAsync(hsb.data(), sb, 32ull * nq, hipMemcpyDeviceToHost, c->stream));
-        uint64_t Stot;
-        read_scalars(c, scal + 1, &Stot, 1);
+        std::vector<uint64_t> hsb;
+        read_words(c, sb, hsb, 4ull * nq);
+        const uint64_t Stot = hsb[4ull * (nq - 1) + 1];
         // next tables (exact sizes) and result rows
         bool any_final = false;
         double kb = (recs ? 8.0 * Stot : gba / 8.0) + 8.0 * ntiles;
@@ -929,7 +1107,7 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
         } else if (Stot) {
             auto link = [&](auto kern) {
                 launch(c, "k_wlink_bits", kb, kern, (uint32_t)ngroups, WT, (const WQ *)d_q, (const uint32_t *)rowq,
-                       (const uint32_t *)g->ci, (const uint64_t *)F, (const uint64_t *)trow, ntiles,
+                       (const uint64_t *)F, (const uint64_t *)trow, ntiles,
                        (const uint32_t *)loc, (const uint64_t *)bitmap, (const uint64_t *)toff,
                        reinterpret_cast<unsigned long long *>(acc));
             };
@@ -941,10 +1119,10 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
         std::vector<uint64_t> dig;
         if (any_final) {
             launch(c, "k_wdigest", 16.0 * WACC * nq, k_wdigest, wblocks(nq), WT, (const uint64_t *)acc, nq, d_dig);
-            dig.resize(2ull * nq);
-            GSI_HIP(hipMemcpyAsync(dig.data(), d_dig, 16ull * nq, hipMemcpyDeviceToHost, c->stream));
+            read_words(c, d_dig, dig, 2ull * nq);  // and the uploads are done
+        } else {
+            sync(c);  // uploads done
         }
-        sync(c);  // uploads done, digests read
         if (any_final)
             for (uint32_t a = 0; a < nq; a++)
                 if (hq[a].final_level) {

@@ -31,7 +31,7 @@ def world():
     return g, qs, want
 
 
-@pytest.mark.parametrize("arena_mib,bits", [(1024, False), (32, True)])
+@pytest.mark.parametrize("arena_mib,bits", [(1024, False), (12, True)])
 @pytest.mark.parametrize("tiles", [1, 2, 4, 8])
 @pytest.mark.parametrize("count_only", [False, True])
 def test_engine_matches_single_queries(world, arena_mib, bits, tiles, count_only):
@@ -55,4 +55,40 @@ def test_engine_matches_single_queries(world, arena_mib, bits, tiles, count_only
         ran = {k["name"]: k["launches"] for k in ctx.kernel_stats()}
         assert ran.get("k_wlink", 0) > 0
         assert (ran.get("k_wlink_bits", 0) > 0) == bits
+        dg.free()
+
+
+@pytest.mark.parametrize("n,k", [(40, 5), (47, 5)])
+def test_engine_filtered_lists(n, k):
+    """Rows that rescan a complete graph's few lists: the step filters the
+    lists of the queries that would save 2^24 slots, beside one that would
+    not; closed forms (falling factorials per label) and the single path."""
+    import paper_1906_03420_amd as gsi
+    g = w.complete_graph(n)
+    g.vlabel[:] = np.arange(n) % 2
+    na, nb = (n + 1) // 2, n // 2
+    path = [(i, i + 1) for i in range(k - 1)]
+    qs = [w.make_query([0] * k, path, [0] * (k - 1)),
+          w.make_query([i % 2 for i in range(k)], path, [0] * (k - 1)),
+          w.make_query([1] * k, path + [(0, k - 1)], [0] * k),
+          w.make_query([0, 1], [(0, 1)], [0])]
+    ff = lambda x, t: int(np.prod([x - i for i in range(t)], dtype=np.int64))  # noqa: E731
+    want = [ff(na, k), ff(na, (k + 1) // 2) * ff(nb, k // 2), ff(nb, k), na * nb]
+    reps = 8  # of the first query: its last levels alone pass 2^24 slots
+    with gsi.Context(8 << 30, flags=gsi.GSI_CTX_PROFILE) as ctx:
+        dg = ctx.load(g)
+        single = []
+        for q in qs:
+            r = dg.query(q, flags=gsi.GSI_COUNT_ONLY)
+            single.append(r.digest)
+            r.free()
+        ctx.kernel_stats_reset()
+        b = dg.batch(qs + qs[:1] * (reps - 1), flags=gsi.GSI_COUNT_ONLY | gsi.GSI_BATCH_LEVELS_ONLY)
+        counts, digests = b.results()
+        b.free()
+        for i, c in enumerate(counts.tolist()):
+            j = i if i < len(qs) else 0
+            assert c == want[j] and tuple(int(x) for x in digests[i]) == single[j]
+        ran = {x["name"]: x["launches"] for x in ctx.kernel_stats()}
+        assert ran.get("k_fn_bits", 0) > 0 and ran.get("k_fn_relocate", 0) > 0
         dg.free()
