@@ -111,7 +111,6 @@ static std::vector<FusedQuery> run_tier(gsi_graph *g, const std::shared_ptr<Roun
     FStatus *d_st = reinterpret_cast<FStatus *>(ts.get<uint64_t>((uint64_t)n * sizeof(FStatus) / 8, "batch status"));
     uint32_t *counter = ts.get<uint32_t>(1, "batch counter");
     GSI_HIP(hipMemcpyAsync(d_items, items.data(), sizeof(FBatchItem) * n, hipMemcpyHostToDevice, c->stream));
-    fill_u64(c, reinterpret_cast<uint64_t *>(d_st), 0, (uint64_t)n * sizeof(FStatus) / 8);
     fill_u32(c, counter, 0, 1);
     launch_fused_batch(c, t, grid, d_plans, d_items, n, d_M0, scratch, slot_words, kmax, count_only ? nullptr : rd->out,
                        d_st, counter, 0.0);

@@ -6,6 +6,7 @@
 // reports where; the caller finishes the query from that level with the
 // per-level kernels.  Results are identical to the per-level path (same
 // tests, same order: parent row, then ascending x).
+#include <cstddef>
 #include <cstring>
 
 #include "fused.h"
@@ -97,6 +98,9 @@ __device__ __forceinline__ void lds_words(const uint32_t *pre, uint32_t nw, cons
     }
 }
 
+// s_waitcnt operand: vmcnt 0, the other counters unconstrained (gfx9 encoding)
+constexpr int WAIT_VMCNT0 = 0x0F70;
+
 // bitmap words a wave takes per round of the fused join and link
 constexpr uint32_t FU = 2;
 
@@ -111,8 +115,20 @@ constexpr uint32_t fused_table_words() {
 // start of each row's scanned list, the keep bits and their prefix sums,
 // (XS) each slot's element x, so that the link re-reads no list, and two
 // table buffers
+//
+// FusedStat: the words of an FStatus, its per-level sizes (all below 2^32
+// here) in 32 bits
+enum : uint32_t { ST_DONE, ST_LEVEL, ST_ROWS, ST_MLOC, ST_LEVELS, ST_COUNT, ST_DIG0, ST_DIG1, ST_OUT_BASE, FSTAT_HEAD };
+struct FusedStat {
+    uint64_t head[FSTAT_HEAD];
+    uint32_t lv[3 * GSI_MAX_K];  // rows, |GBA| and survivors of each level
+};
+static_assert(sizeof(FStatus) == 8 * (FSTAT_HEAD + 3 * GSI_MAX_K) && offsetof(FStatus, lv_rows) == 8 * FSTAT_HEAD,
+              "FusedStat lists the words of an FStatus");
+
 template <uint32_t FT, uint32_t CR, uint32_t CS, bool XS>
 struct FusedLds {
+    FusedStat s;
     uint32_t F[CR + 1];
     uint32_t st[CR];
     uint64_t bits[CS / 64];
@@ -123,7 +139,39 @@ struct FusedLds {
     uint32_t x[XS ? CS : 1];
     uint32_t mt[2][fused_table_words<FT, XS>()];
 };
-static_assert(sizeof(FusedLds<1024, 4096, 16384, true>) <= 160 * 1024, "fused workgroup LDS");
+// The single-query kernel's LDS: the workgroup's and a copy of the plan.
+struct FusedLevelsLds {
+    FusedLds<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true> q;
+    FPlanArg plan;
+};
+static_assert(sizeof(FusedLevelsLds) <= 160 * 1024, "fused workgroup LDS");
+
+// A value every lane holds alike, in a scalar register.
+__device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename T>
+__device__ __forceinline__ T *uni(T *p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<T *>(((uint64_t)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v));
+}
+
+// What a workgroup reports of its query: kept in LDS while the levels run
+// and written out once at the end (st_flush).  A store to the status inside
+// a level costs its wave the acknowledgement at the next load it waits for,
+// the more so when the status lies in host memory.
+__device__ __forceinline__ void st_clear(FusedStat &s) {
+    uint32_t *w = reinterpret_cast<uint32_t *>(&s);
+    for (uint32_t t = threadIdx.x; t < sizeof(FusedStat) / 4; t += blockDim.x) w[t] = 0;
+}
+// the first wave writes `s` to `st`
+__device__ __forceinline__ void st_flush(const FusedStat &s, FStatus *st) {
+    if (threadIdx.x >= 64) return;
+    for (uint32_t t = threadIdx.x; t < sizeof(FStatus) / 8; t += 64) {
+        uint64_t v;
+        if (t < FSTAT_HEAD) v = s.head[t];
+        else v = s.lv[t - FSTAT_HEAD];
+        reinterpret_cast<uint64_t *>(st)[t] = v;
+    }
+}
 
 // Join levels j0 .. k-1 of one query in one workgroup (see the file
 // comment), starting from the table M0 of R0 rows and j0 columns (column c
@@ -134,7 +182,7 @@ static_assert(sizeof(FusedLds<1024, 4096, 16384, true>) <= 160 * 1024, "fused wo
 template <uint32_t FT, uint32_t CR, uint32_t CS, bool XS>
 __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, const uint32_t *M0, uint32_t R0,
                                             uint32_t ld0, uint32_t *buf0, uint32_t *buf1, uint32_t *loc,
-                                            uint32_t *out, FStatus *st, FusedLds<FT, CR, CS, XS> &L,
+                                            uint32_t *out, FusedLds<FT, CR, CS, XS> &L,
                                             unsigned long long *ocount = nullptr, uint64_t ocap = 0) {
     static_assert(CR == 4 * FT, "each thread scans four rows");
     static_assert(CS / 64 <= FT, "one thread per bitmap word in the survivor scan");
@@ -144,7 +192,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
     uint32_t *s_w = L.w;
 
     const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
-    const uint32_t k = plan->k;
+    const uint32_t k = uni(plan->k);
     const uint32_t cap_rows = plan->cap_rows < CR ? plan->cap_rows : CR;
     const uint32_t cap_slots = plan->cap_slots < CS ? plan->cap_slots : CS;
     const uint32_t *M = M0;
@@ -165,9 +213,9 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             mloc = 0;
         }
         if (tid == 0) {
-            st->level = j;
-            st->rows = R;
-            st->mloc = mloc;
+            L.s.head[ST_LEVEL] = j;
+            L.s.head[ST_ROWS] = R;
+            L.s.head[ST_MLOC] = mloc;
         }
     };
     if (R0 > cap_rows) {  // the first table does not fit
@@ -176,11 +224,11 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
     }
 
     for (uint32_t j = j0; j < k; j++) {
-        const uint32_t ne = plan->lv_ne[j], ef = plan->lv_first[j], e0 = plan->lv_e0[j];
-        const uint64_t *Cu = plan->Cu[j];
+        const uint32_t ne = uni(plan->lv_ne[j]), ef = uni(plan->lv_first[j]), e0 = uni(plan->lv_e0[j]);
+        const uint64_t *Cu = uni(plan->Cu[j]);
         const bool final_level = (j == k - 1);
-        const uint32_t *ci_all = plan->ci_all;
-        if (tid == 0) st->lv_rows[j] = R;
+        const uint32_t *ci_all = uni(plan->ci_all);
+        if (tid == 0) L.s.lv[j] = R;
 
         // locate N(v, l) for every row and linking edge; the row scans the
         // list of e0 (Algorithm 4) or, with `pick`, its shortest one
@@ -188,8 +236,8 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             uint32_t s0 = 0, l0 = 0, ob = NONE32, os = 0, ol = 0xFFFFFFFFu;
             for (uint32_t e = 0; e < ne; e++) {
                 const FEdge &ed = plan->edges[ef + e];
-                const uint32_t v = M[(uint64_t)ed.col * ld + i];
-                const uint2 r = pcsr_find(ed.gl, ed.G, ed.H, v);
+                const uint32_t v = M[(uint64_t)uni(ed.col) * ld + i];
+                const uint2 r = pcsr_find(uni(ed.gl), uni(ed.G), uni(ed.H), v);
                 loc[(uint64_t)e * R + i] = r.x;
                 loc[(uint64_t)(ne + e) * R + i] = r.y;
                 if (e == e0) {
@@ -235,16 +283,16 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
         // values every thread reads from LDS are made wave-uniform, so that
         // the exits below are uniform branches
         const uint32_t gba = __builtin_amdgcn_readfirstlane(s_F[R]);
-        if (tid == 0) st->lv_gba[j] = gba;
+        if (tid == 0) L.s.lv[GSI_MAX_K + j] = gba;
         if (gba > cap_slots) {
             stop(j);
             return;
         }
         if (gba == 0) {
             if (tid == 0) {
-                st->lv_surv[j] = 0;
-                st->levels = j;
-                st->done = 1;
+                L.s.lv[2 * GSI_MAX_K + j] = 0;
+                L.s.head[ST_LEVELS] = j;
+                L.s.head[ST_DONE] = 1;
             }
             return;
         }
@@ -288,7 +336,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                 // x not among the row's values in the columns that can hold
                 // it (those of u's label), four columns at a time; past the
                 // last one the last is read again
-                uint32_t mm = plan->lv_mmask[j];
+                uint32_t mm = uni(plan->lv_mmask[j]);
                 const uint32_t last = mm ? 31u - (uint32_t)__builtin_clz(mm) : 0u;
                 while (mm) {
                     uint32_t cq[4];
@@ -316,7 +364,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                     const uint32_t be = keep ? loc[(uint64_t)(2 * ne + 1) * R + i] : e0;
                     for (uint32_t e = 0; keep && e < ne; e++) {
                         if (e == be) continue;
-                        keep = in_sorted(plan->edges[ef + e].ci + loc[(uint64_t)e * R + i],
+                        keep = in_sorted(uni(plan->edges[ef + e].ci) + loc[(uint64_t)e * R + i],
                                          loc[(uint64_t)(ne + e) * R + i], xr[r]);
                     }
                     kp[r] = keep;
@@ -339,11 +387,11 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             if (tid < nw) s_wpre[tid] = ex;
             __syncthreads();
         }
-        if (tid == 0) st->lv_surv[j] = S;
+        if (tid == 0) L.s.lv[2 * GSI_MAX_K + j] = S;
         if (S == 0) {
             if (tid == 0) {
-                st->levels = j;
-                st->done = 1;
+                L.s.head[ST_LEVELS] = j;
+                L.s.head[ST_DONE] = 1;
             }
             return;
         }
@@ -368,7 +416,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                 return;
             }
             out += b;
-            if (tid == 0) st->out_base = b;
+            if (tid == 0) L.s.head[ST_OUT_BASE] = b;
         }
 
         // link: (m_i, x) at its position; the last level writes rows in
@@ -425,7 +473,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                     uint32_t val[FU][4];
 #pragma unroll
                     for (uint32_t q = 0; q < 4; q++) {
-                        const uint32_t c = u0 + q < k ? plan->qcol[u0 + q] : j;
+                        const uint32_t c = u0 + q < k ? uni(plan->qcol[u0 + q]) : j;
 #pragma unroll
                         for (uint32_t r = 0; r < FU; r++) {
                             const uint32_t mv = M[(uint64_t)(c < j ? c : 0u) * ld + ir[r]];
@@ -464,11 +512,11 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                     ts += L.d[0][q];
                     tx ^= L.d[1][q];
                 }
-                st->digest[0] = ts;
-                st->digest[1] = tx;
-                st->count = S;
-                st->levels = j;
-                st->done = 1;
+                L.s.head[ST_DIG0] = ts;
+                L.s.head[ST_DIG1] = tx;
+                L.s.head[ST_COUNT] = S;
+                L.s.head[ST_LEVELS] = j;
+                L.s.head[ST_DONE] = 1;
             }
             return;
         }
@@ -482,24 +530,30 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
     }
 }
 
-// One query in one workgroup.  The status is cleared here (no separate
-// fill), and, when `b0` is given, the first table M0 = C(u_first) is
+// One query in one workgroup.  When `b0` is given, the first table M0 = C(u_first) is
 // written here too from its bitset (ascending vertex order, R0 entries):
 // each thread counts the set bits of a run of bitset words, an exclusive
 // scan over the workgroup places the runs, and each thread writes its ids.
-// INL: the plan is the kernel argument `inl` (read with scalar loads from
-// the argument segment), else d_plan in device memory.  Two instances, not a
-// select: a pointer that may address either space is generic, and every
-// plan field would be read with vector loads.
+// INL: the plan is the kernel argument `inl`, copied to LDS first (the
+// argument segment is read from host memory, a round trip of its own for
+// every line the levels touch); else d_plan in device memory.  Two
+// instances, not a select: a pointer that may address either space is
+// generic.  At the end the status goes to `st` in one go and the completion
+// word is posted (post_seq) once every wave's rows and tables have left it.
 template <bool INL>
 __global__ __launch_bounds__(1024) void k_fused_levels(const FPlan *d_plan, FPlanArg inl, uint32_t j0, uint32_t *M0,
                                                       uint32_t R0, const uint32_t *b0_runs,
                                                       const uint64_t *b0, uint64_t nwords, uint32_t *buf0,
-                                                      uint32_t *buf1, uint32_t *loc, uint32_t *out, FStatus *st) {
-    __shared__ FusedLds<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true> L;
-    const FPlan *plan = INL ? &inl.p : d_plan;
-    uint64_t *sw = reinterpret_cast<uint64_t *>(st);
-    for (uint32_t t = threadIdx.x; t < sizeof(FStatus) / 8; t += 1024) sw[t] = 0;
+                                                      uint32_t *buf1, uint32_t *loc, uint32_t *out, FStatus *st,
+                                                      uint64_t *seq_slot, uint64_t seq_value) {
+    __shared__ FusedLevelsLds L;
+    const FPlan *plan = INL ? &L.plan.p : d_plan;
+    if (INL) {
+        static_assert(sizeof(FPlanArg) / 4 <= 1024, "one word per thread");
+        if (threadIdx.x < sizeof(FPlanArg) / 4)
+            reinterpret_cast<uint32_t *>(&L.plan)[threadIdx.x] = reinterpret_cast<const uint32_t *>(&inl)[threadIdx.x];
+    }
+    st_clear(L.q.s);
     if (b0) {
         // each wave owns a contiguous run of words (the split the filter's
         // counts used, whose per-run set bits `b0_runs` give the wave its
@@ -534,19 +588,27 @@ __global__ __launch_bounds__(1024) void k_fused_levels(const FPlan *d_plan, FPla
             }
         }
     }
-    __syncthreads();  // status cleared and M0 written before the levels read them
-    fused_query<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true>(plan, j0, M0, R0, R0, buf0, buf1, loc, out, st, L);
+    __syncthreads();  // status cleared, plan copied and M0 written before the levels read them
+    fused_query<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true>(plan, j0, M0, R0, R0, buf0, buf1, loc, out, L.q);
+    // every wave's stores are done before the first one releases them
+    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+    __syncthreads();
+    st_flush(L.q.s, st);
+    if (threadIdx.x == 0) post_seq(seq_slot, seq_value);
 }
 
 void launch_fused(gsi_ctx *c, const FPlan *d_plan, const FPlanArg &inl, uint32_t j0, uint32_t *M0, uint32_t R0,
                   const uint32_t *b0_runs, const uint64_t *b0, uint64_t nwords, uint32_t *buf0, uint32_t *buf1, uint32_t *loc, uint32_t *out,
                   FStatus *d_status, double alg_bytes) {
+    uint64_t seqv = 0;
+    uint64_t *seqp = seq_slot(c, d_status, &seqv);
     if (d_plan)
         launch(c, "k_fused_levels", alg_bytes, k_fused_levels<false>, 1, 1024, d_plan, inl, j0, M0, R0, b0_runs, b0,
-               nwords, buf0, buf1, loc, out, d_status);
+               nwords, buf0, buf1, loc, out, d_status, seqp, seqv);
     else
         launch(c, "k_fused_levels", alg_bytes, k_fused_levels<true>, 1, 1024, d_plan, inl, j0, M0, R0, b0_runs, b0,
-               nwords, buf0, buf1, loc, out, d_status);
+               nwords, buf0, buf1, loc, out, d_status, seqp, seqv);
+    c->seq_armed = seqp != nullptr;
 }
 
 // Persistent batch: each workgroup takes the next query from a shared
@@ -565,14 +627,16 @@ __global__ __launch_bounds__(FT, FT == 256 ? 4 : 1) void k_fused_batch(const uin
     uint32_t *buf0 = slot, *buf1 = slot + (uint64_t)CR * kmax, *loc = slot + 2ull * CR * kmax;
     for (;;) {
         if (threadIdx.x == 0) s_q = atomicAdd(counter, 1u);
+        st_clear(L.s);
         __syncthreads();
         const uint32_t qi = __builtin_amdgcn_readfirstlane(s_q);
         __syncthreads();
         if (qi >= nitems) break;
         const FBatchItem it = items[qi];
         fused_query<FT, CR, CS, false>(reinterpret_cast<const FPlan *>(plans + it.plan_off), 1, M0all + it.m0_off,
-                                       it.R0, it.R0, buf0, buf1, loc, outall ? outall + it.out_off : nullptr,
-                                       sts + qi, L);
+                                       it.R0, it.R0, buf0, buf1, loc, outall ? outall + it.out_off : nullptr, L);
+        __syncthreads();
+        st_flush(L.s, sts + qi);
         __syncthreads();
     }
 }
@@ -608,17 +672,17 @@ __global__ __launch_bounds__(FT) void k_fused_chunks(const FPlan *plan, uint32_t
     for (;;) {
         if (threadIdx.x == 0) {
             if (prev != 0xFFFFFFFFu) {
-                // thread 0 wrote the chunk's status itself
-                const FStatus &p = sts[prev];
-                if (p.done) {
+                // the chunk's status is still in LDS
+                const FusedStat &p = L.s;
+                if (p.head[ST_DONE]) {
                     // totals of the finished chunks
-                    atomicAdd(&sum->digest[0], p.digest[0]);
-                    atomicXor(&sum->digest[1], p.digest[1]);
-                    atomicMax(&sum->levels, p.levels);
-                    for (uint32_t j = j0; j <= p.levels && j < k; j++) {
-                        atomicAdd(&sum->lv_rows[j], p.lv_rows[j]);
-                        atomicAdd(&sum->lv_gba[j], p.lv_gba[j]);
-                        atomicAdd(&sum->lv_surv[j], p.lv_surv[j]);
+                    atomicAdd(&sum->digest[0], p.head[ST_DIG0]);
+                    atomicXor(&sum->digest[1], p.head[ST_DIG1]);
+                    atomicMax(&sum->levels, p.head[ST_LEVELS]);
+                    for (uint32_t j = j0; j <= p.head[ST_LEVELS] && j < k; j++) {
+                        atomicAdd(&sum->lv_rows[j], (uint64_t)p.lv[j]);
+                        atomicAdd(&sum->lv_gba[j], (uint64_t)p.lv[GSI_MAX_K + j]);
+                        atomicAdd(&sum->lv_surv[j], (uint64_t)p.lv[2 * GSI_MAX_K + j]);
                     }
                 } else if (atomicAdd(abort + 1, 1u) + 1 > max_fail) {
                     // too many chunks that do not fit: leave the rest to the caller
@@ -629,14 +693,16 @@ __global__ __launch_bounds__(FT) void k_fused_chunks(const FPlan *plan, uint32_t
         }
         __syncthreads();
         const uint32_t qi = __builtin_amdgcn_readfirstlane(s_q);
+        st_clear(L.s);
         __syncthreads();
         if (qi >= nchunks) break;
         const uint32_t first = qi * chunk_rows;
         const uint32_t rows = min(chunk_rows, R0 - first);
-        fused_query<FT, CR, CS, true>(plan, j0, M0 + first, rows, R0, buf0, buf1, loc, staging, sts + qi, L,
-                                      ocount, staging_words);
+        fused_query<FT, CR, CS, true>(plan, j0, M0 + first, rows, R0, buf0, buf1, loc, staging, L, ocount,
+                                      staging_words);
         prev = qi;
         __syncthreads();
+        st_flush(L.s, sts + qi);
     }
 }
 

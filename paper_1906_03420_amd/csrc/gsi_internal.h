@@ -235,6 +235,12 @@ inline uint64_t *seq_slot(gsi_ctx *c, const void *dst, uint64_t *value) {
 __device__ __forceinline__ void post_seq(uint64_t *slot, uint64_t value) {
     if (slot) __hip_atomic_store(slot, value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
+// One of `total` callers, each after the mailbox words it wrote: the last to
+// draw a ticket posts the completion word (nothing without a slot).
+__device__ __forceinline__ void post_last(unsigned long long *tickets, uint32_t total, uint64_t *slot, uint64_t value) {
+    if (slot && __hip_atomic_fetch_add(tickets, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_SYSTEM) + 1 == total)
+        post_seq(slot, value);
+}
 // Reads back `n` uint64 values from device memory, or from the mailbox
 // without a copy (synchronises the stream either way).
 void read_scalars(gsi_ctx *c, const uint64_t *dev, uint64_t *host, int n);

@@ -155,6 +155,13 @@ void make_multi(HostQuery &q) {
 }
 
 // ------------------------------------------------------------------ filter
+// The fused workgroup builds M0 from root bitsets of at most this many
+// words (2^20 vertices); a larger bitset is emitted grid-wide first (k_m0),
+// since one CU reading it all costs more: on 8.4M vertices the fused launches
+// went from 6.2 to 4.1 ms per 50 queries for 0.2 ms of added launches.
+constexpr uint64_t M0_FUSED_MAX_WORDS = 16384;
+constexpr uint32_t M0_RUNS = 64;  // runs (workgroups of k_m0) of a larger bitset
+
 struct FilterArgs {
     uint32_t k;
     uint32_t label_only;
@@ -208,7 +215,8 @@ static void query_signatures(const HostQuery &q, FilterArgs &fa, bool homo = fal
 constexpr uint32_t FILTER_TILES = 1;
 
 __global__ __launch_bounds__(QT) void k_filter(const uint32_t *sig, uint32_t n, uint64_t nwords, FilterArgs fa,
-                                              uint64_t *bits) {
+                                              uint64_t *bits, unsigned long long *acc) {
+    if (blockIdx.x == 0 && threadIdx.x <= fa.k) acc[threadIdx.x] = 0;  // for k_bit_counts
     const uint32_t need = fa.label_only ? 0u : fa.word_mask;
     const uint32_t K = fa.k;
     const uint32_t lane = lane_id();
@@ -258,9 +266,13 @@ __global__ __launch_bounds__(QT) void k_filter(const uint32_t *sig, uint32_t n, 
 
 // counts[r] = set bits of bitset row r (one 1024-thread workgroup per row);
 // wave w counts run w of the row's words (BITS_RUNS runs of equal length)
-// and, with `runs`, writes that count to runs[r * BITS_RUNS + w]
+// and, with `runs`, writes that count to runs[r * BITS_RUNS + w].  With
+// `seq_slot` (counts in the mailbox) the workgroup that draws the last of the
+// tickets (acc[gridDim.x], zeroed by the filter) posts the completion word,
+// which saves the launch of a kernel that posts.
 __global__ __launch_bounds__(1024) void k_bit_counts(const uint64_t *bits, uint64_t nwords, uint32_t *counts,
-                                                    uint32_t *runs) {
+                                                    uint32_t *runs, unsigned long long *acc, uint64_t *seq_slot,
+                                                    uint64_t seq_value) {
     static_assert(BITS_RUNS == 1024 / 64, "one run per wave");
     __shared__ uint32_t s_w[16];
     const uint64_t *row = bits + (uint64_t)blockIdx.x * nwords;
@@ -277,11 +289,46 @@ __global__ __launch_bounds__(1024) void k_bit_counts(const uint64_t *bits, uint6
     if (lane_id() == 0 && runs) runs[(uint64_t)blockIdx.x * BITS_RUNS + wv] = sum;
     if (lane_id() == 0) s_w[threadIdx.x >> 6] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t t = 0;
-        for (int w = 0; w < 16; w++) t += s_w[w];
-        counts[blockIdx.x] = t;
-    }
+    if (threadIdx.x) return;
+    uint32_t t = 0;
+    for (int w = 0; w < 16; w++) t += s_w[w];
+    counts[blockIdx.x] = t;
+    post_last(acc + gridDim.x, gridDim.x, seq_slot, seq_value);
+}
+
+// The same on bitsets of more words: gridDim.x runs a row, a workgroup each.
+// A run's workgroup adds its count and one arrival to the row's accumulator
+// acc[r] in one atomic, so the one that completes the row knows its total
+// without a fence.  For 12 rows of 2^17 words one workgroup per row took 19
+// us, 64 runs a row take 9, 256 took 32 (same-address atomics).
+__global__ __launch_bounds__(QT) void k_bit_counts_wide(const uint64_t *bits, uint64_t nwords, uint32_t *counts,
+                                                       uint32_t *runs, unsigned long long *acc, uint64_t *seq_slot,
+                                                       uint64_t seq_value) {
+    __shared__ uint32_t s_w[QT / 64];
+    const uint32_t r = blockIdx.y;
+    const uint64_t *row = bits + (uint64_t)r * nwords;
+    const uint64_t per = (nwords + gridDim.x - 1) / gridDim.x;
+    const uint64_t ws = per * blockIdx.x < nwords ? per * blockIdx.x : nwords;
+    const uint64_t we = ws + per < nwords ? ws + per : nwords;
+    uint32_t sum = 0;
+    uint64_t q = ws + threadIdx.x;
+    for (; q + 3 * QT < we; q += 4 * QT)
+        sum += (uint32_t)(__popcll(row[q]) + __popcll(row[q + QT]) + __popcll(row[q + 2 * QT]) +
+                          __popcll(row[q + 3 * QT]));
+    for (; q < we; q += QT) sum += (uint32_t)__popcll(row[q]);
+    sum = wave_sum(sum);
+    if (lane_id() == 0) s_w[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x) return;
+    uint32_t t = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < QT / 64; w++) t += s_w[w];
+    if (runs) runs[(uint64_t)r * gridDim.x + blockIdx.x] = t;
+    // arrivals above bit 40: a row has fewer than 2^32 bits
+    const uint64_t old = atomicAdd(acc + r, (1ull << 40) | t);
+    if ((old >> 40) + 1 != gridDim.x) return;
+    counts[r] = (uint32_t)(old & ((1ull << 40) - 1)) + t;
+    post_last(acc + gridDim.y, gridDim.y, seq_slot, seq_value);
 }
 
 // Multi-labelled graphs (Sec. VII-B): the signature test lets through the
@@ -318,14 +365,34 @@ __global__ __launch_bounds__(QT) void k_label_refine(uint64_t *bits, uint64_t nw
     if (keep != *word) *word = keep;
 }
 
+// runs a row's set bits are counted in: as many as the fused workgroup has
+// waves when it may emit the roots itself
+static uint32_t bit_runs(uint64_t nwords) { return nwords <= M0_FUSED_MAX_WORDS ? BITS_RUNS : M0_RUNS; }
+
+// counts (and, with `runs`, the counts of the runs) of k bitsets
+static void bit_counts(gsi_ctx *c, uint32_t k, const uint64_t *bits, uint64_t nwords, uint32_t *counts, uint32_t *runs,
+                       unsigned long long *acc) {
+    uint64_t seqv = 0;
+    uint64_t *seqp = seq_slot(c, counts, &seqv);
+    if (nwords <= M0_FUSED_MAX_WORDS)
+        launch(c, "k_filter_counts", 8.0 * k * nwords, k_bit_counts, k, 1024, bits, nwords, counts, runs, acc, seqp,
+               seqv);
+    else
+        launch(c, "k_filter_counts", 8.0 * k * nwords, k_bit_counts_wide, dim3(M0_RUNS, k), QT, bits, nwords, counts,
+               runs, acc, seqp, seqv);
+    c->seq_armed = seqp != nullptr;
+}
+
 static void launch_filter(gsi_ctx *c, gsi_graph *g, const FilterArgs &fa, uint64_t *bits, uint32_t *counts,
                           uint32_t *runs, const HostQuery *mq = nullptr) {
+    Scratch s(c);
+    unsigned long long *acc = s.get<unsigned long long>(GSI_MAX_K + 1, "count accumulators");
     const uint64_t nwords = ((uint64_t)g->n + 63) / 64;
     const uint32_t nb = nblocks(g->n);
     const uint32_t need = fa.label_only ? 0u : fa.word_mask;
     double bytes = 4.0 * g->n * (1 + __builtin_popcount(need)) + (double)fa.k * nwords * 8;
     const uint32_t nfb = (nb + FILTER_TILES - 1) / FILTER_TILES;
-    launch(c, "k_filter", bytes, k_filter, nfb, QT, (const uint32_t *)g->sig, g->n, nwords, fa, bits);
+    launch(c, "k_filter", bytes, k_filter, nfb, QT, (const uint32_t *)g->sig, g->n, nwords, fa, bits, acc);
     if (g->multi && mq) {
         RefineArgs ra;
         memset(&ra, 0, sizeof(ra));
@@ -340,8 +407,7 @@ static void launch_filter(gsi_ctx *c, gsi_graph *g, const FilterArgs &fa, uint64
         launch(c, "k_label_refine", 16.0 * fa.k * nwords, k_label_refine, dim3(nblocks(nwords), fa.k), QT, bits,
                nwords, (const uint32_t *)g->vl_off, (const uint32_t *)g->vl_lab, ra);
     }
-    launch(c, "k_filter_counts", 8.0 * fa.k * nwords, k_bit_counts, fa.k, 1024, (const uint64_t *)bits, nwords,
-           counts, runs);
+    bit_counts(c, fa.k, bits, nwords, counts, runs, acc);
 }
 
 // Batched filter: the query vertices of many queries, 32 per pass, all
@@ -359,11 +425,29 @@ static void launch_filter(gsi_ctx *c, gsi_graph *g, const FilterArgs &fa, uint64
 // them to part[(pass * 32 + u) * gridDim.x + workgroup].
 constexpr uint32_t FM_TILE = 1024;
 
+template <bool ARG>
+struct FilterOne {};
+template <>
+struct FilterOne<true> {
+    FilterArgs fa;
+};
+__device__ __forceinline__ const FilterArgs &filter_pass(const FilterArgs *, const FilterOne<true> &one) {
+    return one.fa;
+}
+__device__ __forceinline__ const FilterArgs &filter_pass(const FilterArgs *passes, const FilterOne<false> &) {
+    return passes[blockIdx.y];
+}
+
+// ARG: the one pass is the kernel argument `arg` (a single query, which
+// saves its upload), `part` is not written (the counts come from the
+// bitsets) and the accumulators of k_bit_counts are cleared.
+template <bool ARG>
 __global__ __launch_bounds__(QT) void k_filter_multi(const uint32_t *sig, uint32_t n, uint64_t nwords,
-                                                    const FilterArgs *__restrict__ passes, uint64_t *bits,
-                                                    uint32_t *part) {
+                                                    const FilterArgs *__restrict__ passes, FilterOne<ARG> arg,
+                                                    uint64_t *bits, uint32_t *part, unsigned long long *acc) {
     constexpr uint32_t TW = FM_TILE / 64;  // bitset words per round
-    const FilterArgs &fa = passes[blockIdx.y];
+    const FilterArgs &fa = filter_pass(passes, arg);
+    if (ARG && blockIdx.x == 0 && threadIdx.x <= fa.k) acc[threadIdx.x] = 0;
     __shared__ uint32_t s_q[GSI_MAX_K][GSI_SIG_WORDS];
     __shared__ uint32_t s_dst[GSI_MAX_K];
     __shared__ uint32_t s_cnt[GSI_MAX_K];
@@ -467,7 +551,7 @@ __global__ __launch_bounds__(QT) void k_filter_multi(const uint32_t *sig, uint32
         if (threadIdx.x == 0) s_n = 0;
         __syncthreads();
     }
-    if (threadIdx.x < GSI_MAX_K)
+    if (!ARG && threadIdx.x < GSI_MAX_K)
         part[((uint64_t)blockIdx.y * GSI_MAX_K + threadIdx.x) * gridDim.x + blockIdx.x] = s_cnt[threadIdx.x];
 }
 
@@ -533,8 +617,8 @@ void run_filter_many(gsi_graph *g, const std::vector<const HostQuery *> &qs, con
     uint32_t *part = s.get<uint32_t>((uint64_t)npass * GSI_MAX_K * nb, "filter partial counts");
     GSI_HIP(hipMemcpyAsync(dp, passes.data(), sizeof(FilterArgs) * npass, hipMemcpyHostToDevice, c->stream));
     const double bytes = 4.0 * g->n * words + (double)all.size() * nwords * 8;
-    launch(c, "k_filter", bytes, k_filter_multi, dim3(nb, npass), QT, (const uint32_t *)g->sig, g->n, nwords,
-           (const FilterArgs *)dp, bits, part);
+    launch(c, "k_filter", bytes, k_filter_multi<false>, dim3(nb, npass), QT, (const uint32_t *)g->sig, g->n, nwords,
+           (const FilterArgs *)dp, FilterOne<false>{}, bits, part, (unsigned long long *)nullptr);
     launch(c, "k_filter_counts", 4.0 * nb * all.size(), k_filter_counts_multi, dim3(GSI_MAX_K, npass), QT,
            (const uint32_t *)part, nb, (const FilterArgs *)dp, counts);
     sync(c);  // `passes` is read by the copy above
@@ -545,35 +629,29 @@ void run_filter_many(gsi_graph *g, const std::vector<const HostQuery *> &qs, con
 // LDS and tested against the query vertices of that label only.  Counts and
 // per-run counts come from the bitsets (k_bit_counts), as in launch_filter.
 constexpr bool GROUPED_SINGLE_FILTER = true;
-constexpr size_t PINNED_FILTER_ARGS = 5120;  // staging offset in c->pinned (status region, past the chunk summary)
 static void launch_filter_grouped(gsi_ctx *c, gsi_graph *g, const FilterArgs &f, uint64_t *bits, uint32_t *counts,
                                   uint32_t *runs) {
-    static_assert(PINNED_FILTER_ARGS >= 4096 + sizeof(FChunkSummary) &&
-                      PINNED_FILTER_ARGS + sizeof(FilterArgs) <= 8192,
-                  "filter arguments between the chunk summary and the plans");
-    FilterArgs *fa = reinterpret_cast<FilterArgs *>(reinterpret_cast<char *>(c->pinned) + PINNED_FILTER_ARGS);
+    FilterOne<true> one;
+    FilterArgs &fa = one.fa;
     uint32_t idx[GSI_MAX_K];
     for (uint32_t u = 0; u < f.k; u++) idx[u] = u;
     std::stable_sort(idx, idx + f.k, [&](uint32_t x, uint32_t y) { return f.q[x][0] < f.q[y][0]; });
-    memset(fa, 0, sizeof(*fa));
-    fa->k = f.k;
-    fa->word_mask = f.word_mask;
+    memset(&fa, 0, sizeof(fa));
+    fa.k = f.k;
+    fa.word_mask = f.word_mask;
     for (uint32_t t = 0; t < f.k; t++) {
-        fa->dst[t] = f.dst[idx[t]];
-        memcpy(fa->q[t], f.q[idx[t]], sizeof(fa->q[t]));
+        fa.dst[t] = f.dst[idx[t]];
+        memcpy(fa.q[t], f.q[idx[t]], sizeof(fa.q[t]));
     }
     Scratch s(c);
     const uint64_t nwords = ((uint64_t)g->n + 63) / 64;
     const uint32_t nrounds = (uint32_t)(((uint64_t)g->n + FM_TILE - 1) / FM_TILE);
     const uint32_t nb = std::max<uint32_t>(1, std::min<uint32_t>(nrounds, 8192));
-    FilterArgs *dp = reinterpret_cast<FilterArgs *>(s.get<uint32_t>(sizeof(FilterArgs) / 4, "filter pass"));
-    uint32_t *part = s.get<uint32_t>((uint64_t)GSI_MAX_K * nb, "filter partial counts");
-    GSI_HIP(hipMemcpyAsync(dp, fa, sizeof(FilterArgs), hipMemcpyHostToDevice, c->stream));
+    unsigned long long *acc = s.get<unsigned long long>(GSI_MAX_K + 1, "count accumulators");
     const double bytes = 4.0 * g->n * (1 + __builtin_popcount(f.word_mask)) + (double)f.k * nwords * 8;
-    launch(c, "k_filter", bytes, k_filter_multi, dim3(nb, 1), QT, (const uint32_t *)g->sig, g->n, nwords,
-           (const FilterArgs *)dp, bits, part);
-    launch(c, "k_filter_counts", 8.0 * f.k * nwords, k_bit_counts, f.k, 1024, (const uint64_t *)bits, nwords, counts,
-           runs);
+    launch(c, "k_filter", bytes, k_filter_multi<true>, dim3(nb, 1), QT, (const uint32_t *)g->sig, g->n, nwords,
+           (const FilterArgs *)nullptr, one, bits, (uint32_t *)nullptr, acc);
+    bit_counts(c, f.k, bits, nwords, counts, runs, acc);
 }
 
 static void filter_impl(gsi_graph *g, const HostQuery &q, bool label_only, uint64_t *bits, uint32_t *counts,
@@ -594,19 +672,42 @@ void run_filter(gsi_graph *g, const HostQuery &q, uint64_t *bits, uint32_t *coun
 }
 
 // ----------------------------------------------------- M0 from a bitset
-__global__ void k_word_popc(const uint64_t *bits, uint64_t nwords, uint32_t *cnt) {
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nwords) cnt[i] = (uint32_t)__popcll(bits[i]);
-}
-__global__ void k_word_emit(const uint64_t *bits, uint64_t nwords, const uint64_t *off, uint32_t *out) {
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nwords) return;
-    uint64_t b = bits[i];
-    uint64_t o = off[i];
-    while (b) {
-        uint32_t t = (uint32_t)__ffsll((unsigned long long)b) - 1;
-        out[o++] = (uint32_t)(i * 64 + t);
-        b &= b - 1;
+// One workgroup per run of the row's words: the set bits of the runs before
+// it (counted by the filter) give its first row, a scan of its words' set
+// bits the rest.  One launch where popcounts, their scan and the emission
+// took five.
+__global__ __launch_bounds__(QT) void k_m0(const uint64_t *row, uint64_t nwords, const uint32_t *runs, uint32_t *out) {
+    __shared__ uint32_t s_w[QT / 64];
+    const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+    uint32_t before = 0;
+    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += QT) before += runs[b];
+    before = wave_sum(before);
+    if (lane == 0) s_w[w] = before;
+    __syncthreads();
+    uint32_t at = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < QT / 64; q++) at += s_w[q];
+    const uint64_t per = (nwords + gridDim.x - 1) / gridDim.x;
+    const uint64_t ws = per * blockIdx.x < nwords ? per * blockIdx.x : nwords;
+    const uint64_t we = ws + per < nwords ? ws + per : nwords;
+    for (uint64_t c0 = ws; c0 < we; c0 += QT) {
+        const uint64_t i = c0 + threadIdx.x;
+        uint64_t b = i < we ? row[i] : 0ull;
+        const uint32_t pc = (uint32_t)__popcll(b);
+        const uint32_t inc = wave_inclusive_sum(pc);
+        __syncthreads();  // s_w read by the round before
+        if (lane == 63) s_w[w] = inc;
+        __syncthreads();
+        uint32_t o = at + inc - pc;
+#pragma unroll
+        for (uint32_t q = 0; q < QT / 64; q++) {
+            o += q < w ? s_w[q] : 0u;
+            at += s_w[q];
+        }
+        while (b) {
+            out[o++] = (uint32_t)(i * 64 + (uint32_t)__builtin_ctzll(b));
+            b &= b - 1;
+        }
     }
 }
 
@@ -776,12 +877,6 @@ __global__ __launch_bounds__(QT) void k_fn_relocate(LevelArgs a, const uint64_t 
 // |GBA| over the label's directed entries from which the level filters its
 // first-edge lists once for the whole level
 constexpr double FN_FACTOR = 2.0;
-// The fused workgroup builds M0 from root bitsets of at most this many
-// words (2^20 vertices); a larger bitset is emitted grid-wide first
-// (popcounts, scan, emit), since one CU reading it all costs more: on
-// 8.4M vertices the fused launches went from 6.2 to 4.1 ms per 50 queries
-// for 0.8 ms of added launches.
-constexpr uint64_t M0_FUSED_MAX_WORDS = 16384;
 
 // The per-level join and link work on tiles of SPT x 256 |GBA| slots.  On
 // large levels (SPT = 4) a 256-thread workgroup takes four consecutive
@@ -1847,7 +1942,7 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
     uint32_t *dcnt = reinterpret_cast<uint32_t *>(c->mbox_dev + MBOX_COUNTS);
     uint64_t *dscal = c->mbox_dev + MBOX_SCALARS;
     auto tf = std::chrono::steady_clock::now();
-    uint32_t *druns = s.get<uint32_t>((uint64_t)k * BITS_RUNS, "candidate run counts");
+    uint32_t *druns = s.get<uint32_t>((uint64_t)k * bit_runs(nwords), "candidate run counts");
     filter_impl(g, q, (flags & GSI_FILTER_LABEL_ONLY) != 0, bits, dcnt, homo, druns);
     std::vector<uint32_t> cand(k);
     {
@@ -1901,12 +1996,9 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
     const bool m0_in_fused = k >= 2 && !try_chunks && !(flags & GSI_NO_FUSED) && R <= fcap_rows &&
                              fcap_slots >= 64 && nwords <= M0_FUSED_MAX_WORDS;
     if (!m0_in_fused) {
-        Scratch s0(c);
-        uint32_t *wc = s0.get<uint32_t>(nwords, "word counts");
-        uint64_t *wo = s0.get<uint64_t>(nwords + 1, "word offsets");
-        launch(c, "k_word_popc", 8.0 * nwords, k_word_popc, nblocks(nwords), QT, b0, nwords, wc);
-        exclusive_scan(c, wc, nwords, wo, s0);
-        launch(c, "k_word_emit", 16.0 * nwords + 4.0 * R, k_word_emit, nblocks(nwords), QT, b0, nwords, (const uint64_t *)wo, M);
+        const uint32_t nr = bit_runs(nwords);
+        launch(c, "k_m0", 8.0 * nwords + 4.0 * R, k_m0, nr, QT, b0, nwords,
+               (const uint32_t *)druns + (uint64_t)order[0] * nr, M);
     }
     st.rows[0] = R;
 
