@@ -256,6 +256,11 @@ void fill_u64(gsi_ctx *c, uint64_t *p, uint64_t value, uint64_t n);
 // `total` is given the sum is also written there (device memory).
 void exclusive_scan(gsi_ctx *c, const uint32_t *in, uint64_t n, uint64_t *out, Scratch &s,
                     uint64_t *total = nullptr);
+// The scan of one count per tile of `per` slots, *slots slots (device
+// memory) in all, in one workgroup; no tiles (out[0] = *total = 0) when there
+// are more than `cap` slots.  `in` is 16-byte aligned.
+void exclusive_scan_tiles(gsi_ctx *c, const uint32_t *in, const uint64_t *slots, uint32_t per, uint64_t cap,
+                          uint64_t *out, uint64_t *total);
 // Stable sort of n 64-bit keys by their bits [lo, hi).  Returns true if the
 // result ended in tmp.
 bool key_sort(gsi_ctx *c, uint32_t n, uint64_t *a, uint64_t *tmp, int lo, int hi, Scratch &s);

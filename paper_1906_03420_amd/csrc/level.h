@@ -84,9 +84,14 @@ struct LevelArgs {
     uint64_t *scan_total;
     uint64_t *seq_slot;
     uint64_t seq_value;
-    // 1: R <= 256, the join finds each tile's rows in F itself and writes
-    // tile_row for the link (no k_tile_rows launch)
+    // 1: the join finds each tile's rows in F itself and writes tile_row for
+    // the link (no k_tile_rows launch)
     uint32_t rows_in_join;
+    // a join launched before the host knows |GBA| reads it here and, when it
+    // is above gba_cap (what the launch and its outputs were sized for),
+    // does nothing; nullptr otherwise
+    const uint64_t *gba_dev;
+    uint64_t gba_cap;
 };
 
 // The located (start, length) of linking edge e for row i

@@ -107,34 +107,66 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_apply(const uint32_t *in,
     }
 }
 
-// whole scan in one workgroup (1024 threads x 8 consecutive items), for
-// inputs of at most SMALL_SCAN items: one launch instead of three
-constexpr int SMALL_SCAN = 1024 * SCAN_ITEMS;
+// whole scan in one workgroup, rounds of 1024 threads x 8 consecutive items:
+// one launch instead of three.  A round's sums go through LDS, so that they
+// are written in order.  With `slots` the items are the tiles of *slots slots
+// (`per` each), none when there are more than `cap`.
 __global__ __launch_bounds__(1024) void k_scan_small(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *total,
-                                                    uint64_t *seqp, uint64_t seqv) {
-    uint64_t base = (uint64_t)threadIdx.x * SCAN_ITEMS;
-    uint32_t v[SCAN_ITEMS];
-    uint64_t s = 0;
-#pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; i++) {
-        uint64_t idx = base + i;
-        v[i] = idx < n ? in[idx] : 0;
-        s += v[i];
+                                                    uint64_t *seqp, uint64_t seqv, const uint64_t *slots,
+                                                    uint32_t per, uint64_t cap) {
+    constexpr uint32_t ROUND = 1024 * SCAN_ITEMS;
+    __shared__ uint64_t s_out[ROUND + ROUND / 16];  // one spare word in 16: a thread's 8 words start at 16 banks
+    if (slots) {
+        const uint64_t g = *slots;
+        n = g > cap ? 0 : (g + per - 1) / per;
     }
-    uint64_t tot;
-    uint64_t run = block_exclusive_sum<1024>(s, &tot);
+    uint64_t carry = 0;
+    for (uint64_t c0 = 0; c0 < n; c0 += ROUND) {
+        const uint64_t base = c0 + (uint64_t)threadIdx.x * SCAN_ITEMS;
+        uint32_t v[SCAN_ITEMS];
+        uint64_t s = 0;
+        if (base + SCAN_ITEMS <= n) {
+            const uint4 *q = reinterpret_cast<const uint4 *>(in + base);  // `in` is 16-byte aligned
 #pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; i++) {
-        uint64_t idx = base + i;
-        if (idx < n) out[idx] = run;
-        run += v[i];
+            for (int i = 0; i < SCAN_ITEMS / 4; i++) {
+                const uint4 x = q[i];
+                v[4 * i] = x.x;
+                v[4 * i + 1] = x.y;
+                v[4 * i + 2] = x.z;
+                v[4 * i + 3] = x.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < SCAN_ITEMS; i++) v[i] = base + i < n ? in[base + i] : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < SCAN_ITEMS; i++) s += v[i];
+        uint64_t tot;
+        uint64_t run = carry + block_exclusive_sum<1024>(s, &tot);
+#pragma unroll
+        for (int i = 0; i < SCAN_ITEMS; i++) {
+            const uint32_t x = threadIdx.x * SCAN_ITEMS + i;
+            s_out[x + x / 16] = run;
+            run += v[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < SCAN_ITEMS; i++) {
+            const uint32_t x = i * 1024 + threadIdx.x;
+            if (c0 + x < n) out[c0 + x] = s_out[x + x / 16];
+        }
+        carry += tot;
+        __syncthreads();
     }
     if (threadIdx.x == 0) {
-        out[n] = tot;
-        if (total) *total = tot;
+        out[n] = carry;
+        if (total) *total = carry;
         post_seq(seqp, seqv);
     }
 }
+
+// items up to which one workgroup scans, in rounds of 8,192
+constexpr uint64_t SMALL_SCAN = 4 * 8192;
 
 void exclusive_scan(gsi_ctx *c, const uint32_t *in, uint64_t n, uint64_t *out, Scratch &s, uint64_t *total) {
     if (n == 0) {
@@ -144,8 +176,9 @@ void exclusive_scan(gsi_ctx *c, const uint32_t *in, uint64_t n, uint64_t *out, S
     }
     uint64_t seqv = 0;
     uint64_t *seqp = seq_slot(c, total, &seqv);
-    if (n <= (uint64_t)SMALL_SCAN) {
-        launch(c, "k_scan_small", 12.0 * n, k_scan_small, 1, 1024, in, n, out, total, seqp, seqv);
+    if (n <= SMALL_SCAN && (reinterpret_cast<uintptr_t>(in) & 15) == 0) {
+        launch(c, "k_scan_small", 12.0 * n, k_scan_small, 1, 1024, in, n, out, total, seqp, seqv,
+               (const uint64_t *)nullptr, 0u, (uint64_t)0);
         c->seq_armed = seqp != nullptr;
         return;
     }
@@ -159,6 +192,16 @@ void exclusive_scan(gsi_ctx *c, const uint32_t *in, uint64_t n, uint64_t *out, S
     // need not wait for out[]: stream order makes later launches see out[]
     c->seq_armed = seqp != nullptr;
     s.drop(part);
+}
+
+void exclusive_scan_tiles(gsi_ctx *c, const uint32_t *in, const uint64_t *slots, uint32_t per, uint64_t cap,
+                          uint64_t *out, uint64_t *total) {
+    uint64_t seqv = 0;
+    uint64_t *seqp = seq_slot(c, total, &seqv);
+    const double tiles = (double)((cap + per - 1) / per);
+    launch(c, "k_scan_small", 12.0 * tiles, k_scan_small, 1, 1024, in, (uint64_t)0, out, total, seqp, seqv, slots,
+           per, cap);
+    c->seq_armed = seqp != nullptr;
 }
 
 // ------------------------------------------------------- 64-bit key sort

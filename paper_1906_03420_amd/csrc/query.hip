@@ -885,6 +885,9 @@ constexpr double FN_FACTOR = 2.0;
 // each thread has four independent gathers in flight; small levels keep
 // one slot per thread (SPT = 1) and four times as many workgroups.
 constexpr uint64_t WIDE_TILE_SLOTS = 1ull << 20;  // |GBA| from which SPT = 4
+// least slots a join launched before |GBA| is known is sized for (256
+// workgroups; those past the last slot leave at once)
+constexpr uint64_t SPEC_MIN_SLOTS = 1ull << 16;
 // Candidates a join thread tests at once (keep_many).  The join is bound by
 // its gathers (their issue and their latency), so waves in flight matter
 // more than loads per thread: two candidates per thread fit in 64 VGPRs,
@@ -956,32 +959,37 @@ __device__ __forceinline__ void find_row(const LevelArgs &a, const TileRows &t, 
 // slot s reads ci_all[s_base[s_row[s]] + s].  s_row must be zero on entry,
 // published by a barrier.
 template <uint32_t SPT>
-__device__ __forceinline__ TileRows stage_slot_rows(const LevelArgs &a, uint64_t tile, uint32_t *s_row,
+__device__ __forceinline__ TileRows stage_slot_rows(const LevelArgs &a, uint64_t tile, uint64_t gba, uint32_t *s_row,
                                                     uint32_t *s_base, uint32_t *s_w) {
     constexpr uint32_t TS = SPT * QT;
     TileRows t;
     if (a.rows_in_join) {
-        // at most 256 rows: wave 0 counts the row starts at or before the
-        // tile's first slot and the next tile's (four per lane), which gives
-        // the rows holding them; the link reads tile_row[tile] later
-        __shared__ uint32_t s_rr[2];
+        // wave 0 finds the rows holding the tile's first slot and the next
+        // tile's: the largest i with F[i] <= p.  A round probes 64 rows of
+        // the range each search is down to (two rounds for 4,096 rows, three
+        // for 262,144), the searches' loads together; the link reads
+        // tile_row[tile] later.
+        __shared__ uint64_t s_rr[2];
         if (threadIdx.x < 64) {
             const uint64_t p0 = tile * TS, p1 = p0 + TS;
-            uint32_t c0 = 0, c1 = 0;
-#pragma unroll
-            for (uint32_t k = 0; k < 4; k++) {
-                const uint64_t r = 4ull * threadIdx.x + k;
-                const uint64_t f = a.F[r < a.R ? r : 0];
-                c0 += (r < a.R && f <= p0) ? 1u : 0u;
-                c1 += (r < a.R && f <= p1) ? 1u : 0u;
+            uint64_t l0 = 0, l1 = 0, n0 = a.R, n1 = a.R;
+            while (n0 > 1 || n1 > 1) {
+                const uint64_t d0 = (n0 + 63) / 64, d1 = (n1 + 63) / 64;
+                const uint64_t o0 = threadIdx.x * d0, o1 = threadIdx.x * d1;
+                const uint64_t f0 = a.F[l0 + (o0 < n0 ? o0 : 0)], f1 = a.F[l1 + (o1 < n1 ? o1 : 0)];
+                // F[l0] <= p0 and F[l1] <= p1: the first probe always counts
+                const uint32_t c0 = (uint32_t)__popcll(__ballot(o0 < n0 && f0 <= p0)) - 1;
+                const uint32_t c1 = (uint32_t)__popcll(__ballot(o1 < n1 && f1 <= p1)) - 1;
+                l0 += c0 * d0;
+                l1 += c1 * d1;
+                n0 = n0 - c0 * d0 < d0 ? n0 - c0 * d0 : d0;
+                n1 = n1 - c1 * d1 < d1 ? n1 - c1 * d1 : d1;
             }
-            c0 = wave_sum(c0);
-            c1 = wave_sum(c1);
             if (threadIdx.x == 0) {
-                s_rr[0] = c0 - 1;
-                s_rr[1] = p1 < a.gba ? c1 - 1 : (uint32_t)(a.R - 1);
-                const_cast<uint64_t *>(a.tile_row)[tile] = c0 - 1;
-                if (tile + 1 == gridDim.x) const_cast<uint64_t *>(a.tile_row)[tile + 1] = a.R - 1;
+                s_rr[0] = l0;
+                s_rr[1] = p1 < gba ? l1 : a.R - 1;
+                const_cast<uint64_t *>(a.tile_row)[tile] = l0;
+                if (p1 >= gba) const_cast<uint64_t *>(a.tile_row)[tile + 1] = a.R - 1;
             }
         }
         __syncthreads();
@@ -1033,13 +1041,15 @@ __global__ __launch_bounds__(QT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     __shared__ uint64_t s_keep[TS / 64];
     __shared__ uint32_t s_w[QT / 64];
     __shared__ uint32_t s_n;
+    const uint64_t gba = a.gba_dev ? *a.gba_dev : a.gba;
+    const uint64_t p0 = (uint64_t)blockIdx.x * TS;
+    if (a.gba_dev && (gba > a.gba_cap || p0 >= gba)) return;  // uniform
     if (threadIdx.x == 0) s_n = 0;
     if (threadIdx.x < TS / 64) s_keep[threadIdx.x] = 0;
 #pragma unroll
     for (uint32_t k = 0; k < SPT; k++) s_row[threadIdx.x * SPT + k] = 0;
     __syncthreads();
-    const uint64_t p0 = (uint64_t)blockIdx.x * TS;
-    const TileRows tr = stage_slot_rows<SPT>(a, blockIdx.x, s_row, s_base, s_w);
+    const TileRows tr = stage_slot_rows<SPT>(a, blockIdx.x, gba, s_row, s_base, s_w);
     const uint32_t *ci0 = a.ci_all;
     const uint32_t lane = lane_id();
     uint32_t xs[SPT];
@@ -1049,7 +1059,7 @@ __global__ __launch_bounds__(QT) __attribute__((amdgpu_waves_per_eu(8))) void k_
 #pragma unroll
     for (uint32_t r = 0; r < SPT; r++) {
         const uint32_t sl = r * QT + threadIdx.x;
-        kp[r] = p0 + sl < a.gba;
+        kp[r] = p0 + sl < gba;
         xs[r] = 0;
         is[r] = 0;
         if (kp[r]) {
@@ -1532,7 +1542,7 @@ __global__ __launch_bounds__(QT) void k_join_pass(LevelArgs a) {
     __syncthreads();
     const uint64_t tile = s_tile;
     const uint64_t p0 = tile * TS;
-    const TileRows tr = stage_slot_rows<SPT>(a, tile, s_row, s_base, s_w);
+    const TileRows tr = stage_slot_rows<SPT>(a, tile, a.gba, s_row, s_base, s_w);
     const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
     uint32_t xs[SPT];
     uint64_t is[SPT];
@@ -2307,6 +2317,7 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
     uint32_t fused_stuck = NONE32;  // level at which the workgroup last stopped without progress
     // column stride of M when a one-pass level wrote it at its capacity (0: R)
     uint64_t Mld = 0;
+    double slots_per_row = 16;  // of the level just run (a guess before the first)
 
     for (uint32_t j = jstart; j < k; j++) {
         const uint32_t u = order[j];
@@ -2390,10 +2401,51 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
         // |GBA| lands in dscal[3]; the profiling sums go to dscal[4..5]
         if (prof) reduce_pairs(c, a.part, nbr, dscal + 4);
         if (!one_wg) exclusive_scan(c, a.bound, R, F, ls, dscal + 3);
-        uint64_t sc[2];
-        read_scalars(c, dscal + 3, sc, 2);
-        uint64_t gba = sc[0];
-        sc[0] = prof ? sc[1] : 0;
+        uint64_t S = 0, gba;
+        uint64_t sc[4];
+        size_t join_rec = 0;
+        // The join before |GBA| is known: launched for up to `cap` slots, it
+        // reads |GBA| on the device, its tile counts are scanned, and the
+        // host waits once for both sums instead of once for each.  The cap
+        // is four times the last level's slots per row (the fused workgroup
+        // reports the exact |GBA| of the level it stopped at), and never
+        // above the |GBA| from which the level's lists would be filtered; a
+        // level expected to take wide tiles waits for its |GBA|.  One that
+        // turns out larger than its cap is joined again below.
+        uint64_t cap = 0;
+        if (!(flags & (ABL | GSI_SINGLE_PASS))) {
+            const double guess = st.gba[j] ? (double)st.gba[j] : 4.0 * (double)R * slots_per_row;
+            if (guess < (double)WIDE_TILE_SLOTS) cap = std::max<uint64_t>(SPEC_MIN_SLOTS, (uint64_t)guess);
+            if (level_filter) cap = std::min<uint64_t>(cap, (uint64_t)(FN_FACTOR * 2.0 * (double)g->edges[elab[a.e0]]));
+            if (8.0 * (double)cap > (double)c->arena.largest_free() / 8) cap = 0;
+        }
+        bool joined = false;
+        if (cap) {
+            const uint64_t ct = (cap + QT - 1) / QT;
+            a.rec_x = ls.get<uint32_t>(ct * QT, "survivor elements");
+            a.rec_r = ls.get<uint32_t>(ct * QT, "survivor rows");
+            a.tile_cnt = ls.get<uint32_t>(ct, "tile counts");
+            uint64_t *toff = ls.get<uint64_t>(ct + 1, "tile offsets");
+            a.tile_off = toff;
+            a.tile_row = ls.get<uint64_t>(ct + 1, "tile rows");
+            a.gba_dev = F + R;
+            a.gba_cap = cap;
+            a.rows_in_join = 1;
+            launch(c, "k_join", 0.0, k_join<1>, (uint32_t)ct, QT, a);
+            join_rec = c->recs.size();
+            exclusive_scan_tiles(c, a.tile_cnt, F + R, QT, cap, toff, dscal + 1);
+            a.gba_dev = nullptr;
+            a.rows_in_join = 0;
+            read_scalars(c, dscal + 1, sc, 4);  // survivors, (unused), |GBA|, list lengths
+            S = sc[0];
+            gba = sc[2];
+            joined = gba <= cap;
+            sc[0] = prof ? sc[3] : 0;
+        } else {
+            read_scalars(c, dscal + 3, sc, 2);
+            gba = sc[0];
+            sc[0] = prof ? sc[1] : 0;
+        }
         // a level whose rows rescan l0's lists many times over: filter those
         // lists by C(u) once and let the rows scan the filtered copies
         Block fnb(c);
@@ -2532,35 +2584,41 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
         // survivors as (element, row) records when they fit comfortably
         // (8 bytes per |GBA| slot), else as a keep bitmap (and always for the
         // join ablations, which write the bitmap)
-        const bool recs = !(flags & ABL) && 8.0 * (double)(ntiles * ts) <= (double)c->arena.largest_free() / 4;
-        a.rec_x = a.rec_r = nullptr;
-        a.bitmap = nullptr;
-        if (recs) {
-            a.rec_x = ls.get<uint32_t>(ntiles * ts, "survivor elements");
-            a.rec_r = ls.get<uint32_t>(ntiles * ts, "survivor rows");
+        const bool recs = joined || (!(flags & ABL) && 8.0 * (double)(ntiles * ts) <= (double)c->arena.largest_free() / 4);
+        const double jb =
+            4.0 * gba + (double)R * (8.0 + 8.0 * ne + 4.0 * j) + 4.0 * (double)sc[0] + gba / 8.0 + 4.0 * ntiles;
+        if (joined) {
+            if (prof && join_rec > 0 && join_rec <= c->recs.size()) c->recs[join_rec - 1].bytes = jb;
         } else {
-            a.bitmap = ls.get<uint64_t>(ntiles * (ts / 64), "GBA bitmap");
+            a.rec_x = a.rec_r = nullptr;
+            a.bitmap = nullptr;
+            if (recs) {
+                a.rec_x = ls.get<uint32_t>(ntiles * ts, "survivor elements");
+                a.rec_r = ls.get<uint32_t>(ntiles * ts, "survivor rows");
+            } else {
+                a.bitmap = ls.get<uint64_t>(ntiles * (ts / 64), "GBA bitmap");
+            }
+            a.tile_cnt = ls.get<uint32_t>(ntiles, "tile counts");
+            uint64_t *toff = ls.get<uint64_t>(ntiles + 1, "tile offsets");
+            a.tile_off = toff;
+            uint64_t *trow = ls.get<uint64_t>(ntiles + 1, "tile rows");
+            a.tile_row = trow;
+            // levels of one-slot tiles find their tiles' rows in the join
+            // itself (a launch less); larger ones have thousands of tiles,
+            // for which one pass over F is cheaper than a search each
+            const bool rows_in_join = spt == 1 && !(flags & JOIN_ABL);
+            if (!rows_in_join)
+                launch(c, "k_tile_rows", 8.0 * (R + 1) + 8.0 * (ntiles + 1), k_tile_rows, nblocks(R), QT,
+                       (const uint64_t *)F, R, ntiles, ts, trow);
+            a.rows_in_join = rows_in_join ? 1u : 0u;
+            if (flags & JOIN_ABL) run_join_ablation(c, a, flags, ntiles, ts, jb, ls);
+            else if (spt == 4) launch(c, "k_join", jb, k_join<4>, (uint32_t)ntiles, QT, a);
+            else launch(c, "k_join", jb, k_join<1>, (uint32_t)ntiles, QT, a);
+            a.rows_in_join = 0;
+            join_rec = c->recs.size();
+            exclusive_scan(c, a.tile_cnt, ntiles, toff, ls, dscal + 1);
+            read_scalars(c, dscal + 1, &S, 1);
         }
-        a.tile_cnt = ls.get<uint32_t>(ntiles, "tile counts");
-        uint64_t *toff = ls.get<uint64_t>(ntiles + 1, "tile offsets");
-        a.tile_off = toff;
-        uint64_t *trow = ls.get<uint64_t>(ntiles + 1, "tile rows");
-        a.tile_row = trow;
-        // at most 256 rows: the join finds its tiles' rows in F itself
-        const bool rows_in_join = nbr == 1 && !(flags & JOIN_ABL);
-        if (!rows_in_join)
-            launch(c, "k_tile_rows", 8.0 * (R + 1) + 8.0 * (ntiles + 1), k_tile_rows, nblocks(R), QT,
-                   (const uint64_t *)F, R, ntiles, ts, trow);
-        double jb = 4.0 * gba + (double)R * (8.0 + 8.0 * ne + 4.0 * j) + 4.0 * (double)sc[0] + gba / 8.0 + 4.0 * ntiles;
-        a.rows_in_join = rows_in_join ? 1u : 0u;
-        if (flags & JOIN_ABL) run_join_ablation(c, a, flags, ntiles, ts, jb, ls);
-        else if (spt == 4) launch(c, "k_join", jb, k_join<4>, (uint32_t)ntiles, QT, a);
-        else launch(c, "k_join", jb, k_join<1>, (uint32_t)ntiles, QT, a);
-        a.rows_in_join = 0;
-        const size_t join_rec = c->recs.size();
-        exclusive_scan(c, a.tile_cnt, ntiles, toff, ls, dscal + 1);
-        uint64_t S;
-        read_scalars(c, dscal + 1, &S, 1);
         st.survivors[j] = S;
         // the join wrote 8 bytes per survivor, not the keep bitmap
         if (recs && (c->flags & GSI_CTX_PROFILE) && join_rec > 0 && join_rec <= c->recs.size())
@@ -2615,7 +2673,7 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
         Mn.p = nullptr;
         M = a.Mn;
         Mld = 0;
-        const double slots_per_row = (double)gba / (double)R;
+        slots_per_row = (double)gba / (double)R;
         R = S;
         // back to the single workgroup when the table fits and, at this
         // level's slots per row, so would the next level's |GBA|; not right
