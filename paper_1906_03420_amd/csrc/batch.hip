@@ -104,7 +104,7 @@ static std::vector<FusedQuery> run_tier(gsi_graph *g, const std::shared_ptr<Roun
     }
     const uint64_t per_cu = std::max<uint64_t>(1, (uint64_t)t.blocks_per_cu * grid_scale / 8);
     const uint32_t grid = (uint32_t)std::min<uint64_t>(n, per_cu * cu_count(c));
-    const uint64_t slot_words = 2ull * t.cap_rows * kmax + fused_loc_words(kmax, t.cap_rows);
+    const uint64_t slot_words = 2ull * t.cap_rows * kmax + fused_loc_words(kmax - 1, t.cap_rows);
     Scratch ts(c);
     FBatchItem *d_items = ts.get<FBatchItem>(n, "batch items");
     uint32_t *scratch = ts.get<uint32_t>(slot_words * grid, "batch slots");

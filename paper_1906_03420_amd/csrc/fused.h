@@ -19,9 +19,11 @@ struct FEdge {            // one linking edge of a level
     uint32_t ci_off;      // offset of its label's lists in the whole ci array
 };
 
-// Lookups of the fused kernels: rows x (2 ne + 2) words per level (starts,
-// lengths, start of the scanned list in the whole ci array, its edge).
-inline uint64_t fused_loc_words(uint32_t k, uint64_t rows) { return 2ull * k * rows; }
+// Lookups of the fused kernels: rows x (2 ne + 1) words per level ((start,
+// length) pairs by linking edge, then the scanned list's edge).
+// A level of a multi-labelled query can have more linking edges than placed
+// vertices (one per label of a pair).
+inline uint64_t fused_loc_words(uint32_t max_ne, uint64_t rows) { return (2ull * max_ne + 1) * rows; }
 
 struct FPlan {
     uint32_t k, count_only, cap_rows, cap_slots;

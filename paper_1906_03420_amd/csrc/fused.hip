@@ -8,6 +8,7 @@
 // tests, same order: parent row, then ascending x).
 #include <cstddef>
 #include <cstring>
+#include <type_traits>
 
 #include "fused.h"
 #include "join_device.h"
@@ -101,18 +102,20 @@ __device__ __forceinline__ void lds_words(const uint32_t *pre, uint32_t nw, cons
 // s_waitcnt operand: vmcnt 0, the other counters unconstrained (gfx9 encoding)
 constexpr int WAIT_VMCNT0 = 0x0F70;
 
-// bitmap words a wave takes per round of the fused join and link
-constexpr uint32_t FU = 2;
+// bitmap words a wave takes per round of the fused join and link, and per
+// round of the candidate pass of a level of more than one round
+constexpr uint32_t FU = 2, FP = 4;
 
 // Words of each of the two LDS buffers that hold intermediate tables small
 // enough (rows x columns), sized to what the workgroup's LDS has left.
 template <uint32_t FT, bool XS>
 constexpr uint32_t fused_table_words() {
-    return FT == 1024 ? (XS ? 7168u : 14336u) : FT == 256 ? 1536u : 384u;
+    return FT == 1024 ? (XS ? 6912u : 14336u) : FT == 256 ? 1536u : 384u;
 }
 
 // LDS of one fused workgroup with FT threads, CR rows and CS slots: F, the
-// start of each row's scanned list, the keep bits and their prefix sums,
+// start of each row's scanned list, the keep bits (and a second copy for
+// the candidate pass) and their prefix sums,
 // (XS) each slot's element x, so that the link re-reads no list, and two
 // table buffers
 //
@@ -132,6 +135,7 @@ struct FusedLds {
     uint32_t F[CR + 1];
     uint32_t st[CR];
     uint64_t bits[CS / 64];
+    uint64_t keep[CS / 64];
     uint32_t wpre[CS / 64];
     uint32_t w[FT / 64];
     uint64_t d[2][FT / 64];
@@ -228,6 +232,8 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
         const uint64_t *Cu = uni(plan->Cu[j]);
         const bool final_level = (j == k - 1);
         const uint32_t *ci_all = uni(plan->ci_all);
+        const uint32_t lv_mmask = uni(plan->lv_mmask[j]);
+        const bool homo = uni(plan->homo) != 0;
         if (tid == 0) L.s.lv[j] = R;
 
         // locate N(v, l) for every row and linking edge; the row scans the
@@ -238,8 +244,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                 const FEdge &ed = plan->edges[ef + e];
                 const uint32_t v = M[(uint64_t)uni(ed.col) * ld + i];
                 const uint2 r = pcsr_find(uni(ed.gl), uni(ed.G), uni(ed.H), v);
-                loc[(uint64_t)e * R + i] = r.x;
-                loc[(uint64_t)(ne + e) * R + i] = r.y;
+                reinterpret_cast<uint2 *>(loc)[(uint64_t)e * R + i] = r;
                 if (e == e0) {
                     s0 = r.x;
                     l0 = r.y;
@@ -257,7 +262,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             }
             s_F[i] = bl;
             L.st[i] = plan->edges[ef + be].ci_off + bs;
-            if (ne > 1) loc[(uint64_t)(2 * ne + 1) * R + i] = be;
+            if (ne > 1) loc[(uint64_t)(2 * ne) * R + i] = be;
         }
         __syncthreads();
         // F = exclusive prefix sum of the bounds (each thread owns 4 rows)
@@ -300,43 +305,19 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
 
         // join: keep x = N(v'_i, l0)[p - F[i]] iff x not in m_i, x in C(u),
         // x in every other linking list; one ballot word per 64 slots.  A
-        // wave takes FU words per round (words base + r * waves + w) and
-        // issues each step's loads for all of them together, so a round
-        // costs one chain of dependent loads, not FU.
-        for (uint32_t base = 0; base < nw; base += FU * (FT / 64)) {
-            uint32_t pr[FU], ir[FU], fr[FU], xr[FU];
-            bool kp[FU];
-#pragma unroll
-            for (uint32_t r = 0; r < FU; r++) {
-                pr[r] = (base + r * (FT / 64) + w) * 64 + lane;
-                kp[r] = pr[r] < gba;
-                xr[r] = 0;
-            }
-            lds_rows<FU>(s_F, R, pr, ir, fr);
-            // Loads are issued unconditionally, a slot past |GBA| reading
-            // valid addresses (element 0, row 0, column j - 1), and masked
-            // afterwards: a load behind a branch waits for the one before.
-#pragma unroll
-            for (uint32_t r = 0; r < FU; r++) {
-                if (!kp[r]) ir[r] = 0;
-                xr[r] = ci_all[kp[r] ? L.st[ir[r]] + (pr[r] - fr[r]) : 0u];
-                if (!kp[r]) xr[r] = 0;
-            }
-            {
-                uint64_t cw[FU];
-#pragma unroll
-                for (uint32_t r = 0; r < FU; r++) cw[r] = Cu[xr[r] >> 6];
-#pragma unroll
-                for (uint32_t r = 0; r < FU; r++) {
-                    if (XS && kp[r]) L.x[pr[r]] = xr[r];
-                    kp[r] = kp[r] && ((cw[r] >> (xr[r] & 63)) & 1ull);
-                }
-            }
-            if (!plan->homo) {
+        // wave takes several words per round (words base + r * waves + w)
+        // and issues each step's loads for all of them together, so a round
+        // costs one chain of dependent loads.
+        //
+        // the tests after C(u), for U slots of rows ir
+        const bool more_tests = (!homo && lv_mmask) || ne > 1;
+        auto tests = [&](auto U_, const uint32_t *xr, const uint32_t *ir, bool *kp) {
+            constexpr uint32_t U = decltype(U_)::value;
+            if (!homo) {
                 // x not among the row's values in the columns that can hold
                 // it (those of u's label), four columns at a time; past the
                 // last one the last is read again
-                uint32_t mm = uni(plan->lv_mmask[j]);
+                uint32_t mm = lv_mmask;
                 const uint32_t last = mm ? 31u - (uint32_t)__builtin_clz(mm) : 0u;
                 while (mm) {
                     uint32_t cq[4];
@@ -345,36 +326,128 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                         cq[q] = mm ? (uint32_t)__builtin_ctz(mm) : last;
                         mm &= mm - 1;
                     }
-                    uint32_t mv[FU][4];
+                    uint32_t mv[U][4];
 #pragma unroll
-                    for (uint32_t r = 0; r < FU; r++)
+                    for (uint32_t r = 0; r < U; r++)
 #pragma unroll
                         for (uint32_t q = 0; q < 4; q++) mv[r][q] = M[(uint64_t)cq[q] * ld + ir[r]];
 #pragma unroll
-                    for (uint32_t r = 0; r < FU; r++)
+                    for (uint32_t r = 0; r < U; r++)
 #pragma unroll
                         for (uint32_t q = 0; q < 4; q++) kp[r] = kp[r] && mv[r][q] != xr[r];
                 }
             }
-            if (ne > 1) {
+            if (ne < 2) return;
+            uint32_t be[U];
 #pragma unroll
-                for (uint32_t r = 0; r < FU; r++) {
-                    bool keep = kp[r];
-                    const uint32_t i = ir[r];
-                    const uint32_t be = keep ? loc[(uint64_t)(2 * ne + 1) * R + i] : e0;
-                    for (uint32_t e = 0; keep && e < ne; e++) {
-                        if (e == be) continue;
-                        keep = in_sorted(uni(plan->edges[ef + e].ci) + loc[(uint64_t)e * R + i],
-                                         loc[(uint64_t)(ne + e) * R + i], xr[r]);
+            for (uint32_t r = 0; r < U; r++) be[r] = loc[(uint64_t)(2 * ne) * R + ir[r]];
+            for (uint32_t e = 0; e < ne; e++) {
+                uint32_t st[U], len[U];
+                bool act[U], hit[U], any = false;
+#pragma unroll
+                for (uint32_t r = 0; r < U; r++) {
+                    act[r] = kp[r] && e != be[r];
+                    any |= act[r];
+                }
+                if (!any) continue;
+#pragma unroll
+                for (uint32_t r = 0; r < U; r++) {
+                    const uint2 sl = reinterpret_cast<const uint2 *>(loc)[(uint64_t)e * R + ir[r]];
+                    st[r] = sl.x;
+                    len[r] = act[r] ? sl.y : 0u;
+                }
+                in_sorted_many<U, true, 4>(uni(plan->edges[ef + e].ci), st, len, xr, hit);
+#pragma unroll
+                for (uint32_t r = 0; r < U; r++)
+                    if (act[r]) kp[r] = hit[r];
+            }
+        };
+        // U words per wave and round: the slots' elements (kept in L.x with
+        // XS), C(u), and with `all` the other tests.  Loads are issued
+        // unconditionally, a slot past |GBA| reading valid addresses (element
+        // 0, row 0, column j - 1), and masked afterwards: a load behind a
+        // branch waits for the one before.
+        auto pass = [&](auto U_, bool all) {
+            constexpr uint32_t U = decltype(U_)::value;
+            for (uint32_t base = 0; base < nw; base += U * (FT / 64)) {
+                uint32_t pr[U], ir[U], fr[U], xr[U];
+                bool kp[U];
+#pragma unroll
+                for (uint32_t r = 0; r < U; r++) {
+                    pr[r] = (base + r * (FT / 64) + w) * 64 + lane;
+                    kp[r] = pr[r] < gba;
+                }
+                lds_rows<U>(s_F, R, pr, ir, fr);
+#pragma unroll
+                for (uint32_t r = 0; r < U; r++) {
+                    if (!kp[r]) ir[r] = 0;
+                    xr[r] = ci_all[kp[r] ? L.st[ir[r]] + (pr[r] - fr[r]) : 0u];
+                    if (!kp[r]) xr[r] = 0;
+                }
+                {
+                    uint64_t cw[U];
+#pragma unroll
+                    for (uint32_t r = 0; r < U; r++) cw[r] = Cu[xr[r] >> 6];
+#pragma unroll
+                    for (uint32_t r = 0; r < U; r++) {
+                        if (XS && kp[r]) L.x[pr[r]] = xr[r];
+                        kp[r] = kp[r] && ((cw[r] >> (xr[r] & 63)) & 1ull);
                     }
-                    kp[r] = keep;
+                }
+                if (all) tests(U_, xr, ir, kp);
+#pragma unroll
+                for (uint32_t r = 0; r < U; r++) {
+                    const uint64_t mask = __ballot(kp[r]);
+                    const uint32_t word = base + r * (FT / 64) + w;
+                    if (lane == 0 && word < nw) s_bits[word] = mask;
                 }
             }
+        };
+        if (nw <= FU * (FT / 64)) {
+            pass(std::integral_constant<uint32_t, FU>(), more_tests);
+        } else {
+            // more than one round: first C(u) alone, twice as many words in
+            // flight, then the other tests on the slots that passed, in
+            // dense waves (a round of both, chained, took 3 us whatever few
+            // of its slots needed the second part)
+            pass(std::integral_constant<uint32_t, FP>(), false);
+            if (more_tests) {
+                __syncthreads();
+                uint32_t C;
+                const uint64_t word = tid < nw ? s_bits[tid] : 0ull;
+                const uint32_t ex = wg_exclusive_sum<FT>((uint32_t)__popcll(word), s_w, &C);
+                C = uni(C);
+                if (tid < nw) {
+                    s_wpre[tid] = ex;
+                    L.keep[tid] = word;
+                }
+                __syncthreads();
+                for (uint32_t base = 0; base < C; base += FU * FT) {
+                    uint32_t q[FU], wd[FU], rk[FU], pr[FU], ir[FU], fr[FU], xr[FU];
+                    bool kp[FU];
 #pragma unroll
-            for (uint32_t r = 0; r < FU; r++) {
-                const uint64_t mask = __ballot(kp[r]);
-                const uint32_t word = base + r * (FT / 64) + w;
-                if (lane == 0 && word < nw) s_bits[word] = mask;
+                    for (uint32_t r = 0; r < FU; r++) {
+                        q[r] = base + r * FT + tid;
+                        kp[r] = q[r] < C;
+                    }
+                    lds_words<FU>(s_wpre, nw, q, wd, rk);
+#pragma unroll
+                    for (uint32_t r = 0; r < FU; r++)
+                        pr[r] = kp[r] ? wd[r] * 64 + nth_set_bit(s_bits[wd[r]], rk[r]) : 0u;
+                    lds_rows<FU>(s_F, R, pr, ir, fr);
+#pragma unroll
+                    for (uint32_t r = 0; r < FU; r++) {
+                        if (!kp[r]) ir[r] = 0;
+                        if (XS) xr[r] = L.x[pr[r]];
+                        else xr[r] = ci_all[kp[r] ? L.st[ir[r]] + (pr[r] - fr[r]) : 0u];
+                    }
+                    tests(std::integral_constant<uint32_t, FU>(), xr, ir, kp);
+#pragma unroll
+                    for (uint32_t r = 0; r < FU; r++)
+                        if (!kp[r] && q[r] < C) atomicAnd(&L.keep[pr[r] >> 6], ~(1ull << (pr[r] & 63)));
+                }
+                __syncthreads();
+                if (tid < nw) s_bits[tid] = L.keep[tid];
             }
         }
         __syncthreads();

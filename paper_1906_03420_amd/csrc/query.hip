@@ -1988,6 +1988,12 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
     }
     std::vector<uint32_t> col(k, NONE32);
     for (uint32_t j = 0; j < k; j++) col[order[j]] = j;
+    uint32_t max_ne = 1;  // most linking edges of a level
+    for (uint32_t j = 1; j < k; j++) {
+        uint32_t ne = 0;
+        for (auto &p : q.adj[order[j]]) ne += col[p.first] < j;
+        max_ne = std::max(max_ne, ne);
+    }
 
     auto tj = std::chrono::steady_clock::now();
 
@@ -2148,7 +2154,7 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
     // M and R then hold those chunks' rows, for the per-level kernels.
     auto run_chunks = [&](uint32_t j0) -> int {
         const FTier t = fused_tier(256);
-        const uint64_t slot_words = 2ull * t.cap_rows * k + fused_loc_words(k, t.cap_rows);
+        const uint64_t slot_words = 2ull * t.cap_rows * k + fused_loc_words(max_ne, t.cap_rows);
         int ncu = 0;
         if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || ncu < 1)
             ncu = 1;
@@ -2263,7 +2269,7 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
             fdplan = fused_plan(cap_rows, cap_slots, &fhp, finl.get());
             fbuf0 = fs.get<uint32_t>((uint64_t)cap_rows * k, "fused table 0");
             fbuf1 = fs.get<uint32_t>((uint64_t)cap_rows * k, "fused table 1");
-            floc = fs.get<uint32_t>(fused_loc_words(k, cap_rows), "fused lookups");
+            floc = fs.get<uint32_t>(fused_loc_words(max_ne, cap_rows), "fused lookups");
             fdst = reinterpret_cast<FStatus *>(c->mbox_dev + MBOX_STATUS);
         }
         uint32_t *out = count_only ? nullptr : persist<uint32_t>(c, (uint64_t)cap_slots * k, "result rows");

@@ -41,3 +41,22 @@ def test_level_sizes(nb, nc, gap):
                     assert st["gba"][1:] == [nb, len(c)] and st["survivors"][1:] == [nb, len(c)]
                 r.free()
         dg.free()
+
+
+def test_multi_more_labelled_edges_than_vertices():
+    """Eight labels on every pair of a two-vertex query: more linking edges
+    than placed vertices, over a table of thousands of rows."""
+    import paper_1906_03420_amd as gsi
+    n = 3000
+    edges = [(i, (i + 1) % n, l) for i in range(n) for l in range(8)]
+    g = w.make_mgraph(n, [[0]] * n, edges, "eight labels")
+    q = w.make_mquery([[0], [0]], [(0, 1, l) for l in range(8)])
+    i = np.arange(n)
+    want = np.concatenate([np.stack([i, (i + 1) % n], 1), np.stack([(i + 1) % n, i], 1)])
+    with gsi.Context(1 << 30) as ctx:
+        dg = ctx.load_multi(g)
+        r = dg.query_multi(q)
+        assert r.count == 2 * n
+        np.testing.assert_array_equal(r.sorted_rows(), want[np.lexsort((want[:, 1], want[:, 0]))])
+        r.free()
+        dg.free()
