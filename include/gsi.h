@@ -267,12 +267,17 @@ typedef struct {
  * rows, then shrunk); by default it runs as separate join, scan and link
  * launches, which measure faster (a tile's rows wait on the slowest join
  * before it).
- * Up to 4096 roots one fused workgroup runs the levels while the tables stay
- * small (4096 rows and 16384 |GBA| slots per level, with F, the keep bits and
- * the survivor prefix sums in LDS); the per-level kernels run a level that
- * does not fit, and the workgroup takes the query back once the new table
- * fits and the next level's |GBA|, estimated at the current slots per row,
- * would fit too.  Above that, rows of M being
+ * Up to 32768 roots one kernel runs the levels while the tables stay small:
+ * its first workgroup those of up to 1024 rows and 4096 |GBA| slots (with F,
+ * the keep bits and the survivor prefix sums in LDS), that and 63 helper
+ * workgroups together larger ones, up to 131072 rows and 16384 slots for each
+ * workgroup's share.  Without helpers (max_rows, fused_max_rows or
+ * fused_max_slots set, or an arena in which their buffers would take more
+ * than a sixteenth of the free space) the limits are 4096 roots, 4096 rows and
+ * 16384 slots.  The per-level kernels run a level that does not fit, and the
+ * kernel takes the query back once the new table fits and the next level's
+ * |GBA|, estimated at the current slots per row, would fit too.  Above 4096
+ * roots, rows of M being
  * independent at every level, step 3 first runs on root chunks: small groups
  * of rows of M = C(u_first), each taken by one 256-thread workgroup of a
  * persistent launch that runs all levels of its chunk (1024 rows and 4096

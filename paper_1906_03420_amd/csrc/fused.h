@@ -122,7 +122,35 @@ void launch_chunk_gather(gsi_ctx *c, uint32_t nchunks, const FStatus *sts, const
 void launch_take_rows(gsi_ctx *c, uint32_t nlist, const uint32_t *M0, uint32_t R0, uint32_t ncols,
                       uint32_t chunk_rows, const uint32_t *list, uint32_t *dst, uint64_t rows);
 
-// The single-workgroup fused kernel, levels j0.. of the table M0 (R0 rows,
+// The workgroups of the single-query fused kernel (fused.hip, "cluster").
+// 64: a level's two meetings read one word per workgroup with one wave.  With
+// 16 the queries on 10^6 vertices took 3.69 ms (walk) and 1.92 ms
+// (homomorphism), with 32 3.38 and 1.84, with 64 3.42 and 1.85.
+constexpr uint32_t CL_MAX_WG = 64;
+// A level is shared when it has more than CL_ROWS rows or CL_SLOTS slots: one
+// workgroup alone takes about 15 us for 4096 slots, a shared level costs 12 to
+// 15 us whatever it holds.  2048 slots measured the same, 8192 slower (walk
+// 3.42 -> 3.45 ms, two-label queries 0.69 -> 0.70 ms).
+constexpr uint32_t CL_ROWS = 1024, CL_SLOTS = 4096;
+constexpr uint32_t CL_CAP_ROWS = 131072;   // rows of a shared level's table (fewer than 2^22)
+constexpr uint32_t CL_CAP_OUT = 262144;    // result rows
+// A table is handed to the kernel when it has at most this many rows and, at
+// the slots per row of the level before, this many slots; a level past the
+// 2^20 slots that 64 workgroups hold is run twice.  131072 and 524288 slots
+// measured alike (walk 3.42 and 3.41 ms, homomorphism 1.85 and 1.83 ms).
+constexpr uint32_t CL_TAKE_ROWS = 32768, CL_TAKE_SLOTS = 131072;
+// No helpers at first when every level is expected to have fewer slots: with
+// them a query of 16 rows takes 78 us instead of 73.
+constexpr double CL_FEW_SLOTS = 512;
+constexpr uint64_t CL_CTL_BYTES = 4096;    // control block, zeroed before the launch
+struct FusedCluster {
+    uint32_t nb = 1;          // workgroups (1: no helpers)
+    void *ctl = nullptr;
+    uint32_t cap_rows = 0, cap_out = 0;
+    uint64_t loc_stride = 0;  // words of lookups per workgroup
+};
+
+// The single-query fused kernel, levels j0.. of the table M0 (R0 rows,
 // j0 columns, column stride R0); with b0 (the bitset of C(u_first), nwords
 // words; j0 = 1 only) it also writes M0 itself, `b0_runs` being the set bits
 // of each of the BITS_RUNS runs of that bitset.  The plan is d_plan in
@@ -130,6 +158,6 @@ void launch_take_rows(gsi_ctx *c, uint32_t nlist, const uint32_t *M0, uint32_t R
 void launch_fused(gsi_ctx *c, const FPlan *d_plan, const FPlanArg &inl, uint32_t j0, uint32_t *M0, uint32_t R0,
                   const uint32_t *b0_runs, const uint64_t *b0,
                   uint64_t nwords, uint32_t *buf0, uint32_t *buf1, uint32_t *loc, uint32_t *out, FStatus *d_status,
-                  double alg_bytes);
+                  double alg_bytes, const FusedCluster &fc);
 
 }  // namespace gsi

@@ -4,7 +4,8 @@
 // costs no kernel launch and no host round trip.  The workgroup stops at the
 // first level whose rows, slots (|GBA|) or survivors exceed its capacity and
 // reports where; the caller finishes the query from that level with the
-// per-level kernels.  Results are identical to the per-level path (same
+// per-level kernels.  The single-query kernel can share its larger levels
+// among the workgroups of its launch (see Cluster).  Results are identical to the per-level path (same
 // tests, same order: parent row, then ascending x).
 #include <cstddef>
 #include <cstring>
@@ -147,6 +148,7 @@ struct FusedLds {
 struct FusedLevelsLds {
     FusedLds<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true> q;
     FPlanArg plan;
+    uint32_t cl[8];
 };
 static_assert(sizeof(FusedLevelsLds) <= 160 * 1024, "fused workgroup LDS");
 
@@ -177,17 +179,211 @@ __device__ __forceinline__ void st_flush(const FusedStat &s, FStatus *st) {
     }
 }
 
+// ----------------------------------------------------------- cluster
+// A level of a few thousand slots keeps one CU busy for tens of microseconds
+// (a CU brings in some 300 scattered lines per microsecond) while the rest of
+// the chip idles, and handing it to the per-level kernels costs five launches
+// and a host round trip.  The single-query kernel is launched with further
+// workgroups (helpers) that wait while the first one runs small levels alone;
+// on a larger one it publishes the table, and it and the helpers take equal
+// shares of its rows, in order, so a level's rows come out in the same order.
+// A shared level has two meeting points: the survivor counts, which give
+// every workgroup its place in the next table, and the table's completion;
+// they cost about 5 us.  On 10^6 vertices 16 walk queries went from 3.79 to
+// 3.42 ms, 8 homomorphism queries from 1.98 to 1.81 ms.
+//
+// Only helpers that have checked in are called, so no workgroup waits for one
+// that is not running (another stream may hold the CUs).  Every wait is
+// bounded all the same: past CL_SPINS polls a workgroup sets `abort` and
+// leaves, the others see the flag and leave too, and the first reports that
+// it stopped at the table it was given, which nothing has overwritten.
+constexpr uint32_t CL_SPINS = 1u << 16;  // about 50 ms
+
+// One atomic word carries a workgroup's epoch, overflow flag, survivors and
+// slots, so the counts need no fence.  Two sets of words: a workgroup writes
+// epoch e + 2 only after all have read epoch e.
+struct ClusterCtl {
+    unsigned long long word[2][CL_MAX_WG];
+    unsigned long long call;   // the last call: its number << 32 | level << 8 | workgroups
+    uint32_t here[CL_MAX_WG];  // helper checked in
+    uint32_t abort;
+    uint32_t args[4];          // of the last call: rows, stride, place, epoch
+    unsigned long long dig[CL_MAX_WG][2];  // digests of a shared last level
+};
+static_assert(sizeof(ClusterCtl) <= CL_CTL_BYTES, "control block");
+
+struct Cluster {
+    ClusterCtl *c;
+    uint32_t nmax;      // workgroups launched
+    uint32_t nb;        // those of the last call
+    uint32_t cap_rows;  // rows of a shared level's table
+    uint32_t cap_out;   // result rows
+    uint32_t epoch, call;
+    uint32_t *lds;      // 8 words
+};
+
+template <typename T>
+__device__ __forceinline__ T cl_load(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void cl_store(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Every workgroup's survivors and slots: *off = survivors of the workgroups
+// before this one, *S and *gba the sums, *over set when one could not hold
+// its share.  With `table`, what every thread wrote before is visible to
+// every workgroup after.  False when a wait ran out.  Called by all threads.
+__device__ __forceinline__ bool cl_meet(Cluster &cl, bool table, uint32_t myS, uint32_t mygba, bool myover,
+                                        uint32_t *off, uint32_t *S, uint32_t *gba, bool *over) {
+    const uint32_t e = ++cl.epoch;
+    if (table) {
+        __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+        __syncthreads();
+    }
+    if (threadIdx.x < 64) {
+        if (table) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        unsigned long long *w = cl.c->word[e & 1];
+        const uint32_t lane = threadIdx.x;
+        if (lane == 0)
+            cl_store(w + blockIdx.x,
+                     ((unsigned long long)e << 32) | (myover ? 0x80000000ull : 0ull) | (myS << 15) | mygba);
+        unsigned long long x = 0;
+        bool ok = lane >= cl.nb, dead = false;
+        for (uint32_t spins = 1; __ballot(!ok); spins++) {
+            if (!ok) {
+                x = cl_load(w + lane);
+                ok = (uint32_t)(x >> 32) == e;
+            }
+            if (spins > CL_SPINS || ((spins & 63) == 0 && uni(cl_load(&cl.c->abort)))) {
+                dead = true;
+                break;
+            }
+        }
+        if (dead && lane == 0) cl_store(&cl.c->abort, 1u);
+        if (lane >= cl.nb) x = 0;
+        const uint32_t v = (uint32_t)(x >> 15) & 0x7FFFu;
+        const uint32_t inc = wave_inclusive_sum(v);
+        const uint32_t slots = wave_sum((uint32_t)x & 0x7FFFu);
+        const uint64_t any = __ballot((x & 0x80000000ull) != 0);
+        if (table) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if (lane == blockIdx.x) cl.lds[0] = inc - v;
+        if (lane == 63) {
+            cl.lds[1] = inc;
+            cl.lds[2] = slots;
+            cl.lds[3] = any ? 1u : 0u;
+            cl.lds[4] = dead ? 1u : 0u;
+        }
+    }
+    __syncthreads();
+    *off = uni(cl.lds[0]);
+    *S = uni(cl.lds[1]);
+    *gba = uni(cl.lds[2]);
+    *over = uni(cl.lds[3]) != 0;
+    const bool alive = uni(cl.lds[4]) == 0;
+    __syncthreads();  // before the words are written again
+    return alive;
+}
+
+// The call of the first workgroup: level j of the table of R rows (stride
+// ld) at `mloc`, at most `share` of them to a workgroup; j = 0 lets the
+// helpers go.  Called by all its threads, with the table written.  False, and
+// no call, when too few helpers have checked in.
+//
+// Level and workgroups are in the word that a helper polls, so one that is
+// not called reads nothing that a later call may be writing; one that is
+// called has read `args` before the first meeting, and the first workgroup
+// does not write them again before it.
+__device__ __forceinline__ bool cl_call(Cluster &cl, uint32_t j, uint32_t R, uint32_t ld, uint32_t mloc,
+                                        uint32_t share) {
+    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const uint32_t lane = threadIdx.x;
+        const bool here = lane == 0 || (lane < cl.nmax && cl_load(cl.c->here + lane) != 0);
+        const uint64_t out = ~__ballot(here);
+        const uint32_t nb = out ? (uint32_t)__builtin_ctzll(out) : 64u;  // the first ones in a row
+        const bool ok = j == 0 || (nb > 1 && R <= nb * share);
+        if (lane == 0) {
+            cl.lds[0] = ok ? nb : 0u;
+            if (ok) {
+                cl_store(cl.c->args, R);
+                cl_store(cl.c->args + 1, ld);
+                cl_store(cl.c->args + 2, mloc);
+                cl_store(cl.c->args + 3, cl.epoch);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                cl_store(&cl.c->call, ((unsigned long long)(cl.call + 1) << 32) | (j << 8) | nb);
+            }
+        }
+    }
+    __syncthreads();
+    const uint32_t nb = uni(cl.lds[0]);
+    __syncthreads();
+    if (!nb) return false;
+    cl.nb = nb;
+    cl.call++;
+    return true;
+}
+
+// A helper's wait for the next call that includes it; false when it is to
+// leave.
+__device__ __forceinline__ bool cl_wait(Cluster &cl, uint32_t *j, uint32_t *R, uint32_t *ld, uint32_t *mloc) {
+    if (threadIdx.x < 64) {
+        uint32_t lv = 0, nb = 0;
+        bool dead = false;
+        if (threadIdx.x == 0) cl_store(cl.c->here + blockIdx.x, 1u);
+        for (uint32_t spins = 1;; spins++) {
+            const unsigned long long x = cl_load(&cl.c->call);
+            const uint32_t n = uni((uint32_t)(x >> 32));
+            lv = uni((uint32_t)x) >> 8;
+            nb = uni((uint32_t)x) & 255u;
+            if (n != cl.call && (lv == 0 || nb > blockIdx.x)) {
+                cl.call = n;
+                break;
+            }
+            if (spins > CL_SPINS || ((spins & 63) == 0 && uni(cl_load(&cl.c->abort)))) {
+                dead = true;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(8);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if (dead && threadIdx.x == 0) cl_store(&cl.c->abort, 1u);
+        if (threadIdx.x == 0) {
+            cl.lds[0] = dead ? 0u : lv;
+            cl.lds[1] = cl.call;
+            cl.lds[2] = nb;
+#pragma unroll
+            for (uint32_t t = 0; t < 4; t++) cl.lds[t + 3] = cl_load(cl.c->args + t);
+        }
+    }
+    __syncthreads();
+    *j = uni(cl.lds[0]);
+    cl.call = uni(cl.lds[1]);
+    cl.nb = uni(cl.lds[2]);
+    *R = uni(cl.lds[3]);
+    *ld = uni(cl.lds[4]);
+    *mloc = uni(cl.lds[5]);
+    cl.epoch = uni(cl.lds[6]);
+    __syncthreads();
+    return *j != 0;
+}
+
 // Join levels j0 .. k-1 of one query in one workgroup (see the file
 // comment), starting from the table M0 of R0 rows and j0 columns (column c
 // at M0 + c * ld0).  FT threads; at most CR rows per table (CR = 4 FT) and
 // CS slots per level.  With `ocount` set, the last level reserves its S*k
 // output words from that counter (words of `out`, at most `ocap`) instead of
-// writing at out[0].
-template <uint32_t FT, uint32_t CR, uint32_t CS, bool XS>
+// writing at out[0].  CL: the workgroups of `cl` share levels of more than
+// CL_ROWS rows or CL_SLOTS slots (the first workgroup runs the others, and
+// returns with the status); buf0 and buf1 then hold cl->cap_rows rows.
+template <uint32_t FT, uint32_t CR, uint32_t CS, bool XS, bool CL = false>
 __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, const uint32_t *M0, uint32_t R0,
                                             uint32_t ld0, uint32_t *buf0, uint32_t *buf1, uint32_t *loc,
                                             uint32_t *out, FusedLds<FT, CR, CS, XS> &L,
-                                            unsigned long long *ocount = nullptr, uint64_t ocap = 0) {
+                                            unsigned long long *ocount = nullptr, uint64_t ocap = 0,
+                                            Cluster *cl = nullptr) {
     static_assert(CR == 4 * FT, "each thread scans four rows");
     static_assert(CS / 64 <= FT, "one thread per bitmap word in the survivor scan");
     uint32_t *s_F = L.F;
@@ -207,8 +403,15 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
     // of global memory; M then has column stride R.  M sits at index
     // next ^ 1 of its space (global or LDS), M' goes to index `next`.
     constexpr uint32_t MT = fused_table_words<FT, XS>();
+    // a longer list does not fit whatever the others are; CR of them sum to
+    // less than 2^32
+    constexpr uint32_t MAX_BOUND = 0xFFFFFFFFu / CR - 1;
+    static_assert(MAX_BOUND > CS, "a list that is cut does not fit");
     bool m_lds = false;
     uint32_t next = 0;
+    const bool cluster = CL && cl->nmax > 1;
+    const uint32_t bid = CL ? blockIdx.x : 0u;
+    bool wide = false;  // the level is shared
     // level j does not fit: record where, and where its input M lives (a
     // table in LDS is copied to buf0 for the caller)
     auto stop = [&](uint32_t j) {
@@ -222,12 +425,53 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             L.s.head[ST_MLOC] = mloc;
         }
     };
-    if (R0 > cap_rows) {  // the first table does not fit
+    if (R0 > (cluster ? cl->cap_rows : cap_rows)) {  // the first table does not fit
         stop(j0);
         return;
     }
+    // the first workgroup calls the helpers to level j (a table in LDS is
+    // written to buf0 for them); once per level, for none may be there
+    uint32_t called = 0;
+    auto go_wide = [&](uint32_t j) {
+        called = j;
+        if (m_lds) {
+            for (uint32_t t = tid; t < R * j; t += FT) buf0[t] = M[t];
+            M = buf0;
+            m_lds = false;
+            mloc = 0;
+        }
+        wide = cl_call(*cl, j, R, ld, mloc, cap_rows);
+        next = mloc == 0 ? 1u : 0u;
+    };
+    // a wait ran out: the query starts over from its first table
+    auto give_up = [&]() {
+        if (tid == 0) {
+            L.s.head[ST_LEVEL] = j0;
+            L.s.head[ST_ROWS] = R0;
+            L.s.head[ST_MLOC] = FSTATUS_IN_FIRST;
+        }
+    };
 
     for (uint32_t j = j0; j < k; j++) {
+        if (cluster && !wide) {
+            if (bid != 0) {
+                if (!cl_wait(*cl, &j, &R, &ld, &mloc)) return;
+                M = mloc == FSTATUS_IN_FIRST ? M0 : mloc ? buf1 : buf0;
+                wide = true;
+                next = mloc == 0 ? 1u : 0u;
+            } else if (R > CL_ROWS && called != j) {
+                go_wide(j);
+            }
+            if (!wide && R > cap_rows) {
+                stop(j);
+                return;
+            }
+        }
+        // the workgroup's rows of the table: Rw of them from row r0 (all but
+        // when the level is shared)
+        const uint32_t r0 = wide ? (uint32_t)((uint64_t)R * bid / cl->nb) : 0u;
+        const uint32_t Rw = wide ? (uint32_t)((uint64_t)R * (bid + 1) / cl->nb) - r0 : R;
+        const uint32_t *Mw = M + r0;
         const uint32_t ne = uni(plan->lv_ne[j]), ef = uni(plan->lv_first[j]), e0 = uni(plan->lv_e0[j]);
         const uint64_t *Cu = uni(plan->Cu[j]);
         const bool final_level = (j == k - 1);
@@ -238,13 +482,13 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
 
         // locate N(v, l) for every row and linking edge; the row scans the
         // list of e0 (Algorithm 4) or, with `pick`, its shortest one
-        for (uint32_t i = tid; i < R; i += FT) {
+        for (uint32_t i = tid; i < Rw; i += FT) {
             uint32_t s0 = 0, l0 = 0, ob = NONE32, os = 0, ol = 0xFFFFFFFFu;
             for (uint32_t e = 0; e < ne; e++) {
                 const FEdge &ed = plan->edges[ef + e];
-                const uint32_t v = M[(uint64_t)uni(ed.col) * ld + i];
+                const uint32_t v = Mw[(uint64_t)uni(ed.col) * ld + i];
                 const uint2 r = pcsr_find(uni(ed.gl), uni(ed.G), uni(ed.H), v);
-                reinterpret_cast<uint2 *>(loc)[(uint64_t)e * R + i] = r;
+                reinterpret_cast<uint2 *>(loc)[(uint64_t)e * Rw + i] = r;
                 if (e == e0) {
                     s0 = r.x;
                     l0 = r.y;
@@ -260,9 +504,9 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                 bs = os;
                 bl = ol;
             }
-            s_F[i] = bl;
+            s_F[i] = bl < MAX_BOUND ? bl : MAX_BOUND;
             L.st[i] = plan->edges[ef + be].ci_off + bs;
-            if (ne > 1) loc[(uint64_t)(2 * ne) * R + i] = be;
+            if (ne > 1) loc[(uint64_t)(2 * ne) * Rw + i] = be;
         }
         __syncthreads();
         // F = exclusive prefix sum of the bounds (each thread owns 4 rows)
@@ -271,7 +515,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
 #pragma unroll
             for (int q = 0; q < 4; q++) {
                 uint32_t i = 4 * tid + q;
-                v4[q] = i < R ? s_F[i] : 0u;
+                v4[q] = i < Rw ? s_F[i] : 0u;
                 sum += v4[q];
             }
             uint32_t tot;
@@ -279,21 +523,27 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
 #pragma unroll
             for (int q = 0; q < 4; q++) {
                 uint32_t i = 4 * tid + q;
-                if (i < R) s_F[i] = run;
+                if (i < Rw) s_F[i] = run;
                 run += v4[q];
             }
-            if (tid == 0) s_F[R] = tot;
+            if (tid == 0) s_F[Rw] = tot;
             __syncthreads();
         }
         // values every thread reads from LDS are made wave-uniform, so that
         // the exits below are uniform branches
-        const uint32_t gba = __builtin_amdgcn_readfirstlane(s_F[R]);
+        const uint32_t gba = __builtin_amdgcn_readfirstlane(s_F[Rw]);
         if (tid == 0) L.s.lv[GSI_MAX_K + j] = gba;
-        if (gba > cap_slots) {
+        if (cluster && !wide && gba > CL_SLOTS && called != j) {
+            go_wide(j);
+            j--;  // the level again, shared (or alone)
+            continue;
+        }
+        if (!wide && gba > cap_slots) {
             stop(j);
             return;
         }
-        if (gba == 0) {
+        const bool my_over = gba > cap_slots;  // (shared levels only)
+        if (!wide && gba == 0) {
             if (tid == 0) {
                 L.s.lv[2 * GSI_MAX_K + j] = 0;
                 L.s.head[ST_LEVELS] = j;
@@ -301,7 +551,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             }
             return;
         }
-        const uint32_t nw = (gba + 63) / 64;
+        const uint32_t nw = my_over ? 0u : (gba + 63) / 64;
 
         // join: keep x = N(v'_i, l0)[p - F[i]] iff x not in m_i, x in C(u),
         // x in every other linking list; one ballot word per 64 slots.  A
@@ -330,7 +580,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
 #pragma unroll
                     for (uint32_t r = 0; r < U; r++)
 #pragma unroll
-                        for (uint32_t q = 0; q < 4; q++) mv[r][q] = M[(uint64_t)cq[q] * ld + ir[r]];
+                        for (uint32_t q = 0; q < 4; q++) mv[r][q] = Mw[(uint64_t)cq[q] * ld + ir[r]];
 #pragma unroll
                     for (uint32_t r = 0; r < U; r++)
 #pragma unroll
@@ -340,7 +590,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             if (ne < 2) return;
             uint32_t be[U];
 #pragma unroll
-            for (uint32_t r = 0; r < U; r++) be[r] = loc[(uint64_t)(2 * ne) * R + ir[r]];
+            for (uint32_t r = 0; r < U; r++) be[r] = loc[(uint64_t)(2 * ne) * Rw + ir[r]];
             for (uint32_t e = 0; e < ne; e++) {
                 uint32_t st[U], len[U];
                 bool act[U], hit[U], any = false;
@@ -352,7 +602,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                 if (!any) continue;
 #pragma unroll
                 for (uint32_t r = 0; r < U; r++) {
-                    const uint2 sl = reinterpret_cast<const uint2 *>(loc)[(uint64_t)e * R + ir[r]];
+                    const uint2 sl = reinterpret_cast<const uint2 *>(loc)[(uint64_t)e * Rw + ir[r]];
                     st[r] = sl.x;
                     len[r] = act[r] ? sl.y : 0u;
                 }
@@ -377,7 +627,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                     pr[r] = (base + r * (FT / 64) + w) * 64 + lane;
                     kp[r] = pr[r] < gba;
                 }
-                lds_rows<U>(s_F, R, pr, ir, fr);
+                lds_rows<U>(s_F, Rw, pr, ir, fr);
 #pragma unroll
                 for (uint32_t r = 0; r < U; r++) {
                     if (!kp[r]) ir[r] = 0;
@@ -434,7 +684,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
 #pragma unroll
                     for (uint32_t r = 0; r < FU; r++)
                         pr[r] = kp[r] ? wd[r] * 64 + nth_set_bit(s_bits[wd[r]], rk[r]) : 0u;
-                    lds_rows<FU>(s_F, R, pr, ir, fr);
+                    lds_rows<FU>(s_F, Rw, pr, ir, fr);
 #pragma unroll
                     for (uint32_t r = 0; r < FU; r++) {
                         if (!kp[r]) ir[r] = 0;
@@ -460,15 +710,32 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             if (tid < nw) s_wpre[tid] = ex;
             __syncthreads();
         }
-        if (tid == 0) L.s.lv[2 * GSI_MAX_K + j] = S;
-        if (S == 0) {
+        // the level's survivors, and this workgroup's place among them
+        uint32_t off = 0, St = S;
+        if (wide) {
+            uint32_t slots;
+            bool over;
+            if (!cl_meet(*cl, false, S, my_over ? 0u : gba, my_over, &off, &St, &slots, &over)) {
+                give_up();
+                return;
+            }
+            if (tid == 0) L.s.lv[GSI_MAX_K + j] = over ? 0u : slots;
+            // a share of the next table has to fit as well
+            const uint32_t next_cap = cl->nb * cap_rows < cl->cap_rows ? cl->nb * cap_rows : cl->cap_rows;
+            if (over || St > (final_level ? (plan->count_only ? 0xFFFFFFFFu : cl->cap_out) : next_cap)) {
+                stop(j);
+                return;
+            }
+        }
+        if (tid == 0) L.s.lv[2 * GSI_MAX_K + j] = St;
+        if (St == 0) {
             if (tid == 0) {
                 L.s.head[ST_LEVELS] = j;
                 L.s.head[ST_DONE] = 1;
             }
             return;
         }
-        if (!final_level && S > cap_rows) {
+        if (!wide && !final_level && S > cap_rows) {
             stop(j);
             return;
         }
@@ -497,7 +764,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
         // slots (survivor q is at position q; its slot is found from the
         // keep bits' prefix sums), so the waves are dense however sparse the
         // keep bits are; FU survivors per thread and round.
-        const bool n_lds = !final_level && (uint64_t)S * (j + 1) <= MT;
+        const bool n_lds = !wide && !final_level && (uint64_t)S * (j + 1) <= MT;
         // (selects, not an indexed pointer array, which would live in scratch)
         uint32_t *Mn = n_lds ? (next ? L.mt[1] : L.mt[0]) : (next ? buf1 : buf0);
         uint64_t hs = 0, hx = 0;
@@ -512,7 +779,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             lds_words<FU>(s_wpre, nw, pos, wd, rk);
 #pragma unroll
             for (uint32_t r = 0; r < FU; r++) pr[r] = kp[r] ? wd[r] * 64 + nth_set_bit(s_bits[wd[r]], rk[r]) : 0u;
-            lds_rows<FU>(s_F, R, pr, ir, fr);
+            lds_rows<FU>(s_F, Rw, pr, ir, fr);
             // unconditional loads from valid addresses, masked afterwards
 #pragma unroll
             for (uint32_t r = 0; r < FU; r++) {
@@ -528,16 +795,16 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                     for (uint32_t r = 0; r < FU; r++)
 #pragma unroll
                         for (uint32_t q = 0; q < 4; q++)
-                            mv[r][q] = M[(uint64_t)(c + q < j ? c + q : j - 1) * ld + ir[r]];
+                            mv[r][q] = Mw[(uint64_t)(c + q < j ? c + q : j - 1) * ld + ir[r]];
 #pragma unroll
                     for (uint32_t r = 0; r < FU; r++)
 #pragma unroll
                         for (uint32_t q = 0; q < 4; q++)
-                            if (kp[r] && c + q < j) Mn[(uint64_t)(c + q) * S + pos[r]] = mv[r][q];
+                            if (kp[r] && c + q < j) Mn[(uint64_t)(c + q) * St + off + pos[r]] = mv[r][q];
                 }
 #pragma unroll
                 for (uint32_t r = 0; r < FU; r++)
-                    if (kp[r]) Mn[(uint64_t)j * S + pos[r]] = xr[r];
+                    if (kp[r]) Mn[(uint64_t)j * St + off + pos[r]] = xr[r];
             } else {
                 uint64_t f[FU];
 #pragma unroll
@@ -549,7 +816,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                         const uint32_t c = u0 + q < k ? uni(plan->qcol[u0 + q]) : j;
 #pragma unroll
                         for (uint32_t r = 0; r < FU; r++) {
-                            const uint32_t mv = M[(uint64_t)(c < j ? c : 0u) * ld + ir[r]];
+                            const uint32_t mv = Mw[(uint64_t)(c < j ? c : 0u) * ld + ir[r]];
                             val[r][q] = c < j ? mv : xr[r];
                         }
                     }
@@ -558,7 +825,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
 #pragma unroll
                         for (uint32_t r = 0; r < FU; r++) {
                             if (!kp[r] || u0 + q >= k) continue;
-                            if (!plan->count_only) out[(uint64_t)pos[r] * k + u0 + q] = val[r][q];
+                            if (!plan->count_only) out[(uint64_t)(off + pos[r]) * k + u0 + q] = val[r][q];
                             f[r] = fnv_word(f[r], val[r][q]);
                         }
                 }
@@ -587,16 +854,49 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                 }
                 L.s.head[ST_DIG0] = ts;
                 L.s.head[ST_DIG1] = tx;
-                L.s.head[ST_COUNT] = S;
+                L.s.head[ST_COUNT] = St;
                 L.s.head[ST_LEVELS] = j;
-                L.s.head[ST_DONE] = 1;
+                if (!wide) {
+                    L.s.head[ST_DONE] = 1;
+                } else {
+                    cl->c->dig[bid][0] = ts;
+                    cl->c->dig[bid][1] = tx;
+                }
+            }
+            if (wide) {
+                uint32_t u0, u1, u2;
+                bool u3;
+                if (!cl_meet(*cl, true, 0, 0, false, &u0, &u1, &u2, &u3)) {
+                    give_up();
+                    return;
+                }
+                if (tid < 64) {
+                    const uint64_t ts = wave_sum(tid < cl->nb ? (uint64_t)cl->c->dig[tid][0] : 0ull);
+                    const uint64_t tx = wave_xor(tid < cl->nb ? (uint64_t)cl->c->dig[tid][1] : 0ull);
+                    if (tid == 0) {
+                        L.s.head[ST_DIG0] = ts;
+                        L.s.head[ST_DIG1] = tx;
+                        L.s.head[ST_DONE] = 1;
+                    }
+                }
             }
             return;
         }
-        __syncthreads();  // M' complete before it is read as M
+        // M' complete before it is read as M
+        if (wide) {
+            uint32_t u0, u1, u2;
+            bool u3;
+            if (!cl_meet(*cl, true, 0, 0, false, &u0, &u1, &u2, &u3)) {
+                give_up();
+                return;
+            }
+            wide = St > CL_ROWS;
+        } else {
+            __syncthreads();
+        }
         M = Mn;
-        R = S;
-        ld = S;
+        R = St;
+        ld = St;
         m_lds = n_lds;
         if (!n_lds) mloc = next;
         next ^= 1u;
@@ -611,14 +911,16 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
 // argument segment is read from host memory, a round trip of its own for
 // every line the levels touch); else d_plan in device memory.  Two
 // instances, not a select: a pointer that may address either space is
-// generic.  At the end the status goes to `st` in one go and the completion
+// generic.  Workgroups after the first help with its larger levels (each
+// with its lookups at loc + its number * loc_stride).  At the end the status goes to `st` in one go and the completion
 // word is posted (post_seq) once every wave's rows and tables have left it.
 template <bool INL>
 __global__ __launch_bounds__(1024) void k_fused_levels(const FPlan *d_plan, FPlanArg inl, uint32_t j0, uint32_t *M0,
                                                       uint32_t R0, const uint32_t *b0_runs,
                                                       const uint64_t *b0, uint64_t nwords, uint32_t *buf0,
                                                       uint32_t *buf1, uint32_t *loc, uint32_t *out, FStatus *st,
-                                                      uint64_t *seq_slot, uint64_t seq_value) {
+                                                      uint64_t *seq_slot, uint64_t seq_value, ClusterCtl *ctl,
+                                                      uint32_t cl_rows, uint32_t cl_out, uint64_t loc_stride) {
     __shared__ FusedLevelsLds L;
     const FPlan *plan = INL ? &L.plan.p : d_plan;
     if (INL) {
@@ -627,7 +929,7 @@ __global__ __launch_bounds__(1024) void k_fused_levels(const FPlan *d_plan, FPla
             reinterpret_cast<uint32_t *>(&L.plan)[threadIdx.x] = reinterpret_cast<const uint32_t *>(&inl)[threadIdx.x];
     }
     st_clear(L.q.s);
-    if (b0) {
+    if (b0 && blockIdx.x == 0) {
         // each wave owns a contiguous run of words (the split the filter's
         // counts used, whose per-run set bits `b0_runs` give the wave its
         // first output row), read 64 at a time (coalesced) with eight such
@@ -662,25 +964,32 @@ __global__ __launch_bounds__(1024) void k_fused_levels(const FPlan *d_plan, FPla
         }
     }
     __syncthreads();  // status cleared, plan copied and M0 written before the levels read them
-    fused_query<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true>(plan, j0, M0, R0, R0, buf0, buf1, loc, out, L.q);
+    Cluster cl{ctl, gridDim.x, 1u, cl_rows, cl_out, 0u, 0u, L.cl};
+    fused_query<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true, true>(plan, j0, M0, R0, R0, buf0, buf1,
+                                                                   loc + blockIdx.x * loc_stride, out, L.q, nullptr,
+                                                                   0, &cl);
+    if (blockIdx.x != 0) return;
     // every wave's stores are done before the first one releases them
     __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
     __syncthreads();
     st_flush(L.q.s, st);
     if (threadIdx.x == 0) post_seq(seq_slot, seq_value);
+    if (gridDim.x > 1) cl_call(cl, 0, 0, 0, 0, 0);  // the helpers leave
 }
 
 void launch_fused(gsi_ctx *c, const FPlan *d_plan, const FPlanArg &inl, uint32_t j0, uint32_t *M0, uint32_t R0,
                   const uint32_t *b0_runs, const uint64_t *b0, uint64_t nwords, uint32_t *buf0, uint32_t *buf1, uint32_t *loc, uint32_t *out,
-                  FStatus *d_status, double alg_bytes) {
+                  FStatus *d_status, double alg_bytes, const FusedCluster &fc) {
     uint64_t seqv = 0;
     uint64_t *seqp = seq_slot(c, d_status, &seqv);
     if (d_plan)
-        launch(c, "k_fused_levels", alg_bytes, k_fused_levels<false>, 1, 1024, d_plan, inl, j0, M0, R0, b0_runs, b0,
-               nwords, buf0, buf1, loc, out, d_status, seqp, seqv);
+        launch(c, "k_fused_levels", alg_bytes, k_fused_levels<false>, fc.nb, 1024, d_plan, inl, j0, M0, R0, b0_runs, b0,
+               nwords, buf0, buf1, loc, out, d_status, seqp, seqv,
+               reinterpret_cast<ClusterCtl *>(fc.ctl), fc.cap_rows, fc.cap_out, fc.loc_stride);
     else
-        launch(c, "k_fused_levels", alg_bytes, k_fused_levels<true>, 1, 1024, d_plan, inl, j0, M0, R0, b0_runs, b0,
-               nwords, buf0, buf1, loc, out, d_status, seqp, seqv);
+        launch(c, "k_fused_levels", alg_bytes, k_fused_levels<true>, fc.nb, 1024, d_plan, inl, j0, M0, R0, b0_runs, b0,
+               nwords, buf0, buf1, loc, out, d_status, seqp, seqv,
+               reinterpret_cast<ClusterCtl *>(fc.ctl), fc.cap_rows, fc.cap_out, fc.loc_stride);
     c->seq_armed = seqp != nullptr;
 }
 

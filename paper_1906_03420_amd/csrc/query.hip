@@ -215,8 +215,9 @@ static void query_signatures(const HostQuery &q, FilterArgs &fa, bool homo = fal
 constexpr uint32_t FILTER_TILES = 1;
 
 __global__ __launch_bounds__(QT) void k_filter(const uint32_t *sig, uint32_t n, uint64_t nwords, FilterArgs fa,
-                                              uint64_t *bits, unsigned long long *acc) {
-    if (blockIdx.x == 0 && threadIdx.x <= fa.k) acc[threadIdx.x] = 0;  // for k_bit_counts
+                                              uint64_t *bits, unsigned long long *acc, uint32_t nacc) {
+    if (blockIdx.x == 0)
+        for (uint32_t t = threadIdx.x; t < nacc; t += QT) acc[t] = 0;
     const uint32_t need = fa.label_only ? 0u : fa.word_mask;
     const uint32_t K = fa.k;
     const uint32_t lane = lane_id();
@@ -383,16 +384,17 @@ static void bit_counts(gsi_ctx *c, uint32_t k, const uint64_t *bits, uint64_t nw
     c->seq_armed = seqp != nullptr;
 }
 
+// words at `acc` the filter clears at least: k accumulators and a ticket
+constexpr uint32_t FILTER_ACC = GSI_MAX_K + 1;
+
 static void launch_filter(gsi_ctx *c, gsi_graph *g, const FilterArgs &fa, uint64_t *bits, uint32_t *counts,
-                          uint32_t *runs, const HostQuery *mq = nullptr) {
-    Scratch s(c);
-    unsigned long long *acc = s.get<unsigned long long>(GSI_MAX_K + 1, "count accumulators");
+                          uint32_t *runs, unsigned long long *acc, uint32_t nacc, const HostQuery *mq = nullptr) {
     const uint64_t nwords = ((uint64_t)g->n + 63) / 64;
     const uint32_t nb = nblocks(g->n);
     const uint32_t need = fa.label_only ? 0u : fa.word_mask;
     double bytes = 4.0 * g->n * (1 + __builtin_popcount(need)) + (double)fa.k * nwords * 8;
     const uint32_t nfb = (nb + FILTER_TILES - 1) / FILTER_TILES;
-    launch(c, "k_filter", bytes, k_filter, nfb, QT, (const uint32_t *)g->sig, g->n, nwords, fa, bits, acc);
+    launch(c, "k_filter", bytes, k_filter, nfb, QT, (const uint32_t *)g->sig, g->n, nwords, fa, bits, acc, nacc);
     if (g->multi && mq) {
         RefineArgs ra;
         memset(&ra, 0, sizeof(ra));
@@ -440,14 +442,17 @@ __device__ __forceinline__ const FilterArgs &filter_pass(const FilterArgs *passe
 
 // ARG: the one pass is the kernel argument `arg` (a single query, which
 // saves its upload), `part` is not written (the counts come from the
-// bitsets) and the accumulators of k_bit_counts are cleared.
+// bitsets) and nacc words at `acc` are cleared: the accumulators of
+// k_bit_counts and what else the query's later launches expect zero.
 template <bool ARG>
 __global__ __launch_bounds__(QT) void k_filter_multi(const uint32_t *sig, uint32_t n, uint64_t nwords,
                                                     const FilterArgs *__restrict__ passes, FilterOne<ARG> arg,
-                                                    uint64_t *bits, uint32_t *part, unsigned long long *acc) {
+                                                    uint64_t *bits, uint32_t *part, unsigned long long *acc,
+                                                    uint32_t nacc) {
     constexpr uint32_t TW = FM_TILE / 64;  // bitset words per round
     const FilterArgs &fa = filter_pass(passes, arg);
-    if (ARG && blockIdx.x == 0 && threadIdx.x <= fa.k) acc[threadIdx.x] = 0;
+    if (ARG && blockIdx.x == 0)
+        for (uint32_t t = threadIdx.x; t < nacc; t += QT) acc[t] = 0;
     __shared__ uint32_t s_q[GSI_MAX_K][GSI_SIG_WORDS];
     __shared__ uint32_t s_dst[GSI_MAX_K];
     __shared__ uint32_t s_cnt[GSI_MAX_K];
@@ -618,7 +623,7 @@ void run_filter_many(gsi_graph *g, const std::vector<const HostQuery *> &qs, con
     GSI_HIP(hipMemcpyAsync(dp, passes.data(), sizeof(FilterArgs) * npass, hipMemcpyHostToDevice, c->stream));
     const double bytes = 4.0 * g->n * words + (double)all.size() * nwords * 8;
     launch(c, "k_filter", bytes, k_filter_multi<false>, dim3(nb, npass), QT, (const uint32_t *)g->sig, g->n, nwords,
-           (const FilterArgs *)dp, FilterOne<false>{}, bits, part, (unsigned long long *)nullptr);
+           (const FilterArgs *)dp, FilterOne<false>{}, bits, part, (unsigned long long *)nullptr, 0u);
     launch(c, "k_filter_counts", 4.0 * nb * all.size(), k_filter_counts_multi, dim3(GSI_MAX_K, npass), QT,
            (const uint32_t *)part, nb, (const FilterArgs *)dp, counts);
     sync(c);  // `passes` is read by the copy above
@@ -630,7 +635,7 @@ void run_filter_many(gsi_graph *g, const std::vector<const HostQuery *> &qs, con
 // per-run counts come from the bitsets (k_bit_counts), as in launch_filter.
 constexpr bool GROUPED_SINGLE_FILTER = true;
 static void launch_filter_grouped(gsi_ctx *c, gsi_graph *g, const FilterArgs &f, uint64_t *bits, uint32_t *counts,
-                                  uint32_t *runs) {
+                                  uint32_t *runs, unsigned long long *acc, uint32_t nacc) {
     FilterOne<true> one;
     FilterArgs &fa = one.fa;
     uint32_t idx[GSI_MAX_K];
@@ -643,32 +648,31 @@ static void launch_filter_grouped(gsi_ctx *c, gsi_graph *g, const FilterArgs &f,
         fa.dst[t] = f.dst[idx[t]];
         memcpy(fa.q[t], f.q[idx[t]], sizeof(fa.q[t]));
     }
-    Scratch s(c);
     const uint64_t nwords = ((uint64_t)g->n + 63) / 64;
     const uint32_t nrounds = (uint32_t)(((uint64_t)g->n + FM_TILE - 1) / FM_TILE);
     const uint32_t nb = std::max<uint32_t>(1, std::min<uint32_t>(nrounds, 8192));
-    unsigned long long *acc = s.get<unsigned long long>(GSI_MAX_K + 1, "count accumulators");
     const double bytes = 4.0 * g->n * (1 + __builtin_popcount(f.word_mask)) + (double)f.k * nwords * 8;
     launch(c, "k_filter", bytes, k_filter_multi<true>, dim3(nb, 1), QT, (const uint32_t *)g->sig, g->n, nwords,
-           (const FilterArgs *)nullptr, one, bits, (uint32_t *)nullptr, acc);
+           (const FilterArgs *)nullptr, one, bits, (uint32_t *)nullptr, acc, nacc);
     bit_counts(c, f.k, bits, nwords, counts, runs, acc);
 }
 
 static void filter_impl(gsi_graph *g, const HostQuery &q, bool label_only, uint64_t *bits, uint32_t *counts,
-                        bool homo = false, uint32_t *runs = nullptr) {
+                        unsigned long long *acc, uint32_t nacc, bool homo = false, uint32_t *runs = nullptr) {
     gsi_ctx *c = g->ctx;
     FilterArgs fa;
     query_signatures(q, fa, homo);
     fa.label_only = label_only ? 1u : 0u;
     if (GROUPED_SINGLE_FILTER && !label_only && !q.multi && !g->multi) {
-        launch_filter_grouped(c, g, fa, bits, counts, runs);
+        launch_filter_grouped(c, g, fa, bits, counts, runs, acc, nacc);
         return;
     }
-    launch_filter(c, g, fa, bits, counts, runs, q.multi ? &q : nullptr);
+    launch_filter(c, g, fa, bits, counts, runs, acc, nacc, q.multi ? &q : nullptr);
 }
 
 void run_filter(gsi_graph *g, const HostQuery &q, uint64_t *bits, uint32_t *counts) {
-    filter_impl(g, q, false, bits, counts);
+    Scratch s(g->ctx);
+    filter_impl(g, q, false, bits, counts, s.get<unsigned long long>(FILTER_ACC, "count accumulators"), FILTER_ACC);
 }
 
 // ----------------------------------------------------- M0 from a bitset
@@ -1953,7 +1957,12 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
     uint64_t *dscal = c->mbox_dev + MBOX_SCALARS;
     auto tf = std::chrono::steady_clock::now();
     uint32_t *druns = s.get<uint32_t>((uint64_t)k * bit_runs(nwords), "candidate run counts");
-    filter_impl(g, q, (flags & GSI_FILTER_LABEL_ONLY) != 0, bits, dcnt, homo, druns);
+    // cleared by the filter: the counts' accumulators, then the control
+    // blocks of the fused kernel's launches
+    constexpr uint32_t CTL_BLOCKS = 8, ACC_WORDS = 64 + CTL_BLOCKS * (uint32_t)(CL_CTL_BYTES / 8);
+    static_assert(FILTER_ACC <= 64, "accumulators before the control blocks");
+    unsigned long long *zeroed = s.get<unsigned long long>(ACC_WORDS, "count accumulators, control blocks");
+    filter_impl(g, q, (flags & GSI_FILTER_LABEL_ONLY) != 0, bits, dcnt, zeroed, ACC_WORDS, homo, druns);
     std::vector<uint32_t> cand(k);
     {
         uint64_t tmp[GSI_MAX_K / 2 + 1];
@@ -2263,19 +2272,69 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
     std::unique_ptr<FPlanArg> finl;  // the plan as a kernel argument, when it fits
     uint32_t *fbuf0 = nullptr, *fbuf1 = nullptr, *floc = nullptr;
     FStatus *fdst = nullptr;
+    // Helpers for its larger levels, unless a limit of the query's options
+    // applies to tables the workgroup would otherwise not build, or their
+    // buffers would take a noticeable part of the arena.  Where the expected
+    // slots of every level are few, the first launch goes without (starting
+    // and ending them takes 5 us: 78 -> 73 us on a query of 12 rows); if it
+    // stops, the estimate was wrong and the next ones have them.
+    FusedCluster fc;
+    bool helpers_first = true;
+    uint32_t fctl_used = 0;  // control blocks used
+    uint64_t *fctl = reinterpret_cast<uint64_t *>(zeroed + 64);
+    {
+        const uint64_t stride = fused_loc_words(max_ne, FUSED_MAX_ROWS);
+        const uint64_t need = 4 * (2ull * CL_CAP_ROWS * k + stride * CL_MAX_WG + (count_only ? 0ull : (uint64_t)CL_CAP_OUT * k));
+        if (!max_rows && cap_rows == FUSED_MAX_ROWS && cap_slots == FUSED_MAX_SLOTS &&
+            need <= c->arena.largest_free() / 16) {
+            double rows = (double)R, slots = 0;
+            for (uint32_t j = 1; j < k; j++) {
+                // the first edge's mean list, each element surviving as often
+                // as a vertex is a candidate
+                const uint32_t u = order[j];
+                double len = 0;
+                for (auto &p : q.adj[u])
+                    if (p.first == e0src[j] && g->G[p.second]) len = 2.0 * (double)g->edges[p.second] / g->G[p.second];
+                slots = std::max(slots, rows * len);
+                rows *= len * (double)cand[u] / (double)g->n;
+            }
+            fc.nb = CL_MAX_WG;
+            helpers_first = slots > CL_FEW_SLOTS;
+            fc.cap_rows = CL_CAP_ROWS;
+            fc.cap_out = CL_CAP_OUT;
+            fc.loc_stride = stride;
+        }
+    }
+    // tables the workgroup (and its helpers) may be given
+    const uint64_t take_rows = fc.nb > 1 ? CL_TAKE_ROWS : cap_rows;
+    const double take_slots = fc.nb > 1 ? (double)CL_TAKE_SLOTS : (double)cap_slots;
     auto run_fused = [&](uint32_t j0, const uint64_t *root_bits, uint32_t &stop) -> bool {
         if (!fhp) {
             finl.reset(new FPlanArg());
             fdplan = fused_plan(cap_rows, cap_slots, &fhp, finl.get());
-            fbuf0 = fs.get<uint32_t>((uint64_t)cap_rows * k, "fused table 0");
-            fbuf1 = fs.get<uint32_t>((uint64_t)cap_rows * k, "fused table 1");
-            floc = fs.get<uint32_t>(fused_loc_words(max_ne, cap_rows), "fused lookups");
+            const uint64_t rows = fc.nb > 1 ? fc.cap_rows : cap_rows;
+            fbuf0 = fs.get<uint32_t>(rows * k, "fused table 0");
+            fbuf1 = fs.get<uint32_t>(rows * k, "fused table 1");
+            floc = fs.get<uint32_t>(fc.nb > 1 ? fc.loc_stride * fc.nb : fused_loc_words(max_ne, cap_rows),
+                                    "fused lookups");
             fdst = reinterpret_cast<FStatus *>(c->mbox_dev + MBOX_STATUS);
         }
-        uint32_t *out = count_only ? nullptr : persist<uint32_t>(c, (uint64_t)cap_slots * k, "result rows");
+        uint32_t *out =
+            count_only ? nullptr : persist<uint32_t>(c, (uint64_t)(fc.nb > 1 ? fc.cap_out : cap_slots) * k, "result rows");
         res->rows = out;
+        FusedCluster now = fc;
+        if (fc.nb > 1 && !helpers_first) {
+            now = FusedCluster();
+            helpers_first = true;
+        } else if (fc.nb > 1) {
+            if (fctl_used == CTL_BLOCKS) {
+                fill_u64(c, fctl, 0, CTL_BLOCKS * CL_CTL_BYTES / 8);
+                fctl_used = 0;
+            }
+            now.ctl = fctl + fctl_used++ * (CL_CTL_BYTES / 8);
+        }
         launch_fused(c, fdplan, *finl, j0, M, (uint32_t)R, druns + (uint64_t)order[0] * BITS_RUNS, root_bits, nwords,
-                     fbuf0, fbuf1, floc, out, fdst, 0.0);
+                     fbuf0, fbuf1, floc, out, fdst, 0.0, now);
         const size_t frec = c->recs.size();  // the fused launch's record (the wait may add one)
         FStatus *hs = reinterpret_cast<FStatus *>(c->mbox_host + MBOX_STATUS);
         wait_mailbox(c);
@@ -2317,7 +2376,8 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
     // Small root sets: the workgroup starts; the per-level kernels continue
     // from where it stopped, and hand the query back to it once the table
     // fits again.
-    if (!cp.active && fused_ok && R <= cap_rows) {
+    if (!cp.active && fused_ok && R <= take_rows) {
+        helpers_first |= R > CL_ROWS;
         if (run_fused(1, m0_in_fused ? b0 : nullptr, jstart)) return finish();
     }
     uint32_t fused_stuck = NONE32;  // level at which the workgroup last stopped without progress
@@ -2684,7 +2744,7 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
         // back to the single workgroup when the table fits and, at this
         // level's slots per row, so would the next level's |GBA|; not right
         // after it stopped without finishing a level
-        if (!cp.active && fused_ok && R <= cap_rows && (double)R * slots_per_row <= cap_slots && fused_stuck != j) {
+        if (!cp.active && fused_ok && R <= take_rows && (double)R * slots_per_row <= take_slots && fused_stuck != j) {
             uint32_t stop = 0;
             if (run_fused(j + 1, nullptr, stop)) return finish();
             if (stop == j + 1) fused_stuck = j + 1;
