@@ -268,18 +268,17 @@ typedef struct {
  * launches, which measure faster (a tile's rows wait on the slowest join
  * before it).
  * Up to 32768 roots one kernel runs the levels while the tables stay small:
- * its first workgroup those of up to 1024 rows and 4096 |GBA| slots (with F,
+ * its first workgroup those of up to 1024 rows and 8192 |GBA| slots (with F,
  * the keep bits and the survivor prefix sums in LDS), that and 63 helper
- * workgroups together larger ones, up to 131072 rows and 16384 slots for each
- * workgroup's share.  Without helpers (max_rows, fused_max_rows or
+ * workgroups together larger ones, up to 131072 rows and 2^20 slots (each row
+ * counted as five more).  Without helpers (max_rows, fused_max_rows or
  * fused_max_slots set, or an arena in which their buffers would take more
  * than a sixteenth of the free space) the limits are 4096 roots, 4096 rows and
  * 16384 slots.  The per-level kernels run a level that does not fit, and the
  * kernel takes the query back once the new table fits and the next level's
  * |GBA|, estimated at the current slots per row, would fit too.  Above 4096
- * roots, rows of M being
- * independent at every level, step 3 first runs on root chunks: small groups
- * of rows of M = C(u_first), each taken by one 256-thread workgroup of a
+ * roots, rows of M being independent at every level, step 3 first runs on root
+ * chunks: small groups of rows of M = C(u_first), each taken by one 256-thread workgroup of a
  * persistent launch that runs all levels of its chunk (1024 rows and 4096
  * slots per level).  The roots of chunks that do not fit continue with the
  * per-level kernels; the rows of both parts are concatenated (chunk rows
@@ -400,7 +399,8 @@ typedef struct {
  * Algorithm 4) in LDS-staged form.  A first tier uses workgroups of
  * `threads` threads (64, 256 or 1024; tables of up to 4x`threads` rows and
  * 16x`threads` |GBA| slots per level); queries it cannot hold rerun in a
- * second tier of 1024-thread workgroups, and the rest run level-synchronously
+ * second tier of 1024-thread workgroups, then, when at most 32 are left, on
+ * several such workgroups each, and the rest run level-synchronously
  * together.  `grid_scale` (1..8) multiplies the number of
  * resident workgroups per compute unit that is launched, in eighths. */
 typedef struct {
@@ -448,7 +448,7 @@ typedef struct {
     uint32_t queries;
     uint32_t empty;        /* answered by the filter alone (0 rows) */
     uint32_t tier1;        /* finished in the first fused tier */
-    uint32_t tier2;        /* finished in the 1024-thread tier */
+    uint32_t tier2;        /* finished in 1024-thread workgroups */
     uint32_t per_level;    /* finished with the per-level kernels */
     gsi_batch_schedule schedule;
     double filter_ms, tier1_ms, tier2_ms, per_level_ms, total_ms;  /* host wall time */
@@ -532,7 +532,7 @@ gsi_status gsi_server_poll(gsi_server *s, uint64_t *tickets, uint32_t capacity, 
 
 #define GSI_PATH_EMPTY 0   /* answered by the filter (0 rows) */
 #define GSI_PATH_TIER1 1   /* first fused tier */
-#define GSI_PATH_TIER2 2   /* 1024-thread fused tier */
+#define GSI_PATH_TIER2 2   /* 1024-thread workgroups, one or several */
 #define GSI_PATH_SINGLE 3  /* one-vertex query */
 #define GSI_PATH_LEVELS 4  /* level-synchronous engine */
 #define GSI_PATH_SOLO 5    /* alone, through gsi_query_run's path (low load) */

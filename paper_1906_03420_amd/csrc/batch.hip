@@ -137,6 +137,68 @@ static std::vector<FusedQuery> run_tier(gsi_graph *g, const std::shared_ptr<Roun
 }
 
 
+// Runs each query of `list` with the workgroups of cus / n CUs, fills the
+// entries of those that finish and returns the others (all of them when the
+// tables would take too much of the arena).
+static std::vector<FusedQuery> run_clusters(gsi_graph *g, const std::vector<Slot *> &slots, bool count_only,
+                                            uint32_t nb, const std::vector<FusedQuery> &list,
+                                            const std::vector<uint32_t> &ks, const uint8_t *d_plans,
+                                            const uint32_t *d_M0) {
+    gsi_ctx *c = g->ctx;
+    const uint32_t n = (uint32_t)list.size();
+    uint32_t kmax = 2;
+    uint64_t out_words = 0;
+    const uint32_t cap_out = std::min<uint32_t>(CL_CAP_OUT, nb * (CL_CAP_OUT / CL_MAX_WG));
+    for (auto &f : list) {
+        kmax = std::max(kmax, ks[f.qi]);
+        out_words += count_only ? 0 : (uint64_t)cap_out * ks[f.qi];
+    }
+    const uint64_t words = fused_cluster_words(nb, kmax) * n;
+    if (4 * (words + out_words) > c->arena.largest_free() / 8) return list;
+    std::vector<FClusterItem> items(n);
+    for (uint32_t i = 0; i < n; i++) {
+        Slot &sl = *slots[list[i].qi];
+        if (!count_only) sl.own = persist<uint32_t>(c, (uint64_t)cap_out * ks[list[i].qi], "cluster rows");
+        items[i].plan_off = list[i].plan_off;
+        items[i].m0_off = list[i].m0_off;
+        items[i].out = sl.own;
+        items[i].R0 = list[i].R0;
+    }
+    Scratch ts(c);
+    FClusterItem *d_items = ts.get<FClusterItem>(n, "cluster items");
+    uint32_t *scratch = ts.get<uint32_t>(words, "cluster tables");
+    FStatus *d_st = reinterpret_cast<FStatus *>(ts.get<uint64_t>((uint64_t)n * sizeof(FStatus) / 8, "cluster status"));
+    uint64_t *ctl = ts.get<uint64_t>(n * (CL_CTL_BYTES / 8), "cluster control");
+    GSI_HIP(hipMemcpyAsync(d_items, items.data(), sizeof(FClusterItem) * n, hipMemcpyHostToDevice, c->stream));
+    fill_u64(c, ctl, 0, n * (CL_CTL_BYTES / 8));
+    launch_fused_cluster(c, nb, d_plans, d_items, n, d_M0, scratch, kmax, ctl, cap_out, d_st);
+    std::vector<FStatus> hs(n);
+    GSI_HIP(hipMemcpyAsync(hs.data(), d_st, sizeof(FStatus) * n, hipMemcpyDeviceToHost, c->stream));
+    sync(c);  // also keeps `items` alive until its copy has run
+    std::vector<FusedQuery> left;
+    for (uint32_t i = 0; i < n; i++) {
+        Slot &sl = *slots[list[i].qi];
+        if (hs[i].done) {
+            sl.done = true;
+            sl.path = PATH_TIER2;
+            sl.count = hs[i].count;
+            sl.digest[0] = hs[i].digest[0];
+            sl.digest[1] = hs[i].digest[1];
+        } else {
+            left.push_back(list[i]);
+        }
+        if (!sl.own) continue;
+        if (sl.done && sl.count) {
+            c->arena.shrink(sl.own, sl.count * sl.k * 4);
+            sl.rows = sl.own;
+        } else {
+            c->arena.release(sl.own);
+            sl.own = nullptr;
+        }
+    }
+    return left;
+}
+
 static void *round_block(gsi_ctx *c, uint64_t bytes, const char *what) {
     void *p = c->arena.alloc(bytes ? bytes : 256, false);
     if (!p)
@@ -248,7 +310,7 @@ std::vector<WideQuery> admit_round(gsi_graph *g, const std::vector<const HostQue
         pl.m0_off = m0_total;
         m0_total += pl.R0;
         root_rows.push_back(qbase[pl.a] + pl.order[0]);
-        if (levels_only || pl.R0 > t2.cap_rows) continue;
+        if (levels_only || pl.R0 > CL_TAKE_ROWS) continue;
         uint32_t n_edges = 0;
         for (uint32_t j = 1; j < q.k; j++)
             for (uint32_t i = 0; i < j; i++)
@@ -297,7 +359,7 @@ std::vector<WideQuery> admit_round(gsi_graph *g, const std::vector<const HostQue
         f.plan_off = off;
         f.m0_off = pl.m0_off;
         f.out_off = out_total;
-        out_total += count_only ? 0 : (uint64_t)t2.cap_slots * q.k;
+        if (pl.R0 <= t2.cap_rows) out_total += count_only ? 0 : (uint64_t)t2.cap_slots * q.k;
         fused.push_back(f);
     }
 
@@ -324,28 +386,34 @@ std::vector<WideQuery> admit_round(gsi_graph *g, const std::vector<const HostQue
         uint8_t *d_plans = ps.get<uint8_t>(plan_blob.size(), "fused plans");
         GSI_HIP(hipMemcpyAsync(d_plans, plan_blob.data(), plan_blob.size(), hipMemcpyHostToDevice, c->stream));
         if (!count_only && out_total) rd->out = static_cast<uint32_t *>(round_block(c, out_total * 4, "fused rows"));
-        std::vector<FusedQuery> first, second;
-        for (auto &f : fused) (f.R0 <= t1.cap_rows ? first : second).push_back(f);
+        std::vector<FusedQuery> first, second, large;
+        for (auto &f : fused) (f.R0 <= t1.cap_rows ? first : f.R0 <= t2.cap_rows ? second : large).push_back(f);
         auto ta = std::chrono::steady_clock::now();
         std::vector<FusedQuery> left = run_tier(g, rd, slots, count_only, PATH_TIER1, t1, sched.grid_scale, first, ks, d_plans, d_M0);
         st->tier1 += (uint32_t)(first.size() - left.size());
         st->tier1_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - ta).count();
-        if (t1.threads != t2.threads) {
-            second.insert(second.end(), left.begin(), left.end());
-            left.clear();
-        } else {
-            left.insert(left.end(), second.begin(), second.end());
-            second.clear();
-        }
+        second.insert(second.end(), left.begin(), left.end());
         auto tb = std::chrono::steady_clock::now();
-        std::vector<FusedQuery> left2 = run_tier(g, rd, slots, count_only, PATH_TIER2, t2, 8, second, ks, d_plans, d_M0);
-        st->tier2 += (uint32_t)(second.size() - left2.size());
+        std::vector<FusedQuery> left2 = second;
+        if (t1.threads != t2.threads)
+            left2 = run_tier(g, rd, slots, count_only, PATH_TIER2, t2, 8, second, ks, d_plans, d_M0);
+        // A few queries that are left take several CUs each, in passes over
+        // those that did not fit while there are at least twice the CUs for
+        // each; many go to the engine.  (Before the 1024-thread tier, in its
+        // place: a batch of 131 small queries 0.57 -> 0.63 ms.)
+        left2.insert(left2.end(), large.begin(), large.end());
+        for (uint32_t nb = 0; !left2.empty() && left2.size() <= CLB_MAX_QUERIES;) {
+            const uint32_t per = std::min<uint32_t>(CL_MAX_WG, (uint32_t)cu_count(c) / (uint32_t)left2.size());
+            if (per < 2 || per < 2 * nb) break;
+            nb = per;
+            left2 = run_clusters(g, slots, count_only, nb, left2, ks, d_plans, d_M0);
+        }
+        st->tier2 += (uint32_t)(second.size() + large.size() - left2.size());
         st->tier2_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - tb).count();
-        for (auto &f : left) to_wide.push_back(f.qi);
         for (auto &f : left2) to_wide.push_back(f.qi);
     }
     for (auto &pl : planned)
-        if (levels_only || pl.R0 > t2.cap_rows) to_wide.push_back(pl.qi);
+        if (levels_only || pl.R0 > CL_TAKE_ROWS) to_wide.push_back(pl.qi);
 
     // one-vertex queries: the root table is the answer
     for (uint32_t qi : single) {

@@ -24,6 +24,9 @@ struct FEdge {            // one linking edge of a level
 // A level of a multi-labelled query can have more linking edges than placed
 // vertices (one per label of a pair).
 inline uint64_t fused_loc_words(uint32_t max_ne, uint64_t rows) { return (2ull * max_ne + 1) * rows; }
+// words of lookups of a shared level: those and each row's weight before it,
+// first element and list length (a table of the first workgroup alone fits)
+inline uint64_t cluster_loc_words(uint32_t max_ne, uint64_t rows) { return (2ull * max_ne + 4) * rows; }
 
 struct FPlan {
     uint32_t k, count_only, cap_rows, cap_slots;
@@ -96,6 +99,21 @@ void launch_fused_batch(gsi_ctx *c, const FTier &t, uint32_t grid, const uint8_t
                         uint32_t nitems, const uint32_t *M0all, uint32_t *scratch, uint64_t slot_words, uint32_t kmax,
                         uint32_t *outall, FStatus *sts, uint32_t *counter, double bytes);
 
+// A few queries of a batch, each run by nb workgroups as in the single-query
+// kernel (`ctl`: a zeroed control block per query).  Its last level may have
+// cap_out rows, written to `out`.
+struct FClusterItem {
+    uint64_t plan_off;  // byte offset of its FPlan in the plan buffer
+    uint64_t m0_off;    // first root row in the concatenated root tables
+    uint32_t *out;      // cap_out x k words (null: count only)
+    uint32_t R0;        // root rows
+    uint32_t pad;
+};
+uint64_t fused_cluster_words(uint32_t nb, uint32_t kmax);  // scratch of each query
+void launch_fused_cluster(gsi_ctx *c, uint32_t nb, const uint8_t *plans, const FClusterItem *items, uint32_t nitems,
+                          const uint32_t *M0all, uint32_t *scratch, uint32_t kmax, uint64_t *ctl, uint32_t cap_out,
+                          FStatus *sts);
+
 // One query split into chunks of `chunk_rows` rows of its table M0 (R0
 // rows, j0 columns, column stride R0; the rows of M are independent at
 // every level of Algorithm 3): a persistent launch of the tier's workgroups
@@ -128,26 +146,34 @@ void launch_take_rows(gsi_ctx *c, uint32_t nlist, const uint32_t *M0, uint32_t R
 // (homomorphism), with 32 3.38 and 1.84, with 64 3.42 and 1.85.
 constexpr uint32_t CL_MAX_WG = 64;
 // A level is shared when it has more than CL_ROWS rows or CL_SLOTS slots: one
-// workgroup alone takes about 15 us for 4096 slots, a shared level costs 12 to
-// 15 us whatever it holds.  2048 slots measured the same, 8192 slower (walk
-// 3.42 -> 3.45 ms, two-label queries 0.69 -> 0.70 ms).
-constexpr uint32_t CL_ROWS = 1024, CL_SLOTS = 4096;
+// workgroup alone takes 15 us for 4096 slots, a shared level costs 12 to 18 us.
+// 2048 to 12288 slots measured the same within 2 % where levels are larger
+// (walk 3.4 to 3.5 ms, homomorphism 1.8, two-label queries 0.69 to 0.71);
+// queries whose largest level has 4300 slots took 97 us shared, 90 alone.
+constexpr uint32_t CL_ROWS = 1024, CL_SLOTS = 8192;
+// A shared level's parts stay as they are when none weighs more; evening them
+// out publishes every row's list (a meeting with fences, a search: 5 us).
+constexpr uint32_t CL_EVEN = 4096;
 constexpr uint32_t CL_CAP_ROWS = 131072;   // rows of a shared level's table (fewer than 2^22)
 constexpr uint32_t CL_CAP_OUT = 262144;    // result rows
 // A table is handed to the kernel when it has at most this many rows and, at
 // the slots per row of the level before, this many slots; a level past the
-// 2^20 slots that 64 workgroups hold is run twice.  131072 and 524288 slots
+// 2^20 that 64 workgroups hold is run twice.  131072 and 524288 slots
 // measured alike (walk 3.42 and 3.41 ms, homomorphism 1.85 and 1.83 ms).
 constexpr uint32_t CL_TAKE_ROWS = 32768, CL_TAKE_SLOTS = 131072;
 // No helpers at first when every level is expected to have fewer slots: with
 // them a query of 16 rows takes 78 us instead of 73.
 constexpr double CL_FEW_SLOTS = 512;
+// A batch's remaining queries run with several workgroups each when they are
+// at most this many (8 CUs each): a pass takes 150 us where the 1024-thread
+// tier takes 120 and each level of the engine 100.  A batch of 48 queries, 16
+// of them left after the 1024-thread tier: 2.51 -> 1.87 ms.
+constexpr uint32_t CLB_MAX_QUERIES = 32;
 constexpr uint64_t CL_CTL_BYTES = 4096;    // control block, zeroed before the launch
 struct FusedCluster {
     uint32_t nb = 1;          // workgroups (1: no helpers)
     void *ctl = nullptr;
     uint32_t cap_rows = 0, cap_out = 0;
-    uint64_t loc_stride = 0;  // words of lookups per workgroup
 };
 
 // The single-query fused kernel, levels j0.. of the table M0 (R0 rows,

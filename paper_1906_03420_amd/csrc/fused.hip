@@ -145,10 +145,15 @@ struct FusedLds {
     uint32_t mt[2][fused_table_words<FT, XS>()];
 };
 // The single-query kernel's LDS: the workgroup's and a copy of the plan.
+struct ClusterLds {
+    uint64_t pre[CL_MAX_WG + 1];  // of the last meeting: the values before each workgroup's, and their sum
+    uint32_t w[8];
+};
+
 struct FusedLevelsLds {
     FusedLds<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true> q;
     FPlanArg plan;
-    uint32_t cl[8];
+    ClusterLds cl;
 };
 static_assert(sizeof(FusedLevelsLds) <= 160 * 1024, "fused workgroup LDS");
 
@@ -185,12 +190,14 @@ __device__ __forceinline__ void st_flush(const FusedStat &s, FStatus *st) {
 // the chip idles, and handing it to the per-level kernels costs five launches
 // and a host round trip.  The single-query kernel is launched with further
 // workgroups (helpers) that wait while the first one runs small levels alone;
-// on a larger one it publishes the table, and it and the helpers take equal
-// shares of its rows, in order, so a level's rows come out in the same order.
-// A shared level has two meeting points: the survivor counts, which give
-// every workgroup its place in the next table, and the table's completion;
-// they cost about 5 us.  On 10^6 vertices 16 walk queries went from 3.79 to
-// 3.42 ms, 8 homomorphism queries from 1.98 to 1.81 ms.
+// on a larger one it publishes the table, and it and the helpers locate equal
+// parts of its rows and join those, or equal shares of all their slots, in
+// order, so a level's rows come out in the same order.  The meeting points of
+// a shared level are the parts' weights, (where the slots are dealt out anew)
+// the rows' lists, the survivor counts, which give every workgroup its place
+// in the next table, and the table's completion; 2 us each, 3 with fences.
+// On 10^6 vertices 16 walk queries went from 3.79 to 3.5 ms, 8 homomorphism
+// queries from 1.98 to 1.8 ms.
 //
 // Only helpers that have checked in are called, so no workgroup waits for one
 // that is not running (another stream may hold the CUs).  Every wait is
@@ -198,10 +205,11 @@ __device__ __forceinline__ void st_flush(const FusedStat &s, FStatus *st) {
 // leaves, the others see the flag and leave too, and the first reports that
 // it stopped at the table it was given, which nothing has overwritten.
 constexpr uint32_t CL_SPINS = 1u << 16;  // about 50 ms
+constexpr uint32_t CL_HERE_SPINS = 16;   // about 10 us
 
-// One atomic word carries a workgroup's epoch, overflow flag, survivors and
-// slots, so the counts need no fence.  Two sets of words: a workgroup writes
-// epoch e + 2 only after all have read epoch e.
+// One atomic word carries a workgroup's epoch and its value, so the values
+// need no fence.  Two sets of words: a workgroup writes epoch e + 2 only after
+// all have read epoch e.
 struct ClusterCtl {
     unsigned long long word[2][CL_MAX_WG];
     unsigned long long call;   // the last call: its number << 32 | level << 8 | workgroups
@@ -210,16 +218,17 @@ struct ClusterCtl {
     uint32_t args[4];          // of the last call: rows, stride, place, epoch
     unsigned long long dig[CL_MAX_WG][2];  // digests of a shared last level
 };
-static_assert(sizeof(ClusterCtl) <= CL_CTL_BYTES, "control block");
+static_assert(sizeof(ClusterCtl) <= CL_CTL_BYTES && CL_CTL_BYTES % 8 == 0, "control block");
 
 struct Cluster {
     ClusterCtl *c;
+    uint32_t bid;       // this workgroup among them
     uint32_t nmax;      // workgroups launched
     uint32_t nb;        // those of the last call
     uint32_t cap_rows;  // rows of a shared level's table
     uint32_t cap_out;   // result rows
     uint32_t epoch, call;
-    uint32_t *lds;      // 8 words
+    ClusterLds *l;
 };
 
 template <typename T>
@@ -231,12 +240,11 @@ __device__ __forceinline__ void cl_store(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Every workgroup's survivors and slots: *off = survivors of the workgroups
-// before this one, *S and *gba the sums, *over set when one could not hold
-// its share.  With `table`, what every thread wrote before is visible to
-// every workgroup after.  False when a wait ran out.  Called by all threads.
-__device__ __forceinline__ bool cl_meet(Cluster &cl, bool table, uint32_t myS, uint32_t mygba, bool myover,
-                                        uint32_t *off, uint32_t *S, uint32_t *gba, bool *over) {
+// All workgroups meet: cl.l->pre gets the sums of `value` over the workgroups
+// before each one, and over all of them at pre[nb], w[1] the largest.  With `table`, what every
+// thread wrote before is visible to every workgroup after.  False when a wait
+// ran out.  Called by all threads; a barrier must follow before the next one.
+__device__ __forceinline__ bool cl_meet(Cluster &cl, bool table, uint32_t value) {
     const uint32_t e = ++cl.epoch;
     if (table) {
         __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
@@ -246,9 +254,7 @@ __device__ __forceinline__ bool cl_meet(Cluster &cl, bool table, uint32_t myS, u
         if (table) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         unsigned long long *w = cl.c->word[e & 1];
         const uint32_t lane = threadIdx.x;
-        if (lane == 0)
-            cl_store(w + blockIdx.x,
-                     ((unsigned long long)e << 32) | (myover ? 0x80000000ull : 0ull) | (myS << 15) | mygba);
+        if (lane == 0) cl_store(w + cl.bid, ((unsigned long long)e << 32) | value);
         unsigned long long x = 0;
         bool ok = lane >= cl.nb, dead = false;
         for (uint32_t spins = 1; __ballot(!ok); spins++) {
@@ -262,28 +268,54 @@ __device__ __forceinline__ bool cl_meet(Cluster &cl, bool table, uint32_t myS, u
             }
         }
         if (dead && lane == 0) cl_store(&cl.c->abort, 1u);
-        if (lane >= cl.nb) x = 0;
-        const uint32_t v = (uint32_t)(x >> 15) & 0x7FFFu;
-        const uint32_t inc = wave_inclusive_sum(v);
-        const uint32_t slots = wave_sum((uint32_t)x & 0x7FFFu);
-        const uint64_t any = __ballot((x & 0x80000000ull) != 0);
+        const uint64_t v = lane < cl.nb ? (uint64_t)(uint32_t)x : 0ull;
+        uint64_t inc = v;
+#pragma unroll
+        for (uint32_t d = 1; d < 64; d *= 2) {
+            const uint64_t o = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += o;
+        }
         if (table) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        if (lane == blockIdx.x) cl.lds[0] = inc - v;
-        if (lane == 63) {
-            cl.lds[1] = inc;
-            cl.lds[2] = slots;
-            cl.lds[3] = any ? 1u : 0u;
-            cl.lds[4] = dead ? 1u : 0u;
+        uint32_t most = (uint32_t)v;
+#pragma unroll
+        for (uint32_t d = 32; d; d /= 2) {
+            const uint32_t o = __shfl_xor(most, d, 64);
+            most = o > most ? o : most;
+        }
+        if (lane < cl.nb) cl.l->pre[lane + 1] = inc;
+        if (lane == 0) {
+            cl.l->pre[0] = 0;
+            cl.l->w[0] = dead ? 1u : 0u;
+            cl.l->w[1] = most;
         }
     }
     __syncthreads();
-    *off = uni(cl.lds[0]);
-    *S = uni(cl.lds[1]);
-    *gba = uni(cl.lds[2]);
-    *over = uni(cl.lds[3]) != 0;
-    const bool alive = uni(cl.lds[4]) == 0;
-    __syncthreads();  // before the words are written again
-    return alive;
+    return uni(cl.l->w[0]) == 0;
+}
+
+// The row of a shared level of R rows that holds weight a: the rows' weights
+// before them are pre[c] (of their part c) plus W[row].  Called by a wave.
+__device__ __forceinline__ uint32_t cl_row(const Cluster &cl, const uint32_t *W, uint32_t R, uint64_t a) {
+    const uint32_t lane = threadIdx.x & 63;
+    // the last part that starts at or before a and has rows
+    const uint32_t nb = cl.nb;
+    const uint32_t lo0 = (uint32_t)((uint64_t)R * lane / nb), hi0 = (uint32_t)((uint64_t)R * (lane + 1) / nb);
+    const uint64_t in = __ballot(lane < nb && lo0 < hi0 && cl.l->pre[lane] <= a);
+    const uint32_t c = in ? 63u - (uint32_t)__builtin_clzll(in) : 0u;
+    uint32_t lo = uni((uint32_t)((uint64_t)R * c / nb));
+    const uint32_t hi = uni((uint32_t)((uint64_t)R * (c + 1) / nb));
+    const uint64_t rel = a - cl.l->pre[c];
+    // 64 probes a round: row lo starts at or before a, row lo + n after it
+    uint32_t n = hi > lo ? hi - lo : 1u;
+    while (n > 1) {
+        const uint32_t step = (n + 63) / 64;
+        const uint32_t t = lane * step;
+        const uint64_t le = __ballot(t < n && (uint64_t)W[lo + (t < n ? t : 0u)] <= rel);
+        const uint32_t m = le ? 63u - (uint32_t)__builtin_clzll(le) : 0u;
+        lo += m * step;
+        n = n - m * step < step ? n - m * step : step;
+    }
+    return lo;
 }
 
 // The call of the first workgroup: level j of the table of R rows (stride
@@ -301,12 +333,17 @@ __device__ __forceinline__ bool cl_call(Cluster &cl, uint32_t j, uint32_t R, uin
     __syncthreads();
     if (threadIdx.x < 64) {
         const uint32_t lane = threadIdx.x;
-        const bool here = lane == 0 || (lane < cl.nmax && cl_load(cl.c->here + lane) != 0);
-        const uint64_t out = ~__ballot(here);
-        const uint32_t nb = out ? (uint32_t)__builtin_ctzll(out) : 64u;  // the first ones in a row
+        uint32_t nb = 1;
+        for (uint32_t spins = 0;; spins++) {
+            const bool here = lane == 0 || (lane < cl.nmax && cl_load(cl.c->here + lane) != 0);
+            const uint64_t out = ~__ballot(here);
+            nb = out ? (uint32_t)__builtin_ctzll(out) : 64u;  // the first ones in a row
+            // the first call gives helpers that are just starting a moment
+            if (j == 0 || cl.call || nb == cl.nmax || spins == CL_HERE_SPINS) break;
+        }
         const bool ok = j == 0 || (nb > 1 && R <= nb * share);
         if (lane == 0) {
-            cl.lds[0] = ok ? nb : 0u;
+            cl.l->w[0] = ok ? nb : 0u;
             if (ok) {
                 cl_store(cl.c->args, R);
                 cl_store(cl.c->args + 1, ld);
@@ -318,7 +355,7 @@ __device__ __forceinline__ bool cl_call(Cluster &cl, uint32_t j, uint32_t R, uin
         }
     }
     __syncthreads();
-    const uint32_t nb = uni(cl.lds[0]);
+    const uint32_t nb = uni(cl.l->w[0]);
     __syncthreads();
     if (!nb) return false;
     cl.nb = nb;
@@ -332,13 +369,13 @@ __device__ __forceinline__ bool cl_wait(Cluster &cl, uint32_t *j, uint32_t *R, u
     if (threadIdx.x < 64) {
         uint32_t lv = 0, nb = 0;
         bool dead = false;
-        if (threadIdx.x == 0) cl_store(cl.c->here + blockIdx.x, 1u);
+        if (threadIdx.x == 0) cl_store(cl.c->here + cl.bid, 1u);
         for (uint32_t spins = 1;; spins++) {
             const unsigned long long x = cl_load(&cl.c->call);
             const uint32_t n = uni((uint32_t)(x >> 32));
             lv = uni((uint32_t)x) >> 8;
             nb = uni((uint32_t)x) & 255u;
-            if (n != cl.call && (lv == 0 || nb > blockIdx.x)) {
+            if (n != cl.call && (lv == 0 || nb > cl.bid)) {
                 cl.call = n;
                 break;
             }
@@ -351,21 +388,21 @@ __device__ __forceinline__ bool cl_wait(Cluster &cl, uint32_t *j, uint32_t *R, u
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         if (dead && threadIdx.x == 0) cl_store(&cl.c->abort, 1u);
         if (threadIdx.x == 0) {
-            cl.lds[0] = dead ? 0u : lv;
-            cl.lds[1] = cl.call;
-            cl.lds[2] = nb;
+            cl.l->w[0] = dead ? 0u : lv;
+            cl.l->w[1] = cl.call;
+            cl.l->w[2] = nb;
 #pragma unroll
-            for (uint32_t t = 0; t < 4; t++) cl.lds[t + 3] = cl_load(cl.c->args + t);
+            for (uint32_t t = 0; t < 4; t++) cl.l->w[t + 3] = cl_load(cl.c->args + t);
         }
     }
     __syncthreads();
-    *j = uni(cl.lds[0]);
-    cl.call = uni(cl.lds[1]);
-    cl.nb = uni(cl.lds[2]);
-    *R = uni(cl.lds[3]);
-    *ld = uni(cl.lds[4]);
-    *mloc = uni(cl.lds[5]);
-    cl.epoch = uni(cl.lds[6]);
+    *j = uni(cl.l->w[0]);
+    cl.call = uni(cl.l->w[1]);
+    cl.nb = uni(cl.l->w[2]);
+    *R = uni(cl.l->w[3]);
+    *ld = uni(cl.l->w[4]);
+    *mloc = uni(cl.l->w[5]);
+    cl.epoch = uni(cl.l->w[6]);
     __syncthreads();
     return *j != 0;
 }
@@ -403,14 +440,17 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
     // of global memory; M then has column stride R.  M sits at index
     // next ^ 1 of its space (global or LDS), M' goes to index `next`.
     constexpr uint32_t MT = fused_table_words<FT, XS>();
-    // a longer list does not fit whatever the others are; CR of them sum to
-    // less than 2^32
-    constexpr uint32_t MAX_BOUND = 0xFFFFFFFFu / CR - 1;
-    static_assert(MAX_BOUND > CS, "a list that is cut does not fit");
+    // A row of a shared level weighs its slots and PAD: a share of CS weight
+    // then has rows that s_F can hold, whatever their lists.
+    constexpr uint32_t PAD = CL ? 5 : 0;
+    static_assert(!CL || CS / PAD + 2 <= CR, "rows of a share");
+    constexpr uint32_t SHARE_ROWS = CL ? CL_CAP_ROWS / CL_MAX_WG : CR;  // rows a workgroup locates
+    static_assert(SHARE_ROWS <= CR && (!CL || (uint64_t)SHARE_ROWS * (CL_MAX_WG * CS + 1 + PAD) < (1ull << 32)),
+                  "weights of the located rows");
     bool m_lds = false;
     uint32_t next = 0;
     const bool cluster = CL && cl->nmax > 1;
-    const uint32_t bid = CL ? blockIdx.x : 0u;
+    const uint32_t bid = CL ? cl->bid : 0u;
     bool wide = false;  // the level is shared
     // level j does not fit: record where, and where its input M lives (a
     // table in LDS is copied to buf0 for the caller)
@@ -440,7 +480,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             m_lds = false;
             mloc = 0;
         }
-        wide = cl_call(*cl, j, R, ld, mloc, cap_rows);
+        wide = cl_call(*cl, j, R, ld, mloc, SHARE_ROWS);
         next = mloc == 0 ? 1u : 0u;
     };
     // a wait ran out: the query starts over from its first table
@@ -468,10 +508,12 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             }
         }
         // the workgroup's rows of the table: Rw of them from row r0 (all but
-        // when the level is shared)
-        const uint32_t r0 = wide ? (uint32_t)((uint64_t)R * bid / cl->nb) : 0u;
-        const uint32_t Rw = wide ? (uint32_t)((uint64_t)R * (bid + 1) / cl->nb) - r0 : R;
-        const uint32_t *Mw = M + r0;
+        // when the level is shared), lookups of stride ls
+        uint32_t r0 = wide ? (uint32_t)((uint64_t)R * bid / cl->nb) : 0u;
+        uint32_t Rw = wide ? (uint32_t)((uint64_t)R * (bid + 1) / cl->nb) - r0 : R;
+        const uint32_t ls = R;
+        // a longer list does not fit whatever the others are
+        const uint32_t max_bound = (wide ? cl->nb * CS : CS) + 1;
         const uint32_t ne = uni(plan->lv_ne[j]), ef = uni(plan->lv_first[j]), e0 = uni(plan->lv_e0[j]);
         const uint64_t *Cu = uni(plan->Cu[j]);
         const bool final_level = (j == k - 1);
@@ -486,9 +528,9 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             uint32_t s0 = 0, l0 = 0, ob = NONE32, os = 0, ol = 0xFFFFFFFFu;
             for (uint32_t e = 0; e < ne; e++) {
                 const FEdge &ed = plan->edges[ef + e];
-                const uint32_t v = Mw[(uint64_t)uni(ed.col) * ld + i];
+                const uint32_t v = M[(uint64_t)uni(ed.col) * ld + r0 + i];
                 const uint2 r = pcsr_find(uni(ed.gl), uni(ed.G), uni(ed.H), v);
-                reinterpret_cast<uint2 *>(loc)[(uint64_t)e * Rw + i] = r;
+                reinterpret_cast<uint2 *>(loc)[(uint64_t)e * ls + r0 + i] = r;
                 if (e == e0) {
                     s0 = r.x;
                     l0 = r.y;
@@ -504,13 +546,13 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                 bs = os;
                 bl = ol;
             }
-            s_F[i] = bl < MAX_BOUND ? bl : MAX_BOUND;
+            s_F[i] = (bl < max_bound ? bl : max_bound) + (wide ? PAD : 0u);
             L.st[i] = plan->edges[ef + be].ci_off + bs;
-            if (ne > 1) loc[(uint64_t)(2 * ne) * Rw + i] = be;
+            if (ne > 1) loc[(uint64_t)(2 * ne) * ls + r0 + i] = be;
         }
         __syncthreads();
         // F = exclusive prefix sum of the bounds (each thread owns 4 rows)
-        {
+        auto scan_F = [&]() {
             uint32_t v4[4], sum = 0;
 #pragma unroll
             for (int q = 0; q < 4; q++) {
@@ -528,11 +570,83 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             }
             if (tid == 0) s_F[Rw] = tot;
             __syncthreads();
+        };
+        scan_F();
+        if (wide) {
+            // every part's weight
+            const uint32_t weight = uni(s_F[Rw]);
+            if (!cl_meet(*cl, false, weight)) {
+                give_up();
+                return;
+            }
+            const uint32_t nb = cl->nb;
+            const uint64_t T = uni(cl->l->pre[nb]);
+            if (tid == 0) L.s.lv[GSI_MAX_K + j] = (uint32_t)(T - (uint64_t)PAD * R);
+            if (T > (uint64_t)nb * CS) {
+                stop(j);
+                return;
+            }
+            if (T == (uint64_t)PAD * R) {  // no slots
+                if (tid == 0) {
+                    L.s.lv[2 * GSI_MAX_K + j] = 0;
+                    L.s.head[ST_LEVELS] = j;
+                    L.s.head[ST_DONE] = 1;
+                }
+                return;
+            }
+            // Parts differ: rows that follow each other often share a parent,
+            // a hub's list is in all of them, and the largest part was 4 to
+            // 10 times the mean on power-law graphs.  Where it is large, each
+            // workgroup takes an equal share of the weight instead, cut
+            // inside a row where it falls there.
+            if (uni(cl->l->w[1]) <= CL_EVEN) {
+                // the parts as they are; the padding goes
+                uint32_t f[2];
+                static_assert(!CL || SHARE_ROWS <= 2 * FT, "entries per thread");
+#pragma unroll
+                for (uint32_t q = 0; q < 2; q++) f[q] = s_F[tid + q * FT <= Rw ? tid + q * FT : 0u];
+                __syncthreads();
+                if (tid == 0 && Rw == 2 * FT) s_F[Rw] -= PAD * Rw;
+#pragma unroll
+                for (uint32_t q = 0; q < 2; q++)
+                    if (tid + q * FT <= Rw) s_F[tid + q * FT] = f[q] - PAD * (tid + q * FT);
+            } else {
+                uint32_t *gW = loc + (uint64_t)(2 * ne + 1) * ls, *gS = gW + ls, *gL = gS + ls;
+                for (uint32_t i = tid; i < Rw; i += FT) {
+                    const uint32_t f = s_F[i];
+                    gW[r0 + i] = f;
+                    gS[r0 + i] = L.st[i];
+                    gL[r0 + i] = s_F[i + 1] - f - PAD;
+                }
+                if (!cl_meet(*cl, true, weight)) {
+                    give_up();
+                    return;
+                }
+                const uint32_t wa = (uint32_t)(T * bid / nb), wb = (uint32_t)(T * (bid + 1) / nb);
+                if (w < 2) {
+                    const uint32_t r = wa == wb ? 0u : cl_row(*cl, gW, R, w ? wb - 1 : wa);
+                    if (lane == 0) cl->l->w[2 + w] = r;
+                }
+                __syncthreads();
+                r0 = uni(cl->l->w[2]);
+                Rw = wa == wb ? 0u : uni(cl->l->w[3]) + 1 - r0;
+                for (uint32_t i = tid; i < Rw; i += FT) {
+                    const uint32_t c = (uint32_t)(((uint64_t)(r0 + i + 1) * nb - 1) / R);  // the row's part
+                    const uint32_t wr = (uint32_t)cl->l->pre[c] + gW[r0 + i], len = gL[r0 + i];
+                    const uint32_t lo = wr > wa ? wr : wa, hi = wr + len < wb ? wr + len : wb;
+                    s_F[i] = hi > lo ? hi - lo : 0u;
+                    L.st[i] = gS[r0 + i] + (lo - wr);
+                }
+                __syncthreads();
+                scan_F();
+            }
+            __syncthreads();
         }
+        const uint32_t *Mw = M + r0;
         // values every thread reads from LDS are made wave-uniform, so that
         // the exits below are uniform branches
         const uint32_t gba = __builtin_amdgcn_readfirstlane(s_F[Rw]);
-        if (tid == 0) L.s.lv[GSI_MAX_K + j] = gba;
+        if (tid == 0 && !wide) L.s.lv[GSI_MAX_K + j] = gba;
         if (cluster && !wide && gba > CL_SLOTS && called != j) {
             go_wide(j);
             j--;  // the level again, shared (or alone)
@@ -542,7 +656,6 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             stop(j);
             return;
         }
-        const bool my_over = gba > cap_slots;  // (shared levels only)
         if (!wide && gba == 0) {
             if (tid == 0) {
                 L.s.lv[2 * GSI_MAX_K + j] = 0;
@@ -551,7 +664,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             }
             return;
         }
-        const uint32_t nw = my_over ? 0u : (gba + 63) / 64;
+        const uint32_t nw = (gba + 63) / 64;
 
         // join: keep x = N(v'_i, l0)[p - F[i]] iff x not in m_i, x in C(u),
         // x in every other linking list; one ballot word per 64 slots.  A
@@ -590,7 +703,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             if (ne < 2) return;
             uint32_t be[U];
 #pragma unroll
-            for (uint32_t r = 0; r < U; r++) be[r] = loc[(uint64_t)(2 * ne) * Rw + ir[r]];
+            for (uint32_t r = 0; r < U; r++) be[r] = loc[(uint64_t)(2 * ne) * ls + r0 + ir[r]];
             for (uint32_t e = 0; e < ne; e++) {
                 uint32_t st[U], len[U];
                 bool act[U], hit[U], any = false;
@@ -602,7 +715,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                 if (!any) continue;
 #pragma unroll
                 for (uint32_t r = 0; r < U; r++) {
-                    const uint2 sl = reinterpret_cast<const uint2 *>(loc)[(uint64_t)e * Rw + ir[r]];
+                    const uint2 sl = reinterpret_cast<const uint2 *>(loc)[(uint64_t)e * ls + r0 + ir[r]];
                     st[r] = sl.x;
                     len[r] = act[r] ? sl.y : 0u;
                 }
@@ -713,16 +826,14 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
         // the level's survivors, and this workgroup's place among them
         uint32_t off = 0, St = S;
         if (wide) {
-            uint32_t slots;
-            bool over;
-            if (!cl_meet(*cl, false, S, my_over ? 0u : gba, my_over, &off, &St, &slots, &over)) {
+            if (!cl_meet(*cl, false, S)) {
                 give_up();
                 return;
             }
-            if (tid == 0) L.s.lv[GSI_MAX_K + j] = over ? 0u : slots;
-            // a share of the next table has to fit as well
-            const uint32_t next_cap = cl->nb * cap_rows < cl->cap_rows ? cl->nb * cap_rows : cl->cap_rows;
-            if (over || St > (final_level ? (plan->count_only ? 0xFFFFFFFFu : cl->cap_out) : next_cap)) {
+            off = (uint32_t)uni(cl->l->pre[bid]);
+            St = (uint32_t)uni(cl->l->pre[cl->nb]);
+            const uint32_t next_cap = cl->nb * SHARE_ROWS < cl->cap_rows ? cl->nb * SHARE_ROWS : cl->cap_rows;
+            if (St > (final_level ? (plan->count_only ? 0xFFFFFFFFu : cl->cap_out) : next_cap)) {
                 stop(j);
                 return;
             }
@@ -864,9 +975,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                 }
             }
             if (wide) {
-                uint32_t u0, u1, u2;
-                bool u3;
-                if (!cl_meet(*cl, true, 0, 0, false, &u0, &u1, &u2, &u3)) {
+                if (!cl_meet(*cl, true, 0)) {
                     give_up();
                     return;
                 }
@@ -884,9 +993,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
         }
         // M' complete before it is read as M
         if (wide) {
-            uint32_t u0, u1, u2;
-            bool u3;
-            if (!cl_meet(*cl, true, 0, 0, false, &u0, &u1, &u2, &u3)) {
+            if (!cl_meet(*cl, true, 0)) {
                 give_up();
                 return;
             }
@@ -911,16 +1018,18 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
 // argument segment is read from host memory, a round trip of its own for
 // every line the levels touch); else d_plan in device memory.  Two
 // instances, not a select: a pointer that may address either space is
-// generic.  Workgroups after the first help with its larger levels (each
-// with its lookups at loc + its number * loc_stride).  At the end the status goes to `st` in one go and the completion
-// word is posted (post_seq) once every wave's rows and tables have left it.
-template <bool INL>
+// generic.  Workgroups after the first help with its larger levels.
+// At the end the status goes to `st` in one go and the completion word is
+// posted (post_seq) once every wave's rows and tables have left it.
+// CL: there are such workgroups (an instance of its own: what sharing adds to
+// a level alone cost 0.4 us of 7).
+template <bool INL, bool CL>
 __global__ __launch_bounds__(1024) void k_fused_levels(const FPlan *d_plan, FPlanArg inl, uint32_t j0, uint32_t *M0,
                                                       uint32_t R0, const uint32_t *b0_runs,
                                                       const uint64_t *b0, uint64_t nwords, uint32_t *buf0,
                                                       uint32_t *buf1, uint32_t *loc, uint32_t *out, FStatus *st,
                                                       uint64_t *seq_slot, uint64_t seq_value, ClusterCtl *ctl,
-                                                      uint32_t cl_rows, uint32_t cl_out, uint64_t loc_stride) {
+                                                      uint32_t cl_rows, uint32_t cl_out) {
     __shared__ FusedLevelsLds L;
     const FPlan *plan = INL ? &L.plan.p : d_plan;
     if (INL) {
@@ -964,17 +1073,16 @@ __global__ __launch_bounds__(1024) void k_fused_levels(const FPlan *d_plan, FPla
         }
     }
     __syncthreads();  // status cleared, plan copied and M0 written before the levels read them
-    Cluster cl{ctl, gridDim.x, 1u, cl_rows, cl_out, 0u, 0u, L.cl};
-    fused_query<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true, true>(plan, j0, M0, R0, R0, buf0, buf1,
-                                                                   loc + blockIdx.x * loc_stride, out, L.q, nullptr,
-                                                                   0, &cl);
+    Cluster cl{ctl, blockIdx.x, gridDim.x, 1u, cl_rows, cl_out, 0u, 0u, &L.cl};
+    fused_query<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true, CL>(plan, j0, M0, R0, R0, buf0, buf1, loc, out, L.q,
+                                                                 nullptr, 0, CL ? &cl : nullptr);
     if (blockIdx.x != 0) return;
     // every wave's stores are done before the first one releases them
     __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
     __syncthreads();
     st_flush(L.q.s, st);
     if (threadIdx.x == 0) post_seq(seq_slot, seq_value);
-    if (gridDim.x > 1) cl_call(cl, 0, 0, 0, 0, 0);  // the helpers leave
+    if (CL) cl_call(cl, 0, 0, 0, 0, 0);  // the helpers leave
 }
 
 void launch_fused(gsi_ctx *c, const FPlan *d_plan, const FPlanArg &inl, uint32_t j0, uint32_t *M0, uint32_t R0,
@@ -982,14 +1090,17 @@ void launch_fused(gsi_ctx *c, const FPlan *d_plan, const FPlanArg &inl, uint32_t
                   FStatus *d_status, double alg_bytes, const FusedCluster &fc) {
     uint64_t seqv = 0;
     uint64_t *seqp = seq_slot(c, d_status, &seqv);
-    if (d_plan)
-        launch(c, "k_fused_levels", alg_bytes, k_fused_levels<false>, fc.nb, 1024, d_plan, inl, j0, M0, R0, b0_runs, b0,
-               nwords, buf0, buf1, loc, out, d_status, seqp, seqv,
-               reinterpret_cast<ClusterCtl *>(fc.ctl), fc.cap_rows, fc.cap_out, fc.loc_stride);
-    else
-        launch(c, "k_fused_levels", alg_bytes, k_fused_levels<true>, fc.nb, 1024, d_plan, inl, j0, M0, R0, b0_runs, b0,
-               nwords, buf0, buf1, loc, out, d_status, seqp, seqv,
-               reinterpret_cast<ClusterCtl *>(fc.ctl), fc.cap_rows, fc.cap_out, fc.loc_stride);
+    const auto go = [&](auto kernel) {
+        launch(c, "k_fused_levels", alg_bytes, kernel, fc.nb, 1024, d_plan, inl, j0, M0, R0, b0_runs, b0, nwords, buf0,
+               buf1, loc, out, d_status, seqp, seqv, reinterpret_cast<ClusterCtl *>(fc.ctl), fc.cap_rows, fc.cap_out);
+    };
+    if (fc.nb > 1) {
+        if (d_plan) go(k_fused_levels<false, true>);
+        else go(k_fused_levels<true, true>);
+    } else {
+        if (d_plan) go(k_fused_levels<false, false>);
+        else go(k_fused_levels<true, false>);
+    }
     c->seq_armed = seqp != nullptr;
 }
 
@@ -1031,6 +1142,46 @@ static void launch_batch_t(gsi_ctx *c, uint32_t grid, const uint8_t *plans, cons
     launch(c, FT == 64 ? "k_fused_batch<64>" : FT == 256 ? "k_fused_batch<256>" : "k_fused_batch<1024>", bytes,
            k_fused_batch<FT, CR, CS>, grid, FT, plans, items, nitems, M0all, scratch, slot_words, kmax, outall, sts,
            counter);
+}
+
+// A few queries of a batch, each with nb workgroups of its own (one per CU
+// over the launch, see fused_clusters).  The first workgroups of all of them
+// come first in the grid, then every query's second one and so on.
+__global__ __launch_bounds__(1024) void k_fused_cluster(const uint8_t *plans, const FClusterItem *items, uint32_t nitems,
+                                                       uint32_t nb, const uint32_t *M0all, uint32_t *scratch,
+                                                       uint64_t slot_words, uint64_t table_words,
+                                                       uint64_t *ctl, uint32_t cl_rows, uint32_t cl_out,
+                                                       FStatus *sts) {
+    __shared__ FusedLds<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true> L;
+    __shared__ ClusterLds s_cl;
+    const uint32_t i = blockIdx.x % nitems, bid = blockIdx.x / nitems;
+    uint32_t *buf0 = scratch + i * slot_words, *buf1 = buf0 + table_words, *loc = buf1 + table_words;
+    const FClusterItem it = items[i];
+    st_clear(L.s);
+    __syncthreads();
+    Cluster cl{reinterpret_cast<ClusterCtl *>(ctl + (uint64_t)i * (CL_CTL_BYTES / 8)), bid, nb, 1u, cl_rows, cl_out, 0u, 0u, &s_cl};
+    fused_query<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true, true>(reinterpret_cast<const FPlan *>(plans + it.plan_off),
+                                                                   1, M0all + it.m0_off, it.R0, it.R0, buf0, buf1, loc,
+                                                                   it.out, L, nullptr, 0, &cl);
+    if (bid != 0) return;
+    __syncthreads();
+    st_flush(L.s, sts + i);
+    if (nb > 1) cl_call(cl, 0, 0, 0, 0, 0);  // the helpers leave
+}
+
+// Words of scratch of each query: two tables of clb_rows(nb) rows and every
+// the lookups.
+static uint32_t clb_rows(uint32_t nb) { return std::min<uint32_t>(CL_CAP_ROWS, nb * (CL_CAP_ROWS / CL_MAX_WG)); }
+uint64_t fused_cluster_words(uint32_t nb, uint32_t kmax) {
+    return 2ull * clb_rows(nb) * kmax + cluster_loc_words(kmax - 1, clb_rows(nb));
+}
+
+void launch_fused_cluster(gsi_ctx *c, uint32_t nb, const uint8_t *plans, const FClusterItem *items, uint32_t nitems,
+                          const uint32_t *M0all, uint32_t *scratch, uint32_t kmax, uint64_t *ctl, uint32_t cap_out,
+                          FStatus *sts) {
+    launch(c, "k_fused_cluster", 0.0, k_fused_cluster, nb * nitems, 1024, plans, items, nitems, nb, M0all, scratch,
+           fused_cluster_words(nb, kmax), (uint64_t)clb_rows(nb) * kmax,
+           ctl, clb_rows(nb), cap_out, sts);
 }
 
 // Chunks of one query (see launch_fused_chunks).  Every workgroup leaves

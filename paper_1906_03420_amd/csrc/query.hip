@@ -2283,8 +2283,8 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
     uint32_t fctl_used = 0;  // control blocks used
     uint64_t *fctl = reinterpret_cast<uint64_t *>(zeroed + 64);
     {
-        const uint64_t stride = fused_loc_words(max_ne, FUSED_MAX_ROWS);
-        const uint64_t need = 4 * (2ull * CL_CAP_ROWS * k + stride * CL_MAX_WG + (count_only ? 0ull : (uint64_t)CL_CAP_OUT * k));
+        const uint64_t lookups = cluster_loc_words(max_ne, CL_CAP_ROWS);
+        const uint64_t need = 4 * (2ull * CL_CAP_ROWS * k + lookups + (count_only ? 0ull : (uint64_t)CL_CAP_OUT * k));
         if (!max_rows && cap_rows == FUSED_MAX_ROWS && cap_slots == FUSED_MAX_SLOTS &&
             need <= c->arena.largest_free() / 16) {
             double rows = (double)R, slots = 0;
@@ -2302,7 +2302,6 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
             helpers_first = slots > CL_FEW_SLOTS;
             fc.cap_rows = CL_CAP_ROWS;
             fc.cap_out = CL_CAP_OUT;
-            fc.loc_stride = stride;
         }
     }
     // tables the workgroup (and its helpers) may be given
@@ -2315,7 +2314,8 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
             const uint64_t rows = fc.nb > 1 ? fc.cap_rows : cap_rows;
             fbuf0 = fs.get<uint32_t>(rows * k, "fused table 0");
             fbuf1 = fs.get<uint32_t>(rows * k, "fused table 1");
-            floc = fs.get<uint32_t>(fc.nb > 1 ? fc.loc_stride * fc.nb : fused_loc_words(max_ne, cap_rows),
+            floc = fs.get<uint32_t>(fc.nb > 1 ? cluster_loc_words(max_ne, fc.cap_rows)
+                                              : fused_loc_words(max_ne, cap_rows),
                                     "fused lookups");
             fdst = reinterpret_cast<FStatus *>(c->mbox_dev + MBOX_STATUS);
         }

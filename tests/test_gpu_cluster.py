@@ -42,6 +42,7 @@ CASES = [
     ([16] * 8192, 64, 0), ([130] * 1025, 40, 0),       # 131072 rows of a table and more
     ([120] * 1090, 1, 0), ([16] * 8192, 1, 0),
     ([6000], 1, 30000), ([10000] * 2, 1, 60000), ([40] * 300, 1, 100000),  # expected small
+    ([128] * 64, 1, 0), ([241] * 34, 1, 0),            # 8192 and 8194 slots
 ]
 
 
@@ -95,3 +96,36 @@ def test_shared_last_level_past_the_result_rows():
             a.free()
             b.free()
             dg.free()
+
+
+# (copies of the queries, chain): the most copies with several workgroups each
+# and one more, levels that fit only with more CUs per query, and none that fit
+@pytest.mark.parametrize("copies,case", [(1, 3), (1, 11), (2, 14), (5, 12), (16, 4), (16, 14), (9, 6), (16, 1), (17, 1),
+                                         (17, 5), (2, 17), (1, 15)])
+def test_batch_queries_with_several_workgroups(copies, case):
+    import paper_1906_03420_amd as gsi
+    fans, every, singles = CASES[case]
+    g, want, _ = chain(np.asarray(fans), every, singles)
+    two = [w.make_query([0, 1, 2, 3], [(0, 1), (1, 2), (2, 3)], [0, 1, 2]),
+           w.make_query([3, 2, 1], [(0, 1), (1, 2)], [2, 1])]
+    qs = two * copies
+    exact = [want[np.lexsort(want.T[::-1])]]
+    short = want[:, [3, 2, 1]]
+    exact.append(short[np.lexsort(short.T[::-1])])
+    print(copies, case, len(want), flush=True)
+    with gsi.Context(gsi.gsi_graph_bytes_needed(g.n, g.m) + (8 << 30)) as ctx:
+        dg = ctx.load(g)
+        for threads in (64, 256, 1024):
+            for flags in (0, gsi.GSI_COUNT_ONLY):
+                b = dg.batch(qs, flags=flags, threads=threads, grid_scale=8)
+                info = b.info()
+                assert info["empty"] + info["tier1"] + info["tier2"] + info["per_level"] == len(qs)
+                for i in range(len(qs)):
+                    assert b.count(i) == len(want) and b.digest(i) == b.digest(i & 1)
+                    if not flags and i < 4:
+                        np.testing.assert_array_equal(b.sorted_rows(i), exact[i & 1])
+                if flags == 0:
+                    digests = [b.digest(0), b.digest(1)]
+                assert [b.digest(0), b.digest(1)] == digests
+                b.free()
+        dg.free()
