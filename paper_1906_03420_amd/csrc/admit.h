@@ -79,9 +79,14 @@ struct AdmitStats {
 
 // Admits queries hq[i] (answers go to slots[i]): finished ones get their
 // slot filled; the others come back as WideQuery objects (tag = tags[i]).
+// clusters: a few queries the tiers leave run on several workgroups each.
+// The server does without: its engine steps advance those in flight as well,
+// and its small rounds took twice as long (R-MAT-22 saturation 11 980 q/s
+// without, 9 910 with).
 std::vector<WideQuery> admit_round(gsi_graph *g, const std::vector<const HostQuery *> &hq,
                                    const std::vector<Slot *> &slots, const std::vector<uint64_t> &tags,
-                                   bool count_only, bool levels_only, gsi_batch_schedule sched, AdmitStats *st);
+                                   bool count_only, bool levels_only, gsi_batch_schedule sched, bool clusters,
+                                   AdmitStats *st);
 
 // Moves a finished WideQuery's answer into its slot.
 void finish_slot(WideQuery &x, Slot &sl);

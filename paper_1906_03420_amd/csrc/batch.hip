@@ -220,7 +220,8 @@ void finish_slot(WideQuery &x, Slot &sl) {
 
 std::vector<WideQuery> admit_round(gsi_graph *g, const std::vector<const HostQuery *> &hq,
                                    const std::vector<Slot *> &slots, const std::vector<uint64_t> &tags,
-                                   bool count_only, bool levels_only, gsi_batch_schedule sched, AdmitStats *st) {
+                                   bool count_only, bool levels_only, gsi_batch_schedule sched, bool clusters,
+                                   AdmitStats *st) {
     gsi_ctx *c = g->ctx;
     const uint32_t nq = (uint32_t)hq.size();
     std::vector<WideQuery> wide;
@@ -301,6 +302,7 @@ std::vector<WideQuery> admit_round(gsi_graph *g, const std::vector<const HostQue
         planned.push_back(std::move(pl));
     }
 
+    const uint32_t max_roots = clusters ? CL_TAKE_ROWS : t2.cap_rows;
     std::vector<FusedQuery> fused;
     std::vector<uint8_t> plan_blob;
     std::vector<uint32_t> root_rows;
@@ -310,7 +312,7 @@ std::vector<WideQuery> admit_round(gsi_graph *g, const std::vector<const HostQue
         pl.m0_off = m0_total;
         m0_total += pl.R0;
         root_rows.push_back(qbase[pl.a] + pl.order[0]);
-        if (levels_only || pl.R0 > CL_TAKE_ROWS) continue;
+        if (levels_only || pl.R0 > max_roots) continue;
         uint32_t n_edges = 0;
         for (uint32_t j = 1; j < q.k; j++)
             for (uint32_t i = 0; i < j; i++)
@@ -402,7 +404,7 @@ std::vector<WideQuery> admit_round(gsi_graph *g, const std::vector<const HostQue
         // each; many go to the engine.  (Before the 1024-thread tier, in its
         // place: a batch of 131 small queries 0.57 -> 0.63 ms.)
         left2.insert(left2.end(), large.begin(), large.end());
-        for (uint32_t nb = 0; !left2.empty() && left2.size() <= CLB_MAX_QUERIES;) {
+        for (uint32_t nb = 0; clusters && !left2.empty() && left2.size() <= CLB_MAX_QUERIES;) {
             const uint32_t per = std::min<uint32_t>(CL_MAX_WG, (uint32_t)cu_count(c) / (uint32_t)left2.size());
             if (per < 2 || per < 2 * nb) break;
             nb = per;
@@ -413,7 +415,7 @@ std::vector<WideQuery> admit_round(gsi_graph *g, const std::vector<const HostQue
         for (auto &f : left2) to_wide.push_back(f.qi);
     }
     for (auto &pl : planned)
-        if (levels_only || pl.R0 > CL_TAKE_ROWS) to_wide.push_back(pl.qi);
+        if (levels_only || pl.R0 > max_roots) to_wide.push_back(pl.qi);
 
     // one-vertex queries: the root table is the answer
     for (uint32_t qi : single) {
@@ -493,7 +495,7 @@ gsi_batch *run_batch(gsi_graph *g, uint32_t nq, const gsi_query_desc *qd, uint32
     }
     AdmitStats as;
     std::vector<WideQuery> wq = admit_round(g, hp, sp, {}, b->count_only, (flags & GSI_BATCH_LEVELS_ONLY) != 0,
-                                            sched, &as);
+                                            sched, true, &as);
     auto tw0 = std::chrono::steady_clock::now();
     wide_run(g, wq, b->count_only, sched.engine_tiles);
     for (auto &x : wq) finish_slot(x, b->slots[x.qi]);

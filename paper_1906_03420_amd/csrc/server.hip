@@ -153,7 +153,7 @@ static uint32_t admit(gsi_server *s, std::vector<Request *> adm) {
         AdmitStats st;
         std::vector<WideQuery> wq;
         try {
-            wq = admit_round(s->g, hq, sl, tags, s->count_only, false, s->sched, &st);
+            wq = admit_round(s->g, hq, sl, tags, s->count_only, false, s->sched, false, &st);
         } catch (const Fail &f) {
             if (f.st != GSI_E_NOMEM) throw;
             clear_error();
