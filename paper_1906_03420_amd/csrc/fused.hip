@@ -120,8 +120,8 @@ constexpr uint32_t fused_table_words() {
 // (XS) each slot's element x, so that the link re-reads no list, and two
 // table buffers
 //
-// FusedStat: the words of an FStatus, its per-level sizes (all below 2^32
-// here) in 32 bits
+// FusedStat: the words of an FStatus, its per-level sizes in 32 bits (|GBA| of
+// a shared level that does not fit stops there; all others are below)
 enum : uint32_t { ST_DONE, ST_LEVEL, ST_ROWS, ST_MLOC, ST_LEVELS, ST_COUNT, ST_DIG0, ST_DIG1, ST_OUT_BASE, FSTAT_HEAD };
 struct FusedStat {
     uint64_t head[FSTAT_HEAD];
@@ -157,13 +157,18 @@ struct FusedLevelsLds {
 };
 static_assert(sizeof(FusedLevelsLds) <= 160 * 1024, "fused workgroup LDS");
 
-// A value every lane holds alike, in a scalar register.
+// A value every lane holds alike, in scalar registers.  No other type
+// converts to one of these: a 64-bit sum must not lose its upper half.
 __device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uni(uint64_t v) {
+    return ((uint64_t)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v);
+}
 template <typename T>
 __device__ __forceinline__ T *uni(T *p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    return reinterpret_cast<T *>(((uint64_t)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v));
+    return reinterpret_cast<T *>(uni(reinterpret_cast<uint64_t>(p)));
 }
+template <typename T>
+void uni(T) = delete;
 
 // What a workgroup reports of its query: kept in LDS while the levels run
 // and written out once at the end (st_flush).  A store to the status inside
@@ -580,8 +585,10 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
                 return;
             }
             const uint32_t nb = cl->nb;
+            // a part's weight is below 2^32, their sum is not
             const uint64_t T = uni(cl->l->pre[nb]);
-            if (tid == 0) L.s.lv[GSI_MAX_K + j] = (uint32_t)(T - (uint64_t)PAD * R);
+            const uint64_t slots = T - (uint64_t)PAD * R;
+            if (tid == 0) L.s.lv[GSI_MAX_K + j] = slots < NONE32 ? (uint32_t)slots : NONE32;
             if (T > (uint64_t)nb * CS) {
                 stop(j);
                 return;
