@@ -148,7 +148,7 @@ static std::vector<FusedQuery> run_clusters(gsi_graph *g, const std::vector<Slot
     const uint32_t n = (uint32_t)list.size();
     uint32_t kmax = 2;
     uint64_t out_words = 0;
-    const uint32_t cap_out = std::min<uint32_t>(CL_CAP_OUT, nb * (CL_CAP_OUT / CL_MAX_WG));
+    const uint32_t cap_out = cluster_result_rows(nb);
     for (auto &f : list) {
         kmax = std::max(kmax, ks[f.qi]);
         out_words += count_only ? 0 : (uint64_t)cap_out * ks[f.qi];

@@ -170,6 +170,17 @@ constexpr double CL_FEW_SLOTS = 512;
 // of them left after the 1024-thread tier: 2.51 -> 1.87 ms.
 constexpr uint32_t CLB_MAX_QUERIES = 32;
 constexpr uint64_t CL_CTL_BYTES = 4096;    // control block, zeroed before the launch
+// Rows of a table and of the result of a batch query that nb workgroups run:
+// their shares of the single query's, and no fewer than the first one writes
+// when no helper has checked in and it runs a level alone.
+constexpr uint32_t cluster_table_rows(uint32_t nb) {
+    const uint32_t rows = nb * (CL_CAP_ROWS / CL_MAX_WG);
+    return rows < FUSED_MAX_ROWS ? FUSED_MAX_ROWS : rows < CL_CAP_ROWS ? rows : CL_CAP_ROWS;
+}
+constexpr uint32_t cluster_result_rows(uint32_t nb) {
+    const uint32_t rows = nb * (CL_CAP_OUT / CL_MAX_WG);
+    return rows < FUSED_MAX_SLOTS ? FUSED_MAX_SLOTS : rows < CL_CAP_OUT ? rows : CL_CAP_OUT;
+}
 struct FusedCluster {
     uint32_t nb = 1;          // workgroups (1: no helpers)
     void *ctl = nullptr;

@@ -1176,19 +1176,18 @@ __global__ __launch_bounds__(1024) void k_fused_cluster(const uint8_t *plans, co
     if (nb > 1) cl_call(cl, 0, 0, 0, 0, 0);  // the helpers leave
 }
 
-// Words of scratch of each query: two tables of clb_rows(nb) rows and every
-// the lookups.
-static uint32_t clb_rows(uint32_t nb) { return std::min<uint32_t>(CL_CAP_ROWS, nb * (CL_CAP_ROWS / CL_MAX_WG)); }
+// Words of scratch of each query: two tables of cluster_table_rows(nb) rows
+// and the lookups.
 uint64_t fused_cluster_words(uint32_t nb, uint32_t kmax) {
-    return 2ull * clb_rows(nb) * kmax + cluster_loc_words(kmax - 1, clb_rows(nb));
+    return 2ull * cluster_table_rows(nb) * kmax + cluster_loc_words(kmax - 1, cluster_table_rows(nb));
 }
 
 void launch_fused_cluster(gsi_ctx *c, uint32_t nb, const uint8_t *plans, const FClusterItem *items, uint32_t nitems,
                           const uint32_t *M0all, uint32_t *scratch, uint32_t kmax, uint64_t *ctl, uint32_t cap_out,
                           FStatus *sts) {
     launch(c, "k_fused_cluster", 0.0, k_fused_cluster, nb * nitems, 1024, plans, items, nitems, nb, M0all, scratch,
-           fused_cluster_words(nb, kmax), (uint64_t)clb_rows(nb) * kmax,
-           ctl, clb_rows(nb), cap_out, sts);
+           fused_cluster_words(nb, kmax), (uint64_t)cluster_table_rows(nb) * kmax, ctl, cluster_table_rows(nb),
+           cap_out, sts);
 }
 
 // Chunks of one query (see launch_fused_chunks).  Every workgroup leaves
