@@ -2312,18 +2312,26 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
     // tables the workgroup (and its helpers) may be given
     const uint64_t take_rows = fc.nb > 1 ? CL_TAKE_ROWS : cap_rows;
     const double take_slots = fc.nb > 1 ? (double)CL_TAKE_SLOTS : (double)cap_slots;
+    // Between two runs of the kernel its buffers go back to the arena, for the
+    // per-level kernels' levels are the large ones; M may be in one of them.
+    auto drop_fused = [&]() {
+        for (uint32_t **p : {&fbuf0, &fbuf1, &floc})
+            if (*p && *p != M) {
+                fs.drop(*p);
+                *p = nullptr;
+            }
+    };
     auto run_fused = [&](uint32_t j0, const uint64_t *root_bits, uint32_t &stop) -> bool {
         if (!fhp) {
             finl.reset(new FPlanArg());
             fdplan = fused_plan(cap_rows, cap_slots, &fhp, finl.get());
-            const uint64_t rows = fc.nb > 1 ? fc.cap_rows : cap_rows;
-            fbuf0 = fs.get<uint32_t>(rows * k, "fused table 0");
-            fbuf1 = fs.get<uint32_t>(rows * k, "fused table 1");
-            floc = fs.get<uint32_t>(fc.nb > 1 ? cluster_loc_words(max_ne, fc.cap_rows)
-                                              : fused_loc_words(max_ne, cap_rows),
-                                    "fused lookups");
             fdst = reinterpret_cast<FStatus *>(c->mbox_dev + MBOX_STATUS);
         }
+        const uint64_t rows = fc.nb > 1 ? fc.cap_rows : cap_rows;
+        fbuf0 = fs.get<uint32_t>(rows * k, "fused table 0");
+        fbuf1 = fs.get<uint32_t>(rows * k, "fused table 1");
+        floc = fs.get<uint32_t>(fc.nb > 1 ? cluster_loc_words(max_ne, fc.cap_rows) : fused_loc_words(max_ne, cap_rows),
+                                "fused lookups");
         uint32_t *out =
             count_only ? nullptr : persist<uint32_t>(c, (uint64_t)(fc.nb > 1 ? fc.cap_out : cap_slots) * k, "result rows");
         res->rows = out;
@@ -2374,6 +2382,11 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
         R = hs->rows;
         if (hs->mloc == 0) M = fbuf0;
         else if (hs->mloc == 1) M = fbuf1;
+        drop_fused();
+        if (hs->mloc != FSTATUS_IN_FIRST) {
+            c->arena.shrink(M, R * stop * 4);
+            Mb.reset();  // the table the kernel was given
+        }
         return false;
     };
     const bool fused_ok = !(flags & GSI_NO_FUSED) && cap_slots >= 64;
@@ -2648,6 +2661,7 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
             Mb.p = Mn.p;
             Mn.p = nullptr;
             M = a.Mn;
+            drop_fused();
             Mld = gba;
             R = S;
             continue;  // the fused workgroup is not taken back after a one-pass level
@@ -2743,6 +2757,7 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
         Mb.p = Mn.p;
         Mn.p = nullptr;
         M = a.Mn;
+        drop_fused();
         Mld = 0;
         slots_per_row = (double)gba / (double)R;
         R = S;
