@@ -2209,6 +2209,7 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
         FChunkSummary *hsum = reinterpret_cast<FChunkSummary *>(reinterpret_cast<char *>(c->pinned) + 4096);
         GSI_HIP(hipMemcpyAsync(hsum, dsum, sizeof(FChunkSummary), hipMemcpyDeviceToHost, c->stream));
         sync(c);
+        cs.drop(slots);  // the levels of the chunks left may need the room
         if ((c->flags & GSI_CTX_PROFILE) && ri < c->recs.size())
             c->recs[ri].bytes = fused_bytes(hp, (uint32_t)hsum->levels, hsum->lv_rows, hsum->lv_gba,
                                             hsum->lv_surv);
