@@ -2525,6 +2525,16 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
             S = sc[0];
             gba = sc[2];
             joined = gba <= cap;
+            if (!joined) {  // the level is joined again, in the whole arena
+                ls.drop(a.rec_x);
+                ls.drop(a.rec_r);
+                ls.drop(a.tile_cnt);
+                ls.drop(toff);
+                ls.drop(const_cast<uint64_t *>(a.tile_row));
+                a.rec_x = a.rec_r = a.tile_cnt = nullptr;
+                a.tile_off = nullptr;
+                a.tile_row = nullptr;
+            }
             sc[0] = prof ? sc[3] : 0;
         } else {
             read_scalars(c, dscal + 3, sc, 2);

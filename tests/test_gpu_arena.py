@@ -1,5 +1,6 @@
 """Queries in arenas that hold their largest level and little else: what the
-fused kernels use is given back before the per-level kernels run."""
+fused kernels use is given back before the per-level kernels run, and so is
+what a join turned out too small for its level was launched with."""
 import numpy as np
 import pytest
 import torch  # noqa: F401  (its HIP runtime is loaded before the library)
@@ -33,4 +34,33 @@ def test_largest_level_fits(graph, k, count_only, kib):
         r = dg.query(q, flags=gsi.GSI_COUNT_ONLY | gsi.GSI_NO_FUSED)
         assert (count, digest) == (r.count, r.digest)
         r.free()
+        dg.free()
+
+
+def test_level_joined_twice_fits():
+    """1,024 roots with 470 leaves each where 64 slots a row are expected: the
+    join sized for 65,536 slots leaves the room of its records to the one that
+    takes all 481,280.  Kept results XX."""
+    import paper_1906_03420_amd as gsi
+    roots, fan, free = 1024, 470, 4_500_000
+    a = np.repeat(np.arange(roots), fan)
+    b = roots + np.arange(roots * fan)
+    g = w.make_graph(roots + roots * fan, np.repeat([0, 1], [roots, roots * fan]), np.stack([a, b], 1),
+                     [0] * len(a), "fans")
+    pair = w.make_query([0, 1], [(0, 1)], [0])
+    size = gsi.gsi_graph_bytes_needed(g.n, g.m)
+    with gsi.Context(size) as ctx:
+        dg = ctx.load(g)
+        kept = []
+        for lab, rows in ((1, roots * fan), (0, roots)):
+            q = w.make_query([lab], [], [])
+            while size - ctx.memory()[0] - 4 * rows >= free:
+                kept.append(dg.query(q))
+                assert kept[-1].count == rows
+        r = dg.query(pair, flags=gsi.GSI_NO_FUSED, order=[0, 1])
+        assert r.stats()["gba"][1] == len(a)
+        np.testing.assert_array_equal(r.rows(), np.stack([a, b], 1))
+        r.free()
+        for r in kept:
+            r.free()
         dg.free()
