@@ -870,6 +870,7 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
         Scratch s(c);
         std::vector<WQ> hq(nq);
         std::vector<WEdge> he;
+        std::vector<WFilter> fl;  // lists filtered this step
         // per-step allocations of the queries, released unless the step
         // commits; declared after the host arrays so that, on a failure, the
         // stream has drained the copies out of them before they go
@@ -968,7 +969,6 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
             uint64_t *d_qg = s.get<uint64_t>(nq, "wide slots per query");
             launch(c, "k_wgba", 16.0 * nq, k_wgba, wblocks(nq), WT, (const WQ *)d_q, nq, (const uint64_t *)F, d_qg);
             read_words(c, d_qg, qg, nq);
-            std::vector<WFilter> fl;
             uint64_t words = 0, els = 0, blk = 0, rblk = 0, saved = 0;
             const uint64_t room = c->arena.largest_free() / 4;
             for (uint32_t a = 0; a < nq; a++) {
