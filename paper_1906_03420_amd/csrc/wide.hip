@@ -861,9 +861,10 @@ __global__ __launch_bounds__(WT) void k_wlink_bits(const WQ *qs, const uint32_t 
 
 // One join level for the queries in `act` (all of them, or none: on an
 // allocation failure everything allocated for the step is given back and
-// no query changes state).  records: survivors as records where they fit.
-static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool count_only, uint32_t tpw,
-                      bool records) {
+// no query changes state).  records: survivors as records where they fit;
+// filter: lists rescanned many times over are filtered first.
+static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool count_only, uint32_t tpw, bool records,
+                      bool filter) {
     gsi_ctx *c = g->ctx;
     {
         const uint32_t nq = (uint32_t)act.size();
@@ -964,7 +965,7 @@ static void wide_step(gsi_graph *g, const std::vector<WideQuery *> &act, bool co
         }
         // queries whose rows rescan their first edge's lists many times over:
         // filter those lists by C(u) once
-        if ((double)gba > least && gba >= WF_MIN_SLOTS) {
+        if (filter && (double)gba > least && gba >= WF_MIN_SLOTS) {
             std::vector<uint64_t> qg;
             uint64_t *d_qg = s.get<uint64_t>(nq, "wide slots per query");
             launch(c, "k_wgba", 16.0 * nq, k_wgba, wblocks(nq), WT, (const WQ *)d_q, nq, (const uint64_t *)F, d_qg);
@@ -1185,19 +1186,21 @@ uint32_t WideEngine::step() {
     uint64_t est = 0;
     while (n < act.size() && (n == 0 || est + step_bytes(*act[n]) <= room)) est += step_bytes(*act[n++]);
     size_t skipped = 0;  // queries moved behind the others (tolerant engine)
-    bool records = true;
+    bool records = true, filter = true;
     for (;;) {
         std::vector<WideQuery *> part(act.begin(), act.begin() + n);
         try {
-            wide_step(g_, part, count_only_, tpw_, records);
+            wide_step(g_, part, count_only_, tpw_, records, filter);
             steps_++;
             break;
         } catch (const Fail &f) {
-            if (f.st != GSI_E_NOMEM || (n == 1 && !records && !tolerant_)) throw;
+            if (f.st != GSI_E_NOMEM || (n == 1 && !filter && !tolerant_)) throw;
             clear_error();
-            if (n == 1 && records) {
-                // what the records took may be what the next table lacked
-                records = false;
+            if (n == 1 && filter) {
+                // what the records took may be what the next table lacked,
+                // then what the filtered lists took
+                if (records) records = false;
+                else filter = false;
                 continue;
             }
             if (n > 1) {
@@ -1217,7 +1220,7 @@ uint32_t WideEngine::step() {
             act.erase(act.begin());
             act.push_back(x);
             skipped++;
-            records = true;
+            records = filter = true;
         }
     }
     uint32_t done = 0;

@@ -2,6 +2,7 @@
 with filtered lists: allocations that fail before, between and after the
 step's uploads leave it in order; every arena gives the right answer or is
 refused, and none is refused above one that was enough."""
+import numpy as np
 import pytest
 import torch  # noqa: F401  (its HIP runtime is loaded before the library)
 
@@ -53,3 +54,40 @@ def test_filtered_steps_in_tight_arenas():
     # several queries, whose tables wait while others advance: a step of all, of
     # half of them, of one, or refused; there is room for all in the end
     assert any([run(hi + t * hi // 4, 3) for t in range(1, 17)])
+
+
+def test_step_that_fits_without_filtered_lists_only():
+    """28 a's joined to 160,000 b's, each b to eight c's of which one is asked
+    for, and that one to a w.  At the c's a table of 4.48 * 10^6 rows scans
+    eight elements each, fourteen times the label's entries, so the lists are
+    filtered (11 MB); the next table takes 54 MB.  Kept results fill the arena
+    up to 243.5 MB, in which the step fits without them."""
+    import paper_1906_03420_amd as gsi
+    na, nb, dc, free = 28, 160_000, 8, 243_500_000
+    b = na + np.arange(nb)
+    c = na + nb + np.arange(nb * dc)
+    x = na + nb + nb * dc + np.arange(nb)
+    e = np.concatenate([np.stack([np.repeat(np.arange(na), nb), np.tile(b, na)], 1),
+                        np.stack([np.repeat(b, dc), c], 1), np.stack([c[::dc], x], 1)])
+    vl = np.concatenate([np.zeros(na), np.ones(nb), np.where(np.arange(nb * dc) % dc == 0, 2, 4), np.full(nb, 3)])
+    g = w.make_graph(len(vl), vl.astype(np.int64), e, [0] * (na * nb) + [1] * (nb * dc) + [2] * nb, "three levels")
+    q = w.make_query([0, 1, 2, 3], [(0, 1), (1, 2), (2, 3)], [0, 1, 2])
+    size = gsi.gsi_graph_bytes_needed(g.n, g.m)
+    with gsi.Context(size) as ctx:
+        dg = ctx.load(g)
+        want = dg.query(q, flags=gsi.GSI_COUNT_ONLY)
+        digest = want.digest
+        assert want.count == na * nb
+        want.free()
+        kept = []
+        for lab, rows in ((4, nb * (dc - 1)), (1, nb), (0, na)):
+            one = w.make_query([lab], [], [])
+            while size - ctx.memory()[0] - 4 * rows >= free:
+                kept.append(dg.query(one))
+                assert kept[-1].count == rows
+        out = dg.batch([q], flags=gsi.GSI_COUNT_ONLY | gsi.GSI_BATCH_LEVELS_ONLY, threads=256, grid_scale=8)
+        assert out.count(0) == na * nb and out.digest(0) == digest
+        out.free()
+        for r in kept:
+            r.free()
+        dg.free()
