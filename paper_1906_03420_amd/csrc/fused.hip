@@ -854,6 +854,11 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             return;
         }
         if (!wide && !final_level && S > cap_rows) {
+            if (cluster && called != j) {
+                go_wide(j);
+                j--;  // the level again, shared: its table may be larger
+                continue;
+            }
             stop(j);
             return;
         }
