@@ -100,19 +100,19 @@ void launch_fused_batch(gsi_ctx *c, const FTier &t, uint32_t grid, const uint8_t
                         uint32_t *outall, FStatus *sts, uint32_t *counter, double bytes);
 
 // A few queries of a batch, each run by nb workgroups as in the single-query
-// kernel (`ctl`: a zeroed control block per query).  Its last level may have
-// cap_out rows, written to `out`.
+// kernel (`ctl`: a zeroed control block per query), from level j0 of a table.
+// Its last level may have cap_out rows, written to `out`; a query that does
+// not fit leaves the table it stopped at in its first or one of its buffers.
 struct FClusterItem {
     uint64_t plan_off;  // byte offset of its FPlan in the plan buffer
-    uint64_t m0_off;    // first root row in the concatenated root tables
+    uint32_t *M;        // R rows x j0 columns, column stride R
+    uint32_t *buf0, *buf1;  // tables (cluster_table_rows(nb) x k words)
+    uint32_t *loc;      // lookups (cluster_loc_words)
     uint32_t *out;      // cap_out x k words (null: count only)
-    uint32_t R0;        // root rows
-    uint32_t pad;
+    uint32_t R, j0;
 };
-uint64_t fused_cluster_words(uint32_t nb, uint32_t kmax);  // scratch of each query
 void launch_fused_cluster(gsi_ctx *c, uint32_t nb, const uint8_t *plans, const FClusterItem *items, uint32_t nitems,
-                          const uint32_t *M0all, uint32_t *scratch, uint32_t kmax, uint64_t *ctl, uint32_t cap_out,
-                          FStatus *sts);
+                          uint64_t *ctl, uint32_t cap_out, FStatus *sts);
 
 // One query split into chunks of `chunk_rows` rows of its table M0 (R0
 // rows, j0 columns, column stride R0; the rows of M are independent at
@@ -156,6 +156,9 @@ constexpr uint32_t CL_ROWS = 1024, CL_SLOTS = 8192;
 constexpr uint32_t CL_EVEN = 4096;
 constexpr uint32_t CL_CAP_ROWS = 131072;   // rows of a shared level's table (fewer than 2^22)
 constexpr uint32_t CL_CAP_OUT = 262144;    // result rows
+// A row of a shared level weighs its slots and this, so that a share of equal
+// weight has rows that a workgroup can hold, whatever their lists.
+constexpr uint32_t CL_ROW_WEIGHT = 5;
 // A table is handed to the kernel when it has at most this many rows and, at
 // the slots per row of the level before, this many slots; a level past the
 // 2^20 that 64 workgroups hold is run twice.  131072 and 524288 slots
@@ -169,6 +172,7 @@ constexpr double CL_FEW_SLOTS = 512;
 // tier takes 120 and each level of the engine 100.  A batch of 48 queries, 16
 // of them left after the 1024-thread tier: 2.51 -> 1.87 ms.
 constexpr uint32_t CLB_MAX_QUERIES = 32;
+constexpr uint32_t CLB_PASSES = 3;
 constexpr uint64_t CL_CTL_BYTES = 4096;    // control block, zeroed before the launch
 // Rows of a table and of the result of a batch query that nb workgroups run:
 // their shares of the single query's, and no fewer than the first one writes

@@ -445,9 +445,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
     // of global memory; M then has column stride R.  M sits at index
     // next ^ 1 of its space (global or LDS), M' goes to index `next`.
     constexpr uint32_t MT = fused_table_words<FT, XS>();
-    // A row of a shared level weighs its slots and PAD: a share of CS weight
-    // then has rows that s_F can hold, whatever their lists.
-    constexpr uint32_t PAD = CL ? 5 : 0;
+    constexpr uint32_t PAD = CL ? CL_ROW_WEIGHT : 0;
     static_assert(!CL || CS / PAD + 2 <= CR, "rows of a share");
     constexpr uint32_t SHARE_ROWS = CL ? CL_CAP_ROWS / CL_MAX_WG : CR;  // rows a workgroup locates
     static_assert(SHARE_ROWS <= CR && (!CL || (uint64_t)SHARE_ROWS * (CL_MAX_WG * CS + 1 + PAD) < (1ull << 32)),
@@ -840,6 +838,7 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             off = (uint32_t)uni(cl->l->pre[bid]);
             St = (uint32_t)uni(cl->l->pre[cl->nb]);
             const uint32_t next_cap = cl->nb * SHARE_ROWS < cl->cap_rows ? cl->nb * SHARE_ROWS : cl->cap_rows;
+            if (tid == 0) L.s.lv[2 * GSI_MAX_K + j] = St;
             if (St > (final_level ? (plan->count_only ? 0xFFFFFFFFu : cl->cap_out) : next_cap)) {
                 stop(j);
                 return;
@@ -1156,24 +1155,21 @@ static void launch_batch_t(gsi_ctx *c, uint32_t grid, const uint8_t *plans, cons
            counter);
 }
 
-// A few queries of a batch, each with nb workgroups of its own (one per CU
-// over the launch, see fused_clusters).  The first workgroups of all of them
-// come first in the grid, then every query's second one and so on.
+// A few queries of a batch, each with nb workgroups of its own (at most one
+// per CU over the launch).  The first workgroups of all of them come first in
+// the grid, then every query's second one and so on.
 __global__ __launch_bounds__(1024) void k_fused_cluster(const uint8_t *plans, const FClusterItem *items, uint32_t nitems,
-                                                       uint32_t nb, const uint32_t *M0all, uint32_t *scratch,
-                                                       uint64_t slot_words, uint64_t table_words,
-                                                       uint64_t *ctl, uint32_t cl_rows, uint32_t cl_out,
+                                                       uint32_t nb, uint64_t *ctl, uint32_t cl_rows, uint32_t cl_out,
                                                        FStatus *sts) {
     __shared__ FusedLds<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true> L;
     __shared__ ClusterLds s_cl;
     const uint32_t i = blockIdx.x % nitems, bid = blockIdx.x / nitems;
-    uint32_t *buf0 = scratch + i * slot_words, *buf1 = buf0 + table_words, *loc = buf1 + table_words;
     const FClusterItem it = items[i];
     st_clear(L.s);
     __syncthreads();
     Cluster cl{reinterpret_cast<ClusterCtl *>(ctl + (uint64_t)i * (CL_CTL_BYTES / 8)), bid, nb, 1u, cl_rows, cl_out, 0u, 0u, &s_cl};
     fused_query<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true, true>(reinterpret_cast<const FPlan *>(plans + it.plan_off),
-                                                                   1, M0all + it.m0_off, it.R0, it.R0, buf0, buf1, loc,
+                                                                   it.j0, it.M, it.R, it.R, it.buf0, it.buf1, it.loc,
                                                                    it.out, L, nullptr, 0, &cl);
     if (bid != 0) return;
     __syncthreads();
@@ -1181,18 +1177,10 @@ __global__ __launch_bounds__(1024) void k_fused_cluster(const uint8_t *plans, co
     if (nb > 1) cl_call(cl, 0, 0, 0, 0, 0);  // the helpers leave
 }
 
-// Words of scratch of each query: two tables of cluster_table_rows(nb) rows
-// and the lookups.
-uint64_t fused_cluster_words(uint32_t nb, uint32_t kmax) {
-    return 2ull * cluster_table_rows(nb) * kmax + cluster_loc_words(kmax - 1, cluster_table_rows(nb));
-}
-
 void launch_fused_cluster(gsi_ctx *c, uint32_t nb, const uint8_t *plans, const FClusterItem *items, uint32_t nitems,
-                          const uint32_t *M0all, uint32_t *scratch, uint32_t kmax, uint64_t *ctl, uint32_t cap_out,
-                          FStatus *sts) {
-    launch(c, "k_fused_cluster", 0.0, k_fused_cluster, nb * nitems, 1024, plans, items, nitems, nb, M0all, scratch,
-           fused_cluster_words(nb, kmax), (uint64_t)cluster_table_rows(nb) * kmax, ctl, cluster_table_rows(nb),
-           cap_out, sts);
+                          uint64_t *ctl, uint32_t cap_out, FStatus *sts) {
+    launch(c, "k_fused_cluster", 0.0, k_fused_cluster, nb * nitems, 1024, plans, items, nitems, nb, ctl,
+           cluster_table_rows(nb), cap_out, sts);
 }
 
 // Chunks of one query (see launch_fused_chunks).  Every workgroup leaves

@@ -22,6 +22,8 @@ struct WideQuery {
     const uint32_t *M = nullptr;          // current table (column-major)
     uint64_t R = 0;
     void *own = nullptr;                  // arena block of M when owned
+    const uint32_t *root = nullptr;       // first table (kept alive by `keep`) and its rows
+    uint64_t root_rows = 0;
     void *next = nullptr;
     bool done = false;
     gsi_status status = GSI_OK;           // GSI_E_NOMEM: a level did not fit alone
@@ -34,6 +36,15 @@ struct WideQuery {
     void release_table() {
         if (own) ctx->arena.release(own);
         own = nullptr;
+    }
+    // back to the first table, where that gives memory back
+    bool restart() {
+        if (done || !own || !root) return false;
+        release_table();
+        M = root;
+        R = root_rows;
+        j = 1;
+        return true;
     }
     void finish_empty() {
         release_table();
@@ -53,6 +64,7 @@ struct WideQuery {
     WideQuery &operator=(WideQuery &&o) noexcept {
         ctx = o.ctx; q = o.q; qi = o.qi; tag = o.tag; keep = std::move(o.keep); order = std::move(o.order); e0src = std::move(o.e0src); cand = std::move(o.cand);
         col = std::move(o.col); Cu = std::move(o.Cu); j = o.j; M = o.M; R = o.R; own = o.own; next = o.next;
+        root = o.root; root_rows = o.root_rows;
         done = o.done; status = o.status; count = o.count; digest[0] = o.digest[0]; digest[1] = o.digest[1]; rows = o.rows;
         levels = o.levels;
         for (int i = 0; i < GSI_MAX_K; i++) {
@@ -75,8 +87,10 @@ struct WideQuery {
 // Holds queries in flight; each step() advances the active ones by one
 // join level in shared launches (a prefix of them when the arena cannot
 // hold a step for all: a step that fails to allocate is retried on half as
-// many queries, the others keep their state).  A query whose level does not
-// fit even alone raises GSI_E_NOMEM, or, in a tolerant engine, is moved
+// many queries, the others keep their state).  When the first query's level
+// does not fit even alone, the others go back to their first tables (the
+// first one advances at every step, so that ends); if that gives nothing it
+// raises GSI_E_NOMEM, or, in a tolerant engine, is moved
 // behind the others; when it is the only query left it is finished with
 // status GSI_E_NOMEM.
 class WideEngine {

@@ -1194,7 +1194,16 @@ uint32_t WideEngine::step() {
             steps_++;
             break;
         } catch (const Fail &f) {
-            if (f.st != GSI_E_NOMEM || (n == 1 && !filter && !tolerant_)) throw;
+            if (f.st != GSI_E_NOMEM) throw;
+            if (n == 1 && !filter && !tolerant_) {
+                // the tables of the others may be what it lacks
+                bool freed = false;
+                for (size_t i = 1; i < act.size(); i++) freed |= act[i]->restart();
+                if (!freed) throw;
+                records = filter = true;
+                clear_error();
+                continue;
+            }
             clear_error();
             if (n == 1 && filter) {
                 // what the records took may be what the next table lacked,
