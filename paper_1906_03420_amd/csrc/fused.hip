@@ -121,7 +121,7 @@ constexpr uint32_t fused_table_words() {
 // table buffers
 //
 // FusedStat: the words of an FStatus, its per-level sizes in 32 bits (|GBA| of
-// a shared level that does not fit stops there; all others are below)
+// a level that does not fit stops there; all others are below)
 enum : uint32_t { ST_DONE, ST_LEVEL, ST_ROWS, ST_MLOC, ST_LEVELS, ST_COUNT, ST_DIG0, ST_DIG1, ST_OUT_BASE, FSTAT_HEAD };
 struct FusedStat {
     uint64_t head[FSTAT_HEAD];
@@ -658,6 +658,19 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             continue;
         }
         if (!wide && gba > cap_slots) {
+            // what the level does hold, for who runs it next: the lists' full
+            // lengths (each thread reads the rows that it located)
+            uint64_t sum = 0;
+            for (uint32_t i = tid; i < R; i += FT)
+                sum += reinterpret_cast<const uint2 *>(loc)[(uint64_t)(ne > 1 ? loc[(uint64_t)(2 * ne) * ls + i] : 0u) * ls + i].y;
+            sum = wave_sum(sum);
+            if (lane == 0) L.d[0][w] = sum;
+            __syncthreads();
+            if (tid == 0) {
+                uint64_t all = 0;
+                for (uint32_t q = 0; q < FT / 64; q++) all += L.d[0][q];
+                L.s.lv[GSI_MAX_K + j] = all < NONE32 ? (uint32_t)all : NONE32;
+            }
             stop(j);
             return;
         }

@@ -2492,8 +2492,9 @@ gsi_result *run_query(gsi_graph *g, const HostQuery &q, const gsi_query_options 
         // The join before |GBA| is known: launched for up to `cap` slots, it
         // reads |GBA| on the device, its tile counts are scanned, and the
         // host waits once for both sums instead of once for each.  The cap
-        // is four times the last level's slots per row (the fused workgroup
-        // reports the exact |GBA| of the level it stopped at), and never
+        // is four times the last level's slots per row (or the |GBA| that the
+        // fused kernel reports of the level it stopped at: exact, or of a
+        // shared level a bound from below that few lists pass), and never
         // above the |GBA| from which the level's lists would be filtered; a
         // level expected to take wide tiles waits for its |GBA|.  One that
         // turns out larger than its cap is joined again below.
