@@ -65,6 +65,14 @@ typedef struct gsi_result gsi_result;
 
 /* Context flags */
 #define GSI_CTX_PROFILE 0x1u  /* time every kernel launch with HIP events */
+/* Test only: what the workgroups that share a query's levels do when some of
+ * them are not there.  Every kernel still ends by itself, and the results are
+ * the same. */
+#define GSI_CTX_TEST_NO_HELPERS 0x100u   /* no helper checks in: the first
+                                            workgroup runs the levels alone */
+#define GSI_CTX_TEST_SHORT_WAITS 0x200u  /* a wait runs out after 64 polls, not 65536 */
+#define GSI_CTX_TEST_QUIT(n) ((uint32_t)(n) << 16)  /* n in 1..255: the second
+                                            workgroup leaves at its n-th meeting */
 
 typedef struct {
     int32_t device;       /* HIP device ordinal of the arena */

@@ -21,6 +21,8 @@ GSI_OK, GSI_E_INVALID, GSI_E_NOMEM, GSI_E_DEVICE, GSI_E_CAPACITY, GSI_E_BUSY, GS
 GSI_MAX_K = 32
 GSI_SIG_WORDS = 16
 GSI_CTX_PROFILE = 0x1
+GSI_CTX_TEST_NO_HELPERS = 0x100
+GSI_CTX_TEST_SHORT_WAITS = 0x200
 GSI_GRAPH_TEST_FEW_HOME_GROUPS = 0x1
 GSI_COUNT_ONLY = 0x1
 GSI_FILTER_LABEL_ONLY = 0x2

@@ -212,6 +212,20 @@ __device__ __forceinline__ void st_flush(const FusedStat &s, FStatus *st) {
 constexpr uint32_t CL_SPINS = 1u << 16;  // about 50 ms
 constexpr uint32_t CL_HERE_SPINS = 16;   // about 10 us
 
+// How long the workgroups wait and whether they are there: other values than
+// these in tests only, by the context's flags.
+struct ClusterWaits {
+    uint32_t spins = CL_SPINS;  // polls after which a wait runs out
+    uint32_t quit = 0;          // the meeting at which workgroup 1 leaves, or CL_ABSENT
+};
+constexpr uint32_t CL_ABSENT = 0xFFFFFFFFu;  // no helper checks in
+static ClusterWaits cluster_waits(const gsi_ctx *c) {
+    ClusterWaits w;
+    if (c->flags & GSI_CTX_TEST_SHORT_WAITS) w.spins = 64;
+    w.quit = c->flags & GSI_CTX_TEST_NO_HELPERS ? CL_ABSENT : (c->flags >> 16) & 255u;
+    return w;
+}
+
 // One atomic word carries a workgroup's epoch and its value, so the values
 // need no fence.  Two sets of words: a workgroup writes epoch e + 2 only after
 // all have read epoch e.
@@ -233,6 +247,7 @@ struct Cluster {
     uint32_t cap_rows;  // rows of a shared level's table
     uint32_t cap_out;   // result rows
     uint32_t epoch, call;
+    ClusterWaits waits;
     ClusterLds *l;
 };
 
@@ -261,13 +276,13 @@ __device__ __forceinline__ bool cl_meet(Cluster &cl, bool table, uint32_t value)
         const uint32_t lane = threadIdx.x;
         if (lane == 0) cl_store(w + cl.bid, ((unsigned long long)e << 32) | value);
         unsigned long long x = 0;
-        bool ok = lane >= cl.nb, dead = false;
-        for (uint32_t spins = 1; __ballot(!ok); spins++) {
+        bool ok = lane >= cl.nb, dead = cl.bid == 1 && e == cl.waits.quit;
+        for (uint32_t spins = 1; !dead && __ballot(!ok); spins++) {
             if (!ok) {
                 x = cl_load(w + lane);
                 ok = (uint32_t)(x >> 32) == e;
             }
-            if (spins > CL_SPINS || ((spins & 63) == 0 && uni(cl_load(&cl.c->abort)))) {
+            if (spins > cl.waits.spins || ((spins & 63) == 0 && uni(cl_load(&cl.c->abort)))) {
                 dead = true;
                 break;
             }
@@ -374,7 +389,7 @@ __device__ __forceinline__ bool cl_wait(Cluster &cl, uint32_t *j, uint32_t *R, u
     if (threadIdx.x < 64) {
         uint32_t lv = 0, nb = 0;
         bool dead = false;
-        if (threadIdx.x == 0) cl_store(cl.c->here + cl.bid, 1u);
+        if (threadIdx.x == 0 && cl.waits.quit != CL_ABSENT) cl_store(cl.c->here + cl.bid, 1u);
         for (uint32_t spins = 1;; spins++) {
             const unsigned long long x = cl_load(&cl.c->call);
             const uint32_t n = uni((uint32_t)(x >> 32));
@@ -384,7 +399,7 @@ __device__ __forceinline__ bool cl_wait(Cluster &cl, uint32_t *j, uint32_t *R, u
                 cl.call = n;
                 break;
             }
-            if (spins > CL_SPINS || ((spins & 63) == 0 && uni(cl_load(&cl.c->abort)))) {
+            if (spins > cl.waits.spins || ((spins & 63) == 0 && uni(cl_load(&cl.c->abort)))) {
                 dead = true;
                 break;
             }
@@ -1053,7 +1068,7 @@ __global__ __launch_bounds__(1024) void k_fused_levels(const FPlan *d_plan, FPla
                                                       const uint64_t *b0, uint64_t nwords, uint32_t *buf0,
                                                       uint32_t *buf1, uint32_t *loc, uint32_t *out, FStatus *st,
                                                       uint64_t *seq_slot, uint64_t seq_value, ClusterCtl *ctl,
-                                                      uint32_t cl_rows, uint32_t cl_out) {
+                                                      uint32_t cl_rows, uint32_t cl_out, ClusterWaits waits) {
     __shared__ FusedLevelsLds L;
     const FPlan *plan = INL ? &L.plan.p : d_plan;
     if (INL) {
@@ -1097,7 +1112,7 @@ __global__ __launch_bounds__(1024) void k_fused_levels(const FPlan *d_plan, FPla
         }
     }
     __syncthreads();  // status cleared, plan copied and M0 written before the levels read them
-    Cluster cl{ctl, blockIdx.x, gridDim.x, 1u, cl_rows, cl_out, 0u, 0u, &L.cl};
+    Cluster cl{ctl, blockIdx.x, gridDim.x, 1u, cl_rows, cl_out, 0u, 0u, waits, &L.cl};
     fused_query<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true, CL>(plan, j0, M0, R0, R0, buf0, buf1, loc, out, L.q,
                                                                  nullptr, 0, CL ? &cl : nullptr);
     if (blockIdx.x != 0) return;
@@ -1116,7 +1131,8 @@ void launch_fused(gsi_ctx *c, const FPlan *d_plan, const FPlanArg &inl, uint32_t
     uint64_t *seqp = seq_slot(c, d_status, &seqv);
     const auto go = [&](auto kernel) {
         launch(c, "k_fused_levels", alg_bytes, kernel, fc.nb, 1024, d_plan, inl, j0, M0, R0, b0_runs, b0, nwords, buf0,
-               buf1, loc, out, d_status, seqp, seqv, reinterpret_cast<ClusterCtl *>(fc.ctl), fc.cap_rows, fc.cap_out);
+               buf1, loc, out, d_status, seqp, seqv, reinterpret_cast<ClusterCtl *>(fc.ctl), fc.cap_rows, fc.cap_out,
+               cluster_waits(c));
     };
     if (fc.nb > 1) {
         if (d_plan) go(k_fused_levels<false, true>);
@@ -1173,14 +1189,15 @@ static void launch_batch_t(gsi_ctx *c, uint32_t grid, const uint8_t *plans, cons
 // the grid, then every query's second one and so on.
 __global__ __launch_bounds__(1024) void k_fused_cluster(const uint8_t *plans, const FClusterItem *items, uint32_t nitems,
                                                        uint32_t nb, uint64_t *ctl, uint32_t cl_rows, uint32_t cl_out,
-                                                       FStatus *sts) {
+                                                       ClusterWaits waits, FStatus *sts) {
     __shared__ FusedLds<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true> L;
     __shared__ ClusterLds s_cl;
     const uint32_t i = blockIdx.x % nitems, bid = blockIdx.x / nitems;
     const FClusterItem it = items[i];
     st_clear(L.s);
     __syncthreads();
-    Cluster cl{reinterpret_cast<ClusterCtl *>(ctl + (uint64_t)i * (CL_CTL_BYTES / 8)), bid, nb, 1u, cl_rows, cl_out, 0u, 0u, &s_cl};
+    Cluster cl{reinterpret_cast<ClusterCtl *>(ctl + (uint64_t)i * (CL_CTL_BYTES / 8)), bid, nb, 1u, cl_rows, cl_out, 0u, 0u,
+               waits, &s_cl};
     fused_query<1024, FUSED_MAX_ROWS, FUSED_MAX_SLOTS, true, true>(reinterpret_cast<const FPlan *>(plans + it.plan_off),
                                                                    it.j0, it.M, it.R, it.R, it.buf0, it.buf1, it.loc,
                                                                    it.out, L, nullptr, 0, &cl);
@@ -1193,7 +1210,7 @@ __global__ __launch_bounds__(1024) void k_fused_cluster(const uint8_t *plans, co
 void launch_fused_cluster(gsi_ctx *c, uint32_t nb, const uint8_t *plans, const FClusterItem *items, uint32_t nitems,
                           uint64_t *ctl, uint32_t cap_out, FStatus *sts) {
     launch(c, "k_fused_cluster", 0.0, k_fused_cluster, nb * nitems, 1024, plans, items, nitems, nb, ctl,
-           cluster_table_rows(nb), cap_out, sts);
+           cluster_table_rows(nb), cap_out, cluster_waits(c), sts);
 }
 
 // Chunks of one query (see launch_fused_chunks).  Every workgroup leaves
