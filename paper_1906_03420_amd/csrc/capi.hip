@@ -312,8 +312,9 @@ gsi_status gsi_graph_bytes_needed(uint32_t n, uint64_t m, uint64_t *out) {
         // persistent: signatures 64 B per vertex, at most one 128 B group per
         // directed edge, ci 4 B per directed edge
         uint64_t persistent = 64ull * n + 128ull * d + 4ull * d;
-        // build scratch (see build_graph): sort buffers 6 x 4 B, scans 3 x 8 B
-        // and the per-run / per-group arrays, bounded by directed edges
+        // build scratch (see build_graph), bounded by directed edges: two arrays
+        // of 8-byte sort keys (six of 4 bytes when entries do not pack into
+        // one) and the per-run and per-group arrays
         uint64_t scratch = d * (24 + 8) + d * 96 + 4ull * n + (64ull << 20);
         *out = persistent + scratch;
     })

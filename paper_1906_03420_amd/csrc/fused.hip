@@ -621,15 +621,10 @@ __device__ __forceinline__ void fused_query(const FPlan *plan, uint32_t j0, cons
             // inside a row where it falls there.
             if (uni(cl->l->w[1]) <= CL_EVEN) {
                 // the parts as they are; the padding goes
-                uint32_t f[2];
-                static_assert(!CL || SHARE_ROWS <= 2 * FT, "entries per thread");
-#pragma unroll
-                for (uint32_t q = 0; q < 2; q++) f[q] = s_F[tid + q * FT <= Rw ? tid + q * FT : 0u];
+                static_assert(!CL || CL_EVEN / CL_ROW_WEIGHT < FT, "rows of a part");
+                const uint32_t f = s_F[tid <= Rw ? tid : 0u];
                 __syncthreads();
-                if (tid == 0 && Rw == 2 * FT) s_F[Rw] -= PAD * Rw;
-#pragma unroll
-                for (uint32_t q = 0; q < 2; q++)
-                    if (tid + q * FT <= Rw) s_F[tid + q * FT] = f[q] - PAD * (tid + q * FT);
+                if (tid <= Rw) s_F[tid] = f - PAD * tid;
             } else {
                 uint32_t *gW = loc + (uint64_t)(2 * ne + 1) * ls, *gS = gW + ls, *gL = gS + ls;
                 for (uint32_t i = tid; i < Rw; i += FT) {

@@ -67,13 +67,13 @@ __host__ __device__ __forceinline__ bool in_sorted(const uint32_t *list, uint32_
 // is compared, so a thread waits for one chain of dependent loads instead
 // of U.  A pair whose range is already down to 9 (or an empty list) probes
 // base[lo] again, a valid address: base[0] when the list is empty, which
-// every label holding an edge has.  With VEC (the per-level join), the
+// every label holding an edge has.  With VEC (every join uses it), the
 // last <= 9 elements are read as three aligned 16-byte words (12 elements
 // from the 16-byte boundary at or below base + lo), 3 vector loads instead
 // of 8 scalar ones: the join is bound by the address units, which pay per
 // load instruction.  The window may read up to CI_PAD elements past the
 // array's last list.  Without VEC the last <= 8 elements are read one by
-// one (fewer registers: the engine's join holds four pairs).
+// one: fewer registers, for a caller that holds more searches at once.
 template <uint32_t U, bool VEC = true, uint32_t A = 8>
 __host__ __device__ __forceinline__ void in_sorted_many(const uint32_t *base, const uint32_t *st, const uint32_t *len,
                                                const uint32_t *x, bool *hit) {
