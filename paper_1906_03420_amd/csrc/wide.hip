@@ -695,8 +695,7 @@ __global__ __launch_bounds__(WT) void k_wlink(const WQ *__restrict__ qs, const u
     }
 }
 
-// The same from keep bits, for steps whose records would not fit: (m_i, x) of every survivor into its query's next table, or, at a query's
-// last level, the row in query-vertex order and its hash.  A workgroup
+// The same from keep bits, for steps whose records would not fit.  A workgroup
 // takes the same WJ_TILES consecutive tiles as the join: their kept slots
 // are listed in slot order in LDS first, so that the waves that gather,
 // write and hash are dense, and survivor q of the list is survivor
@@ -796,41 +795,8 @@ __global__ __launch_bounds__(WT) void k_wlink_bits(const WQ *qs, const uint32_t 
             if (pos < Q.S) {  // always, when the survivor ranges are consistent
                 const uint32_t st0 = (one && staged) ? s_st[lr] : loc[Q.locbase + (uint64_t)(2 * Q.ne) * Q.R + i];
                 const uint32_t x = Q.ci[st0 + (uint32_t)(p - Fr)];
-                // the row's values are loaded eight at a time, every load
-                // issued before any is used (clamped columns: valid
-                // addresses), not one dependent round trip per column
-                if (!Q.final_level) {
-                    for (uint32_t c = 0; c < Q.j; c += 8) {
-                        uint32_t m[8];
-#pragma unroll
-                        for (uint32_t k4 = 0; k4 < 8; k4++)
-                            m[k4] = Q.M[(uint64_t)(c + k4 < Q.j ? c + k4 : Q.j - 1) * Q.R + i];
-#pragma unroll
-                        for (uint32_t k4 = 0; k4 < 8; k4++)
-                            if (c + k4 < Q.j) Q.Mn[(uint64_t)(c + k4) * Q.S + pos] = m[k4];
-                    }
-                    Q.Mn[(uint64_t)Q.j * Q.S + pos] = x;
-                } else {
-                    uint64_t f = 14695981039346656037ull;
-                    for (uint32_t u0 = 0; u0 < Q.k; u0 += 8) {
-                        uint32_t val[8];
-#pragma unroll
-                        for (uint32_t k4 = 0; k4 < 8; k4++) {
-                            const uint32_t qc = Q.qcol[u0 + k4 < GSI_MAX_K ? u0 + k4 : GSI_MAX_K - 1];
-                            const uint32_t c = u0 + k4 < Q.k ? qc : Q.j;
-                            const uint32_t mv = Q.M[(uint64_t)(c < Q.j ? c : 0u) * Q.R + i];
-                            val[k4] = c < Q.j ? mv : x;
-                        }
-#pragma unroll
-                        for (uint32_t k4 = 0; k4 < 8; k4++) {
-                            const uint32_t u = u0 + k4;
-                            if (u >= Q.k) break;
-                            if (stage) s_rows[local * Q.k + u] = val[k4];
-                            else if (Q.out) Q.out[pos * Q.k + u] = val[k4];
-                            f = fnv_word(f, val[k4]);
-                        }
-                    }
-                    const uint64_t h = mix64(f);
+                const uint64_t h = link_row(Q, i, x, pos, stage ? s_rows + local * Q.k : nullptr);
+                if (Q.final_level) {
                     if (one) {
                         hs += h;
                         hx ^= h;
