@@ -7,14 +7,15 @@
 //   tier 1   persistent fused launch, workgroups of the scheduled size pull
 //            queries from a shared counter and run all levels per query
 //   tier 2   what tier 1 could not hold, in 1024-thread workgroups
+//   clusters a few queries that are left then, several workgroups each
 //   rest     the level-synchronous engine (wide.hip), all at once
 //
 // The schedule (tier-1 workgroup size, launched occupancy) is chosen by the
 // autotuner, which times every candidate on a sample of the batch.
 #include <algorithm>
 #include <chrono>
-#include <map>
 #include <cstring>
+#include <map>
 #include <memory>
 
 #include "admit.h"

@@ -168,9 +168,10 @@ constexpr uint32_t CL_TAKE_ROWS = 32768, CL_TAKE_SLOTS = 131072;
 // them a query of 16 rows takes 78 us instead of 73.
 constexpr double CL_FEW_SLOTS = 512;
 // A batch's remaining queries run with several workgroups each when they are
-// at most this many (8 CUs each): a pass takes 150 us where the 1024-thread
-// tier takes 120 and each level of the engine 100.  A batch of 48 queries, 16
-// of them left after the 1024-thread tier: 2.51 -> 1.87 ms.
+// at most this many (8 CUs each): a pass takes 100 to 200 us where the
+// 1024-thread tier takes 120 and each level of the engine 100.  A batch of 48
+// queries, 16 of them left after the 1024-thread tier: 2.51 -> 1.78 ms.  At most
+// CLB_PASSES passes, each with more workgroups a query (run_left).
 constexpr uint32_t CLB_MAX_QUERIES = 32;
 constexpr uint32_t CLB_PASSES = 3;
 constexpr uint64_t CL_CTL_BYTES = 4096;    // control block, zeroed before the launch
