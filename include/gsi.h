@@ -407,9 +407,9 @@ typedef struct {
  * Algorithm 4) in LDS-staged form.  A first tier uses workgroups of
  * `threads` threads (64, 256 or 1024; tables of up to 4x`threads` rows and
  * 16x`threads` |GBA| slots per level); queries it cannot hold rerun in a
- * second tier of 1024-thread workgroups, then, when at most 32 are left, on
- * several such workgroups each, and the rest run level-synchronously
- * together.  `grid_scale` (1..8) multiplies the number of
+ * second tier of 1024-thread workgroups, then, when at most 32 are left and
+ * none is known to need more than 64, on several such workgroups each, and the
+ * rest run level-synchronously together, from the levels they have reached.  `grid_scale` (1..8) multiplies the number of
  * resident workgroups per compute unit that is launched, in eighths. */
 typedef struct {
     uint32_t threads;     /* first-tier workgroup size: 64, 256 or 1024 */
